@@ -95,6 +95,10 @@ enum {
  *                     mfg_fp8_scale_offset(rows, ld), by ceil(rows/128) x
  *                     ceil(cols/128) FP32 tile scales, row-major.
  *   F32               ignores the flag.
+ * 16-bit operands whose rows are 16-byte aligned (base and ld a multiple of
+ * 8 elements) are read in whole 16-byte pieces, which may touch up to 14
+ * bytes past a row's last element (inside the same aligned 16 bytes, never
+ * another page); those bytes never reach a result.
  */
 enum {
     MFG_F32 = 0,

@@ -189,7 +189,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.M = M, a.N = N, a.K = kk, a.C = C, a.ldc = ldc, a.alpha = alpha, a.beta = beta;
         a.A[0] = a0, a.B[0] = b0, a.lda = kk, a.ldb = ldn;
         const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(kk, ldn);
-        return launch_gemm16(K_BF16, choose_split6(config, M, N, K, ldc, vec), a, 1, vec, s);
+        return launch_gemm16(K_BF16, choose_split6(config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
     }
 
     // 16-bit modes
@@ -222,7 +222,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.lda = lda, a.ldb = ldb;
         const bool vec =
             al16(A) && al16(B) && lda % 8 == 0 && ldb % 8 == 0 && buffer_ldc_ok(ldc) && operand_ld_ok(lda, ldb);
-        return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s);
+        return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
     }
     const int64_t ldk = up(K, 8), ldn = up(N, 8);
     const int64_t pa_elems = M * ldk, pb_elems = K * ldn;
@@ -238,7 +238,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     if ((st = convert16(m, K, N, static_cast<const float*>(B), ldb, b0, b1, ldn, npb(m) == 2, s)) != MFG_OK) return st;
     a.A[0] = a0, a.A[1] = a1, a.B[0] = b0, a.B[1] = b1, a.lda = ldk, a.ldb = ldn;
     const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(ldk, ldn);  // workspace planes: aligned, ld a multiple of 8
-    return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s);
+    return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
 }
 
 }  // namespace mfg
@@ -422,7 +422,7 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
         vec = buffer_ldc_ok(ldc) && operand_ld_ok(ldk, ldn);
     }
     if (M <= 32 && N <= 32) return launch_batched_small(kind, a, count, vec, device_cu_count(), s);
-    const int cfg = vec ? pick_config16(kind, M, N, K, vec) : 0;
+    const int cfg = vec ? pick_config16(kind, M, N, K, vec, count) : 0;
     for (int64_t b0 = 0; b0 < count; b0 += 65535) {
         Gemm16Args c = a;
         for (int q = 0; q < 2; ++q) {
@@ -430,7 +430,7 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
             if (c.B[q]) c.B[q] += b0 * a.sB;
         }
         c.C = C + b0 * strideC;
-        if ((st = launch_gemm16(kind, cfg, c, std::min<int64_t>(65535, count - b0), vec, s)) != MFG_OK) return st;
+        if ((st = launch_gemm16(kind, cfg, c, std::min<int64_t>(65535, count - b0), vec, s, true)) != MFG_OK) return st;
     }
     return MFG_OK;
 }

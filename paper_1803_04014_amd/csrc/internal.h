@@ -78,8 +78,13 @@ enum Kind16 { K_F16 = 0, K_BF16 = 1, K_REFINE_A = 2, K_SPLIT3 = 3, K_SPLIT4 = 4,
 // Tile configurations (index 0 is always the simple one-wave-per-32x32 kernel).
 int num_configs16(int kind);
 const char* config16_name(int kind, int cfg);
-int pick_config16(int kind, int64_t M, int64_t N, int64_t K, bool vec_ok);
-int launch_gemm16(int kind, int cfg, const Gemm16Args& a, int64_t batch, bool vec_ok, hipStream_t s);
+int pick_config16(int kind, int64_t M, int64_t N, int64_t K, bool vec_ok, int64_t batch = 1);
+// The tile variant of the ring kernels for a problem (launch_ring's menu).
+int pick_ring16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch);
+// any_k: cfg came from pick_config16, whose choices serve any K and N; an
+// explicit or tuned cfg of the fast and pipelined kernels needs whole stages.
+int launch_gemm16(int kind, int cfg, const Gemm16Args& a, int64_t batch, bool vec_ok, hipStream_t s,
+                  bool any_k = false);
 // Whether a configuration serves a problem (its launch would not return
 // MFG_ERR_UNSUPPORTED); a tuned choice that does not is replaced by the
 // default.  vec_ok: 16-byte aligned rows of A and B (FP8: of A's codes).

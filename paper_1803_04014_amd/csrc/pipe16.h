@@ -372,6 +372,25 @@ __device__ __forceinline__ void pipe64_load(const uint16_t* const (&Ap)[2], cons
     }
 }
 
+// 16 zero bytes: what a lane whose piece lies at or past K loads.
+__device__ const uint32_t kZeros16[4] __attribute__((aligned(16))) = {0, 0, 0, 0};
+
+// The last stage has landed in `st` and K % 8 != 0: clear A's elements at or
+// past K in the piece that straddles it (`kl` = K columns of the stage).
+// Every thread of the workgroup calls it; the caller's barrier follows.
+template <class G, int BM>
+__device__ __forceinline__ void clear_straddle(uint16_t* st, int kl, int tid) {
+    const int c = kl >> 3, keep = kl & 7;
+    for (int e = tid; e < G::NPA * BM; e += G::NT) {
+        const int q = e / BM, row = e % BM;
+        u32x4* p = reinterpret_cast<u32x4*>(st + q * G::A_PLANE + row * 64 + ((c ^ swz<8>(row)) * 8));
+        u32x4 v = *p;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) v[d] &= (2 * d < keep ? 0xFFFFu : 0u) | (2 * d + 1 < keep ? 0xFFFF0000u : 0u);
+        *p = v;
+    }
+}
+
 // The same loads with their addressing split into a per-lane part fixed for
 // the whole K loop and a per-stage part that is the same in every lane.  Each
 // lane's byte offset from the tile's corner (A: row m0, column 0 of the stage;
@@ -382,19 +401,36 @@ __device__ __forceinline__ void pipe64_load(const uint16_t* const (&Ap)[2], cons
 // wavefront index made visibly uniform, so a load costs one address add
 // instead of a 64-bit multiply per lane.  Same sources, same LDS layout and
 // the same instruction order as pipe64_load.
-template <int KIND, int BM, int BN, int WM, int WN, int S>
+//
+// RAG: K need not be a multiple of 64.  Pieces of A at or past K and rows of
+// B at or past K are loaded from kZeros16 instead (a compare and a select
+// per load, which the variant for whole stages does without).
+template <int KIND, int BM, int BN, int WM, int WN, int S, bool RAG>
 struct P64Loader {
     using G = Pipe64Cfg<KIND, BM, BN, WM, WN, S>;
     const char* a[2];  // tile corner of each A plane, row m0 (same in every lane)
     const char* b[2];  // of each B plane, column n0
     int64_t ldb2;      // B row pitch in bytes
+    int64_t K;         // RAG only
     int wid;           // this wavefront's index (scalar)
     uint32_t offa[G::A_INSTR];
     uint32_t offb[G::B_INSTR];
+    int lane;
+
+    __device__ __forceinline__ int ka(int i) const {  // K column of the lane's A piece i in a stage
+        const int row = (wid * G::A_INSTR + i) * 8 + (lane >> 3);
+        return ((lane & 7) ^ swz<8>(row)) * 8;
+    }
+    __device__ __forceinline__ int kb(int i) const {  // K row of its B piece i
+        return (wid * G::B_INSTR + i) * G::B_ROWS_PER_INSTR + lane / G::B_CPR;
+    }
 
     __device__ __forceinline__ void init(const uint16_t* const (&Ap)[2], const uint16_t* const (&Bp)[2], int64_t lda,
-                                         int64_t ldb, int64_t M, int64_t N, int64_t m0, int64_t n0, int wid_, int lane) {
+                                         int64_t ldb, int64_t M, int64_t N, int64_t K_, int64_t m0, int64_t n0,
+                                         int wid_, int lane_) {
         wid = __builtin_amdgcn_readfirstlane(wid_);
+        lane = lane_;
+        if constexpr (RAG) K = uniform64(K_);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             a[q] = (const char*)uniform64((int64_t)(Ap[q] ? Ap[q] + m0 * lda : nullptr));
@@ -404,27 +440,32 @@ struct P64Loader {
 #pragma unroll
         for (int i = 0; i < G::A_INSTR; ++i) {
             const int row = (wid * G::A_INSTR + i) * 8 + (lane >> 3);
-            const int c = (lane & 7) ^ swz<8>(row);
             const int64_t gm = m0 + row < M ? m0 + row : M - 1;
-            offa[i] = (uint32_t)(((gm - m0) * lda + c * 8) * 2);
+            offa[i] = (uint32_t)(((gm - m0) * lda + ka(i)) * 2);
         }
+        // B pieces past N are clamped to the row's last whole 16 bytes: N
+        // rounded up to 8 is at most ldb, a multiple of 8
+        const int64_t n8 = (N + 7) / 8 * 8;
 #pragma unroll
         for (int i = 0; i < G::B_INSTR; ++i) {
-            const int krow = (wid * G::B_INSTR + i) * G::B_ROWS_PER_INSTR + lane / G::B_CPR;
+            const int krow = kb(i);
             const int c = (lane % G::B_CPR) ^ swzB(krow);
-            const int64_t gn = n0 + c * 8 + 8 <= N ? n0 + c * 8 : N - 8;
+            const int64_t gn = n0 + c * 8 < n8 ? n0 + c * 8 : n8 - 8;
             offb[i] = (uint32_t)((krow * ldb + (gn - n0)) * 2);
         }
     }
 
     // The loads of the stage starting at column (A) / row (B) k0 into `st`.
     __device__ __forceinline__ void load(int64_t k0, uint16_t* st) const {
-        const int64_t ka = uniform64(k0 * 2), kb = uniform64(k0 * ldb2);
+        const int64_t ko = uniform64(k0 * 2), kb2 = uniform64(k0 * ldb2);
+        int kl = 64;
+        if constexpr (RAG) kl = (int)min(uniform64(K - k0), (int64_t)64);
+        auto at = [&](const char* p, bool in) { return (const void*)(!RAG || in ? p : (const char*)kZeros16); };
 #pragma unroll
         for (int q = 0; q < G::NPA; ++q)
 #pragma unroll
             for (int i = 0; i < G::A_INSTR; ++i)
-                __builtin_amdgcn_global_load_lds((const void*)(a[q] + ka + offa[i]),
+                __builtin_amdgcn_global_load_lds(at(a[q] + ko + offa[i], ka(i) < kl),
                                                  (lds_void*)(st + q * G::A_PLANE + (wid * G::A_INSTR + i) * 512), 16,
                                                  0, 0);
 #pragma unroll
@@ -432,7 +473,7 @@ struct P64Loader {
 #pragma unroll
             for (int i = 0; i < G::B_INSTR; ++i)
                 __builtin_amdgcn_global_load_lds(
-                    (const void*)(b[q] + kb + offb[i]),
+                    at(b[q] + kb2 + offb[i], kb(i) < kl),
                     (lds_void*)(st + G::NPA * G::A_PLANE + q * G::B_PLANE + (wid * G::B_INSTR + i) * 512), 16, 0, 0);
     }
 };
@@ -476,8 +517,13 @@ __device__ __forceinline__ void pipe64_read(const uint16_t* st, int h, int wm, i
     }
 }
 
-template <int KIND, int BM, int BN, int WM, int WN, int S, int KK, bool EVEN = false>
+// Flags of gemm16_pipe64: LDS reads and loads spread evenly over the MFMAs;
+// any K (P64Loader's RAG; the last stage is multiplied after the loop, once
+// its elements past K are cleared), where otherwise K is a multiple of 64.
+constexpr int kP64Even = 1, kP64Rag = 2;
+template <int KIND, int BM, int BN, int WM, int WN, int S, int KK, int FLAGS>
 __global__ __launch_bounds__(64 * WM * WN) void gemm16_pipe64(Gemm16Args p, int tiles_m, int tiles_n, int group_m) {
+    constexpr bool EVEN = (FLAGS & kP64Even) != 0, RAG = (FLAGS & kP64Rag) != 0;
     using T = KT<KIND>;
     using G = Pipe64Cfg<KIND, BM, BN, WM, WN, S, KK>;
     constexpr int FM = G::FM, FN = G::FN, BK = G::BK, KSUB = G::KSUB;
@@ -501,9 +547,9 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm16_pipe64(Gemm16Args p, int 
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / WN, wn = wid % WN;
-    const int64_t KTN = uniform64(K / BK);  // >= 1
+    const int64_t KTN = uniform64(RAG ? (K + BK - 1) / BK : K / BK);  // >= 1
     auto kclamp = [&](int64_t t) { return (t < KTN ? t : KTN - 1) * BK; };
-    auto stage = [&](int s) -> uint16_t* { return s == 0 ? st0 : s == 1 ? st1 : st2; };
+    auto stage = [&](int s) -> uint16_t* { return s == 0 ? st0 : (S == 2 || s == 1) ? st1 : st2; };
 
     f32x16 hi[FM][FN], lo[FM][FN], rr[FM][FN];
 #pragma unroll
@@ -515,8 +561,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm16_pipe64(Gemm16Args p, int 
             if constexpr (T::RR) rr[i][j] = f32x16{};
         }
 
-    P64Loader<KIND, BM, BN, WM, WN, S> ld;
-    ld.init(Ap, Bp, lda, ldb, M, N, m0, n0, wid, lane);
+    P64Loader<KIND, BM, BN, WM, WN, S, RAG> ld;
+    ld.init(Ap, Bp, lda, ldb, M, N, K, m0, n0, wid, lane);
 
     // prologue: stages 0 .. S-1 in flight; wait for stage 0, read its first fragments
 #pragma unroll
@@ -563,17 +609,33 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm16_pipe64(Gemm16Args p, int 
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const int64_t KFULL = KTN - KTN % S;
+    // RAG: the loop stops before the last stage
+    const int64_t KLOOP = RAG ? KTN - 1 : KTN, KFULL = KLOOP - KLOOP % S;
     for (int64_t t0 = 0; t0 < KFULL; t0 += S) {
         step(std::integral_constant<int, 0>{}, t0);
         step(std::integral_constant<int, 1>{}, t0 + 1);
         if constexpr (S == 3) step(std::integral_constant<int, 2>{}, t0 + 2);
     }
-    if (KFULL < KTN) step(std::integral_constant<int, 0>{}, KFULL);
+    if (KFULL < KLOOP) step(std::integral_constant<int, 0>{}, KFULL);
     if constexpr (S == 3)
-        if (KFULL + 1 < KTN) step(std::integral_constant<int, 1>{}, KFULL + 1);
+        if (KFULL + 1 < KLOOP) step(std::integral_constant<int, 1>{}, KFULL + 1);
 
     wait_vmcnt<0>();  // no global->LDS load may outlive the workgroup's LDS
+    if constexpr (RAG) {
+        uint16_t* tail = stage((int)(KLOOP - KFULL));
+        wait_lgkm0();
+        bare_barrier();
+        if ((K & 7) != 0) {
+            clear_straddle<G, BM>(tail, (int)(K - KLOOP * BK), tid);
+            wait_lgkm0();
+            bare_barrier();
+        }
+#pragma unroll
+        for (int h = 0; h < KSUB; ++h) {
+            pipe64_read<KIND, BM, BN, WM, WN, S, KK>(tail, h, wm, wn, lane, f[0]);
+            mma(f[0]);
+        }
+    }
     store_tile<FM, FN>(C, p.ldc, M, N, m0 + wm * G::TMW, n0 + wn * G::TNW, lane, p.alpha, p.beta,
                        [&](int fm, int fn, int i) { return combine_at<KIND>(hi[fm][fn], lo[fm][fn], rr[fm][fn], i); });
 }

@@ -1,6 +1,6 @@
 // select.cpp -- default tile configuration of each mode when the caller
-// asks for none and the tuned table has no entry: thresholds on the number
-// of output tiles, from measured sweeps on MI355X.  Host code only; kept
+// asks for none and the tuned table has no entry, from measured sweeps on
+// MI355X.  Host code only; kept
 // apart from the kernels so that the policy can change without touching
 // them.  Configuration indices refer to the menus in gemm16.hip,
 // gemm_f8.hip and gemm_f32.hip.
@@ -10,34 +10,85 @@
 
 namespace mfg {
 
-// Default configuration per kind, from measured sweeps on MI355X (square
-// N = 1024 .. 8192, random operands): the pipelined 64-wide kernels once the
-// grid fills the chip, the 64 x 64 tiled kernel below that, the simple
-// kernel when rows are not 16-byte aligned.
-int pick_config16(int kind, int64_t M, int64_t N, int64_t K, bool vec_ok) {
-    if (!vec_ok) return 0;
-    const bool fast = K % 64 == 0 && N % 8 == 0 && N >= 8;
-    const int64_t t256 = cdiv(M, 256) * cdiv(N, 256);
-    const int64_t t128 = cdiv(M, 128) * cdiv(N, 128);
-    const bool big = M >= 64 && N >= 64;
-    if (kind == K_F16 || kind == K_BF16) {
-        if (fast && t256 >= 256) return 29;  // q256x256k64s2w2x2g8e
-        if (fast && t128 >= 64) return 28;   // q128x128k64s3w2x2g8
-        return big ? 6 : 0;                  // t64x64k64w2x2g8
+// The default of the 16-bit kinds is the candidate with the least estimated
+// time.  A tile's time is its K stages (64 deep) plus its part of C; a
+// stage costs `lat` us on a workgroup that has its CU to itself on an
+// otherwise idle chip (latency), `full` us per tile when every CU is busy
+// (bandwidth and clock).  Kernels that put one workgroup on a CU run
+// ceil(tiles / 256) rounds, with the stage between lat and full as the chip
+// fills; the ring kernels share a CU, whose n tiles take n full stages
+// but at least one latency.  Figures measured on MI355X (random operands):
+// lat at 128 x 128 x 4096, full at 4096^3.  What the choice replaces (the
+// 64 x 64 tiled kernel served every K % 64 != 0 and every small problem):
+// SPLIT3 777 x 1234 x 1999 128 -> 30 us, 4000 x 4000 x 4001 1472 -> 375 us,
+// F16 32 x 4096 x 4096 53 -> 18 us, 3000^3 212 -> 71 us, 1024^3 15 -> 7.6 us.
+struct Cost16 {
+    int cfg, variant;  // menu index; of the ring kernels also launch_ring's variant
+    int bm, bn;
+    bool shared;       // several workgroups per CU
+    float lat, full;   // us per 64-deep stage
+};
+static const Cost16 kCostPlain[] = {
+    {6, 0, 64, 64, true, 0.27f, 0.203f},     // ring 64 x 64
+    {6, 1, 64, 128, true, 0.38f, 0.348f},    // ring 64 x 128
+    {28, 0, 128, 128, false, 0.42f, 0.55f},  // q128x128k64s3w2x2g8
+    {30, 0, 256, 128, false, 0.68f, 0.98f},  // q256x128k64s3w2x2g8e
+    {29, 0, 256, 256, false, 1.20f, 1.80f},  // q256x256k64s2w2x2g8e
+};
+static const Cost16 kCostRefineA[] = {
+    {3, 1, 32, 64, true, 0.36f, 0.21f},
+    {3, 0, 64, 64, true, 0.37f, 0.33f},
+    {7, 0, 128, 128, false, 0.70f, 1.01f},
+    {9, 0, 192, 128, false, 0.93f, 1.36f},
+};
+static const Cost16 kCostSplit3[] = {
+    {3, 1, 32, 64, true, 0.45f, 0.31f},
+    {3, 0, 64, 64, true, 0.48f, 0.474f},
+    {7, 0, 128, 128, false, 0.95f, 1.36f},
+    {9, 0, 192, 128, false, 1.28f, 1.79f},
+};
+static const Cost16 kCostSplit4[] = {
+    {2, 1, 32, 64, true, 0.51f, 0.34f},
+    {2, 0, 64, 64, true, 0.53f, 0.547f},
+    {5, 0, 128, 128, false, 1.12f, 1.70f},
+};
+
+static double cost16(const Cost16& c, int64_t M, int64_t N, int64_t K, int64_t batch) {
+    constexpr double kCus = 256.0, kStartUs = 2.0, kCBytesPerUs = 20000.0;  // per CU: a 256th of 5.1 TB/s
+    const double tiles = (double)cdiv(M, c.bm) * (double)cdiv(N, c.bn) * (double)batch;
+    const double stages = (double)cdiv(K, 64), ctime = c.bm * c.bn * 4.0 / kCBytesPerUs;
+    const double n = tiles <= kCus ? 1.0 : (double)(int64_t)((tiles + kCus - 1.0) / kCus);
+    if (c.shared) {
+        const double stage = n * c.full > c.lat ? n * c.full : c.lat;
+        return kStartUs + n * ctime + stages * stage;
     }
-    if (kind == K_SPLIT4) {
-        if (fast && t128 >= 256) return 5;   // q128x128k64s2w2x2g8e
-        if (fast && t128 >= 64) return 3;    // f128x128k32w2x2g8dma
-        return big ? 2 : 0;                  // t64x64k32w2x2g8
+    const double load = tiles < kCus ? tiles / kCus : 1.0;
+    return n * (kStartUs + ctime * load + stages * (c.lat + (c.full - c.lat) * load));
+}
+
+static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch, bool ring_only) {
+    const Cost16* c = kCostSplit3;
+    int n = (int)(sizeof(kCostSplit3) / sizeof(Cost16));
+    if (kind == K_F16 || kind == K_BF16) c = kCostPlain, n = (int)(sizeof(kCostPlain) / sizeof(Cost16));
+    else if (kind == K_REFINE_A) c = kCostRefineA, n = (int)(sizeof(kCostRefineA) / sizeof(Cost16));
+    else if (kind == K_SPLIT4) c = kCostSplit4, n = (int)(sizeof(kCostSplit4) / sizeof(Cost16));
+    int best = 0;
+    double least = cost16(c[0], M, N, K, batch);
+    for (int i = 1; i < n; ++i) {
+        if (ring_only && !c[i].shared) continue;
+        const double t = cost16(c[i], M, N, K, batch);
+        if (t < least) least = t, best = i;
     }
-    // 192 x 128: two 64-deep stages fill the 160 KB of LDS and each MFMA
-    // needs 17% fewer operand bytes than on 128 x 128 (N = 8192: SPLIT3
-    // 2.74 vs 2.96 ms, BF16_SPLIT3 2.63 vs 2.87, REFINE_A 2.16 vs 2.27); at
-    // N = 4096 the partial last wave of 192-row tiles makes it a tie
-    if (fast && cdiv(M, 192) * cdiv(N, 128) >= 1024) return 9;  // q192x128k64s2w2x2g8e
-    if (fast && t128 >= 256) return 7;       // q128x128k64s2w2x2g8
-    if (fast && t128 >= 64) return 6;        // f128x128k64w2x2g8dma
-    return big ? 3 : 0;                      // t64x64k32w2x2g8
+    return c[best];
+}
+
+// Index 0, the simple kernel, where rows are not 16-byte aligned.
+int pick_config16(int kind, int64_t M, int64_t N, int64_t K, bool vec_ok, int64_t batch) {
+    return vec_ok ? pick16(kind, M, N, K, batch, false).cfg : 0;
+}
+
+int pick_ring16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch) {
+    return pick16(kind, M, N, K, batch, true).variant;
 }
 
 // Default: the tiled kernels once the grid fills the chip (measured sweeps,
