@@ -45,6 +45,33 @@ static int convert16(int m, int64_t rows, int64_t cols, const float* X, int64_t 
     return launch_round_f16(rows, cols, X, ldx, p0, ldo, s);
 }
 
+// ConvJob::kind of an operand of mode m (split: head and residual planes).
+static int conv_kind(int m, bool split) { return (split ? 2 : 0) + ((m == MFG_BF16 || m == MFG_BF16_SPLIT3) ? 1 : 0); }
+
+// The planes of A (M x K) and B (K x N) in one launch (p1: null for an
+// operand with one plane).
+static int convert16_pair(int m, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
+                          int64_t ldb, uint16_t* a0, uint16_t* a1, int64_t ldk, uint16_t* b0, uint16_t* b1, int64_t ldn,
+                          hipStream_t s) {
+    const ConvJob ja{A, a0, lda, ldk, M, K, a1 ? a1 - a0 : 0, conv_kind(m, a1 != nullptr), 0};
+    const ConvJob jb{B, b0, ldb, ldn, K, N, b1 ? b1 - b0 : 0, conv_kind(m, b1 != nullptr), 0};
+    int st = launch_convert_pair(ja, jb, s);
+    if (st != MFG_ERR_UNSUPPORTED) return st;
+    if ((st = convert16(m, M, K, A, lda, a0, a1, ldk, a1 != nullptr, s)) != MFG_OK) return st;
+    return convert16(m, K, N, B, ldb, b0, b1, ldn, b1 != nullptr, s);
+}
+
+int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, void* wa, int64_t lda_c,
+                     const float* B, int64_t ldb, void* wb, int64_t ldb_c, hipStream_t s) {
+    if (M > 0 && N > 0 && K > 0 && kind_of(m) >= 0) {
+        uint16_t *a0 = static_cast<uint16_t*>(wa), *b0 = static_cast<uint16_t*>(wb);
+        return convert16_pair(m, M, N, K, A, lda, B, ldb, a0, npa(m) == 2 ? a0 + M * lda_c : nullptr, lda_c, b0,
+                              npb(m) == 2 ? b0 + K * ldb_c : nullptr, ldb_c, s);
+    }
+    const int st = mfg_convert(M, K, A, lda, wa, lda_c, m, s);
+    return st != MFG_OK ? st : mfg_convert(K, N, B, ldb, wb, ldb_c, m == MFG_F16_REFINE_A ? MFG_F16 : m, s);
+}
+
 // The tuned table is keyed by size buckets, so its entry may name a
 // configuration that does not serve this particular shape (e.g. K % 64 != 0
 // in a bucket tuned on K % 64 == 0): then the default choice is used.
@@ -234,8 +261,9 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     uint16_t* a1 = npa(m) == 2 ? a0 + up(pa_elems, 128) : nullptr;
     uint16_t* b0 = (a1 ? a1 : a0) + up(pa_elems, 128);
     uint16_t* b1 = npb(m) == 2 ? b0 + up(pb_elems, 128) : nullptr;
-    if ((st = convert16(m, M, K, static_cast<const float*>(A), lda, a0, a1, ldk, npa(m) == 2, s)) != MFG_OK) return st;
-    if ((st = convert16(m, K, N, static_cast<const float*>(B), ldb, b0, b1, ldn, npb(m) == 2, s)) != MFG_OK) return st;
+    if ((st = convert16_pair(m, M, N, K, static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, a0, a1, ldk,
+                             b0, b1, ldn, s)) != MFG_OK)
+        return st;
     a.A[0] = a0, a.A[1] = a1, a.B[0] = b0, a.B[1] = b1, a.lda = ldk, a.ldb = ldn;
     const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(ldk, ldn);  // workspace planes: aligned, ld a multiple of 8
     return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
@@ -401,21 +429,30 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
         const float* Af = static_cast<const float*>(A);
         const float* Bf = static_cast<const float*>(B);
         // A contiguous batch (stride == rows * ld) is one tall matrix.
-        if (strideA == M * lda && pa == M * ldk) {
-            if ((st = convert16(m, count * M, K, Af, lda, a0, a1, ldk, true, s)) != MFG_OK) return st;
-        } else {
-            for (int64_t b = 0; b < count; ++b)
-                if ((st = convert16(m, M, K, Af + b * strideA, lda, a0 + b * pa, a1 + b * pa, ldk, true, s)) != MFG_OK)
-                    return st;
-        }
+        const bool tall_a = strideA == M * lda && pa == M * ldk, tall_b = strideB == K * ldb && pb == K * ldn;
         const bool bsplit = npb(m) == 2;  // REFINE_A: B rounded to its FP16 head only
-        if (strideB == K * ldb && pb == K * ldn) {
-            if ((st = convert16(m, count * K, N, Bf, ldb, b0, b1, ldn, bsplit, s)) != MFG_OK) return st;
-        } else {
-            for (int64_t b = 0; b < count; ++b)
-                if ((st = convert16(m, K, N, Bf + b * strideB, ldb, b0 + b * pb, bsplit ? b1 + b * pb : nullptr, ldn,
-                                    bsplit, s)) != MFG_OK)
-                    return st;
+        st = MFG_ERR_UNSUPPORTED;
+        if (tall_a && tall_b)
+            st = launch_convert_pair(ConvJob{Af, a0, lda, ldk, count * M, K, a1 - a0, conv_kind(m, true), 0},
+                                     ConvJob{Bf, b0, ldb, ldn, count * K, N, bsplit ? b1 - b0 : 0, conv_kind(m, bsplit), 0},
+                                     s);
+        if (st != MFG_OK && st != MFG_ERR_UNSUPPORTED) return st;
+        if (st == MFG_ERR_UNSUPPORTED) {
+            if (tall_a) {
+                if ((st = convert16(m, count * M, K, Af, lda, a0, a1, ldk, true, s)) != MFG_OK) return st;
+            } else {
+                for (int64_t b = 0; b < count; ++b)
+                    if ((st = convert16(m, M, K, Af + b * strideA, lda, a0 + b * pa, a1 + b * pa, ldk, true, s)) != MFG_OK)
+                        return st;
+            }
+            if (tall_b) {
+                if ((st = convert16(m, count * K, N, Bf, ldb, b0, b1, ldn, bsplit, s)) != MFG_OK) return st;
+            } else {
+                for (int64_t b = 0; b < count; ++b)
+                    if ((st = convert16(m, K, N, Bf + b * strideB, ldb, b0 + b * pb, bsplit ? b1 + b * pb : nullptr, ldn,
+                                        bsplit, s)) != MFG_OK)
+                        return st;
+            }
         }
         a.A[0] = a0, a.A[1] = a1, a.B[0] = b0, a.B[1] = b1;
         a.lda = ldk, a.ldb = ldn, a.sA = pa, a.sB = pb;
@@ -566,12 +603,10 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
             GroupedDesc& d = descs[(size_t)i];
             d.A = reinterpret_cast<const uint16_t*>(base + conv_off[2 * i]);
             d.B = reinterpret_cast<const uint16_t*>(base + conv_off[2 * i + 1]);
-            const bool bf = m == MFG_BF16 || m == MFG_BF16_SPLIT3;
-            const int ka = two_a ? (bf ? 3 : 2) : (bf ? 1 : 0), kb = two_b ? (bf ? 3 : 2) : (bf ? 1 : 0);
             const ConvJob ja{static_cast<const float*>(p.A), const_cast<uint16_t*>(d.A), p.lda, d.lda, p.M, p.K,
-                             d.pa, ka, (al16(p.A) && p.lda % 4 == 0) ? 1 : 0, conv_rows_per_task(p.M, p.K), 0};
+                             d.pa, conv_kind(m, two_a), conv_rows_per_task(p.M, p.K)};
             const ConvJob jb{static_cast<const float*>(p.B), const_cast<uint16_t*>(d.B), p.ldb, d.ldb, p.K, p.N,
-                             d.pb, kb, (al16(p.B) && p.ldb % 4 == 0) ? 1 : 0, conv_rows_per_task(p.K, p.N), 0};
+                             d.pb, conv_kind(m, two_b), conv_rows_per_task(p.K, p.N)};
             for (const ConvJob& j : {ja, jb}) {
                 if (j.rows == 0 || j.cols == 0) continue;
                 if ((int64_t)jobs.size() >= INT32_MAX) return MFG_ERR_UNSUPPORTED;

@@ -334,59 +334,123 @@ int launch_split6_bf16(int64_t rows, int64_t cols, const float* X, int64_t ldx, 
     return MFG_OK;
 }
 
-// ---------------------------------------------------- conversion job lists
-// Many (rows x cols) FP32 matrices rounded or split in one launch: one
-// workgroup per task of j.rpt rows of one job, whose four-element pieces
-// (row-major over the task's rows) are dealt to the threads in turn, so
-// narrow matrices keep every thread busy.  The element formulas are
-// round16_kernel's and split16_kernel's, so every value comes out bitwise as
-// the per-matrix conversions write it.  dst (and dst + plane) rows must be
-// 16-byte aligned with ldo a multiple of 8.
+// ------------------------------------------- conversions into library planes
+// Planes the library owns (workspace, plan storage): rows 16-byte aligned, ld
+// a multiple of 8, so a piece of eight elements is one 16-byte store per
+// plane and the last piece of a row may be written whole (zeros past its
+// columns, inside the row's ld).  The element formulas are round16_kernel's
+// and split16_kernel's, so every value comes out bitwise as the per-matrix
+// conversions write it.
+//
+// HBM-bound: 4 B read and 2 B per plane written per element.  A source piece
+// is two 16-byte loads whatever the row's alignment (global loads need only
+// the element's; element by element, rows with ld % 4 != 0 took twice as
+// long).  kP pieces per thread are loaded before the first is converted.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+
+struct Piece8 {
+    float v[8];
+};
+
+// Elements c0 .. c0 + 7 of a source row, zero at or past `cols`.
+__device__ __forceinline__ Piece8 piece_load(const float* x, int64_t c0, int64_t cols) {
+    Piece8 p;
+    if (c0 + 8 <= cols) {
+        const f32x4 a = *reinterpret_cast<const f32x4_any*>(x + c0), b = *reinterpret_cast<const f32x4_any*>(x + c0 + 4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p.v[j] = a[j], p.v[4 + j] = b[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) p.v[j] = c0 + j < cols ? x[c0 + j] : 0.0f;
+    }
+    return p;
+}
+
+// kind: ConvJob's.  Head plane at h, residual plane at q (split kinds).
+__device__ __forceinline__ void piece_store(int kind, const Piece8& p, uint16_t* h, uint16_t* q) {
+    uint32_t hw[4], qw[4];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        uint16_t a[2], r[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const float v = p.v[j + i];
+            if (kind & 1) {  // bfloat16
+                a[i] = f32_to_bf16_bits(v);
+                r[i] = f32_to_bf16_bits(v - bf16_bits_to_f32(a[i]));
+            } else {
+                a[i] = f32_to_f16_bits(v);
+                r[i] = f32_to_f16_bits((v - f16_bits_to_f32(a[i])) * 2048.0f);
+            }
+        }
+        hw[j >> 1] = (uint32_t)a[0] | ((uint32_t)a[1] << 16);
+        qw[j >> 1] = (uint32_t)r[0] | ((uint32_t)r[1] << 16);
+    }
+    *reinterpret_cast<u32x4*>(h) = u32x4{hw[0], hw[1], hw[2], hw[3]};
+    if (kind >= 2) *reinterpret_cast<u32x4*>(q) = u32x4{qw[0], qw[1], qw[2], qw[3]};
+}
+
+// Both operands of one GEMM in one launch: blocks below `blocks_a` take
+// matrix a, the rest matrix b; a block takes 256 kP consecutive pieces
+// (row-major), whatever the row length, so narrow and wide matrices fill
+// every thread.
+template <int kP>
+__global__ __launch_bounds__(kEltThreads) void convert_pair_kernel(ConvJob a, ConvJob b, uint32_t blocks_a) {
+    const bool second = blockIdx.x >= blocks_a;
+    const ConvJob& j = second ? b : a;
+    const uint32_t blk = second ? blockIdx.x - blocks_a : blockIdx.x;
+    const uint32_t cpr = (uint32_t)((j.cols + 7) / 8), total = (uint32_t)j.rows * cpr;
+    const float* src = j.src;
+    uint16_t* dst = j.dst;
+    const int64_t lds = j.lds, ldo = j.ldo, cols = j.cols, plane = j.plane;
+    const int kind = j.kind;
+    Piece8 p[kP];
+    int64_t at[kP];
+#pragma unroll
+    for (int i = 0; i < kP; ++i) {
+        const uint32_t e = (blk * kP + i) * kEltThreads + threadIdx.x;
+        at[i] = -1;
+        if (e < total) {
+            const uint32_t r = e / cpr, c0 = (e - r * cpr) * 8;
+            p[i] = piece_load(src + (int64_t)r * lds, c0, cols);
+            at[i] = (int64_t)r * ldo + c0;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kP; ++i)
+        if (at[i] >= 0) piece_store(kind, p[i], dst + at[i], dst + plane + at[i]);
+}
+
+// a, b: rows, cols >= 1.
+int launch_convert_pair(const ConvJob& a, const ConvJob& b, hipStream_t s) {
+    const int64_t pa = a.rows * cdiv(a.cols, 8), pb = b.rows * cdiv(b.cols, 8);
+    if (pa > 0x7FFFFFFF || pb > 0x7FFFFFFF) return MFG_ERR_UNSUPPORTED;
+    // one piece per thread until that alone gives the chip eight workgroups per CU
+    const int per = pa + pb >= (int64_t)4 * 2048 * kEltThreads ? 4 : pa + pb >= (int64_t)2 * 2048 * kEltThreads ? 2 : 1;
+    const uint32_t ba = (uint32_t)cdiv(pa, kEltThreads * per), bb = (uint32_t)cdiv(pb, kEltThreads * per);
+    const dim3 grid(ba + bb), block(kEltThreads);
+    if (per == 4) hipLaunchKernelGGL(convert_pair_kernel<4>, grid, block, 0, s, a, b, ba);
+    else if (per == 2) hipLaunchKernelGGL(convert_pair_kernel<2>, grid, block, 0, s, a, b, ba);
+    else hipLaunchKernelGGL(convert_pair_kernel<1>, grid, block, 0, s, a, b, ba);
+    MFG_LAUNCH_CHECK();
+    return MFG_OK;
+}
+
+// Many (rows x cols) FP32 matrices in one launch: one workgroup per task of
+// j.rpt rows of one job, whose pieces (row-major over the task's rows) are
+// dealt to the threads in turn, so narrow matrices keep every thread busy.
 __global__ __launch_bounds__(kEltThreads) void convert_jobs_kernel(const ConvJob* jobs, const ConvTask* tasks) {
     const ConvTask t = tasks[blockIdx.x];
     const ConvJob j = jobs[t.job];
-    const uint32_t cpr = (uint32_t)((j.cols + 3) / 4);  // pieces per row
+    const uint32_t cpr = (uint32_t)((j.cols + 7) / 8);  // pieces per row
     const int64_t nr = j.rows - t.row0 < j.rpt ? j.rows - t.row0 : j.rpt;
-    const uint32_t total = (uint32_t)nr * cpr;  // <= max(kJobChunks, cpr)
+    const uint32_t total = (uint32_t)nr * cpr;  // <= max(kJobPieces, cpr)
     for (uint32_t e = threadIdx.x; e < total; e += kEltThreads) {
         const uint32_t rr = e / cpr;
-        const int64_t r = t.row0 + rr, c0 = (int64_t)(e - rr * cpr) * 4;
-        const float* x = j.src + r * j.lds;
-        uint16_t* ho = j.dst + r * j.ldo;
-        uint16_t* qo = ho + j.plane;  // residual plane (split jobs)
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        int cnt = 0;
-        if (j.vec && c0 + kColsPerThread <= j.cols) {
-            const f32x4 w = *reinterpret_cast<const f32x4*>(x + c0);
-            v[0] = w[0], v[1] = w[1], v[2] = w[2], v[3] = w[3];
-            cnt = 4;
-        } else {
-            for (int q = 0; q < kColsPerThread; ++q)
-                if (c0 + q < j.cols) v[q] = x[c0 + q], cnt = q + 1;
-        }
-        uint16_t h[4], q[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (j.kind == 1 || j.kind == 3) {  // as split16_kernel<true>
-                h[i] = f32_to_bf16_bits(v[i]);
-                q[i] = f32_to_bf16_bits(v[i] - bf16_bits_to_f32(h[i]));
-            } else {  // as split16_kernel<false>
-                h[i] = f32_to_f16_bits(v[i]);
-                q[i] = f32_to_f16_bits((v[i] - f16_bits_to_f32(h[i])) * 2048.0f);
-            }
-        }
-        if (cnt == 4) {  // dst rows are 16-byte aligned (ldo a multiple of 8): 8-byte pieces
-            *reinterpret_cast<u32x2*>(ho + c0) =
-                u32x2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
-            if (j.kind >= 2)
-                *reinterpret_cast<u32x2*>(qo + c0) =
-                    u32x2{(uint32_t)q[0] | ((uint32_t)q[1] << 16), (uint32_t)q[2] | ((uint32_t)q[3] << 16)};
-        } else {
-            for (int i = 0; i < cnt; ++i) {
-                ho[c0 + i] = h[i];
-                if (j.kind >= 2) qo[c0 + i] = q[i];
-            }
-        }
+        const int64_t r = t.row0 + rr, c0 = (int64_t)(e - rr * cpr) * 8;
+        const Piece8 p = piece_load(j.src + r * j.lds, c0, j.cols);
+        uint16_t* h = j.dst + r * j.ldo + c0;
+        piece_store(j.kind, p, h, h + j.plane);
     }
 }
 

@@ -137,23 +137,33 @@ int launch_quantize_fp8(int64_t rows, int64_t cols, const float* X, int64_t ldx,
 // scales in the untransposed tile order.
 int launch_quantize_fp8_t(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint8_t* codes_t, int64_t ldt,
                           float* scales, hipStream_t s);
-// Conversion job lists (grouped plans over FP32 operands): job = one matrix,
-// rows x cols FP32 at src (ld lds) into 16-bit dst (ld ldo); kind 0 rne16,
-// 1 rnebf16, 2 FP16 split (head at dst, scaled residual at dst + plane),
-// 3 BF16 split (unscaled residual).  Task =
-// rpt rows of one job (one workgroup): about kJobChunks four-element pieces.
-constexpr int kJobChunks = 512;
+// Conversion jobs: one matrix, rows x cols FP32 at src (ld lds, any
+// alignment) into 16-bit library planes at dst (16-byte aligned, ld ldo a
+// multiple of 8); kind 0 rne16, 1 rnebf16, 2 FP16 split (head at dst, scaled
+// residual at dst + plane, a multiple of 8), 3 BF16 split (unscaled
+// residual).  Columns from cols to the next multiple of 8 are written as 0.
+// Job lists (grouped plans over FP32 operands): task = rpt rows of one job
+// (one workgroup), about kJobPieces eight-element pieces.
+constexpr int kJobPieces = 512;
 struct ConvJob {
     const float* src;
     uint16_t* dst;
     int64_t lds, ldo, rows, cols, plane;
-    int32_t kind, vec;  // vec: src rows 16-byte aligned (whole four-float loads)
-    int32_t rpt, pad;   // rows per task
+    int32_t kind;
+    int32_t rpt;  // rows per task
 };
 inline int32_t conv_rows_per_task(int64_t rows, int64_t cols) {
-    const int64_t cpr = (cols + 3) / 4, r = kJobChunks / (cpr > 0 ? cpr : 1);
+    const int64_t cpr = (cols + 7) / 8, r = kJobPieces / (cpr > 0 ? cpr : 1);
     return (int32_t)(r < 1 ? 1 : (r < rows ? r : rows));
 }
+// Both operands of one GEMM (or of a batch laid out as one tall matrix) in
+// one launch; rpt is not used.  MFG_ERR_UNSUPPORTED beyond 2^31 pieces.
+int launch_convert_pair(const ConvJob& a, const ConvJob& b, hipStream_t s);
+// A (M x K) and B (K x N) in mode m's preconverted storage form at wa, wb
+// (library memory, 256-byte aligned, lda_c and ldb_c multiples of 8; FP8: of
+// 16); Eq. 1 keeps B's head alone.  capi.cpp.
+int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, void* wa, int64_t lda_c,
+                     const float* B, int64_t ldb, void* wb, int64_t ldb_c, hipStream_t s);
 struct ConvTask {
     int32_t job, row0;
 };

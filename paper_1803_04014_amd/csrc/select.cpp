@@ -11,59 +11,58 @@
 namespace mfg {
 
 // The default of the 16-bit kinds is the candidate with the least estimated
-// time.  A tile's time is its K stages (64 deep) plus its part of C; a
-// stage costs `lat` us on a workgroup that has its CU to itself on an
-// otherwise idle chip (latency), `full` us per tile when every CU is busy
-// (bandwidth and clock).  Kernels that put one workgroup on a CU run
-// ceil(tiles / 256) rounds, with the stage between lat and full as the chip
-// fills; the ring kernels share a CU, whose n tiles take n full stages
-// but at least one latency.  Figures measured on MI355X (random operands):
-// lat at 128 x 128 x 4096, full at 4096^3.  What the choice replaces (the
-// 64 x 64 tiled kernel served every K % 64 != 0 and every small problem):
-// SPLIT3 777 x 1234 x 1999 128 -> 30 us, 4000 x 4000 x 4001 1472 -> 375 us,
-// F16 32 x 4096 x 4096 53 -> 18 us, 3000^3 212 -> 71 us, 1024^3 15 -> 7.6 us.
+// time: `start` (launch, prologue, one tile's epilogue latency), then per
+// tile its part of C at the CU's share of HBM and its 64-deep K stages.  A
+// stage costs `lat` us on a workgroup with an otherwise idle chip (latency),
+// `full` us per tile when every CU is busy (bandwidth and clock).  Kernels
+// that put one workgroup on a CU run ceil(tiles / 256) rounds, with the stage
+// between lat and full as the chip fills; the ring kernels share a CU,
+// whose n tiles take n full stages but at least one latency.  Figures
+// measured on MI355X (random operands): start at 64^3, lat at
+// 128 x 128 x 4096, full at 4096^3.  What the choice replaces (the 64 x 64
+// tiled kernel served every K % 64 != 0 and every small problem): SPLIT3
+// 777 x 1234 x 1999 128 -> 30 us, 4000 x 4000 x 4001 1472 -> 375 us, F16
+// 32 x 4096 x 4096 53 -> 18 us, 3000^3 212 -> 71 us, 1024^3 15 -> 7.6 us.
 struct Cost16 {
     int cfg, variant;  // menu index; of the ring kernels also launch_ring's variant
     int bm, bn;
     bool shared;       // several workgroups per CU
-    float lat, full;   // us per 64-deep stage
+    float start, lat, full;  // us; us per 64-deep stage
 };
 static const Cost16 kCostPlain[] = {
-    {6, 0, 64, 64, true, 0.27f, 0.203f},     // ring 64 x 64
-    {6, 1, 64, 128, true, 0.38f, 0.348f},    // ring 64 x 128
-    {28, 0, 128, 128, false, 0.42f, 0.55f},  // q128x128k64s3w2x2g8
-    {30, 0, 256, 128, false, 0.68f, 0.98f},  // q256x128k64s3w2x2g8e
-    {29, 0, 256, 256, false, 1.20f, 1.80f},  // q256x256k64s2w2x2g8e
+    {6, 0, 64, 64, true, 2.6f, 0.27f, 0.19f},       // ring 64 x 64
+    {6, 1, 64, 128, true, 2.9f, 0.38f, 0.32f},      // ring 64 x 128
+    {28, 0, 128, 128, false, 4.7f, 0.42f, 0.50f},   // q128x128k64s3w2x2g8
+    {30, 0, 256, 128, false, 6.9f, 0.68f, 0.83f},   // q256x128k64s3w2x2g8e
+    {29, 0, 256, 256, false, 10.0f, 1.20f, 1.44f},  // q256x256k64s2w2x2g8e
 };
 static const Cost16 kCostRefineA[] = {
-    {3, 1, 32, 64, true, 0.36f, 0.21f},
-    {3, 0, 64, 64, true, 0.37f, 0.33f},
-    {7, 0, 128, 128, false, 0.70f, 1.01f},
-    {9, 0, 192, 128, false, 0.93f, 1.36f},
+    {3, 1, 32, 64, true, 2.9f, 0.36f, 0.20f},
+    {3, 0, 64, 64, true, 2.9f, 0.37f, 0.32f},
+    {7, 0, 128, 128, false, 5.0f, 0.70f, 0.96f},
+    {9, 0, 192, 128, false, 6.4f, 0.93f, 1.26f},
 };
 static const Cost16 kCostSplit3[] = {
-    {3, 1, 32, 64, true, 0.45f, 0.31f},
-    {3, 0, 64, 64, true, 0.48f, 0.474f},
-    {7, 0, 128, 128, false, 0.95f, 1.36f},
-    {9, 0, 192, 128, false, 1.28f, 1.79f},
+    {3, 1, 32, 64, true, 2.9f, 0.45f, 0.30f},
+    {3, 0, 64, 64, true, 2.9f, 0.48f, 0.46f},
+    {7, 0, 128, 128, false, 5.0f, 0.95f, 1.30f},
+    {9, 0, 192, 128, false, 6.4f, 1.28f, 1.68f},
 };
 static const Cost16 kCostSplit4[] = {
-    {2, 1, 32, 64, true, 0.51f, 0.34f},
-    {2, 0, 64, 64, true, 0.53f, 0.547f},
-    {5, 0, 128, 128, false, 1.12f, 1.70f},
+    {2, 1, 32, 64, true, 2.9f, 0.51f, 0.33f},
+    {2, 0, 64, 64, true, 2.9f, 0.53f, 0.53f},
+    {5, 0, 128, 128, false, 5.0f, 1.12f, 1.64f},
 };
 
 static double cost16(const Cost16& c, int64_t M, int64_t N, int64_t K, int64_t batch) {
-    constexpr double kCus = 256.0, kStartUs = 2.0, kCBytesPerUs = 20000.0;  // per CU: a 256th of 5.1 TB/s
+    constexpr double kCus = 256.0, kCBytesPerUs = 20000.0;  // per CU: a 256th of 5.1 TB/s
     const double tiles = (double)cdiv(M, c.bm) * (double)cdiv(N, c.bn) * (double)batch;
-    const double stages = (double)cdiv(K, 64), ctime = c.bm * c.bn * 4.0 / kCBytesPerUs;
+    const double stages = (double)cdiv(K, 64), load = tiles < kCus ? tiles / kCus : 1.0;
     const double n = tiles <= kCus ? 1.0 : (double)(int64_t)((tiles + kCus - 1.0) / kCus);
-    if (c.shared) {
-        const double stage = n * c.full > c.lat ? n * c.full : c.lat;
-        return kStartUs + n * ctime + stages * stage;
-    }
-    const double load = tiles < kCus ? tiles / kCus : 1.0;
-    return n * (kStartUs + ctime * load + stages * (c.lat + (c.full - c.lat) * load));
+    const double ctime = c.bm * c.bn * 4.0 / kCBytesPerUs * load;
+    double stage = c.lat + (c.full - c.lat) * load;
+    if (c.shared) stage = (n * c.full > c.lat ? n * c.full : c.lat) / n;
+    return c.start + n * (ctime + stages * stage);
 }
 
 static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch, bool ring_only) {

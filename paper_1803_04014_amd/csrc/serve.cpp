@@ -350,9 +350,7 @@ int mfg_server::run_request(Slot& sl, Req* q, bool grouped) {
     }
     char* wa = static_cast<char*>(q->ws);
     char* wb = wa + q->off_b;
-    const int mb = (r.mode == MFG_F16_REFINE_A) ? MFG_F16 : r.mode;
-    int s = mfg_convert(r.M, r.K, r.A, r.lda, wa, q->lda_c, r.mode, sl.stream);
-    if (s == MFG_OK) s = mfg_convert(r.K, r.N, r.B, r.ldb, wb, q->ldb_c, mb, sl.stream);
+    const int s = convert_operands(r.mode, r.M, r.N, r.K, r.A, r.lda, wa, q->lda_c, r.B, r.ldb, wb, q->ldb_c, sl.stream);
     if (s != MFG_OK || grouped) return s;
     return mfg_gemm(r.M, r.N, r.K, wa, q->lda_c, wb, q->ldb_c, r.C, r.ldc, r.alpha, r.beta,
                     r.mode | MFG_IN_PRECONVERTED, sl.stream);
