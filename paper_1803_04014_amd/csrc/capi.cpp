@@ -48,15 +48,16 @@ static int convert16(int m, int64_t rows, int64_t cols, const float* X, int64_t 
 // ConvJob::kind of an operand of mode m (split: head and residual planes).
 static int conv_kind(int m, bool split) { return (split ? 2 : 0) + ((m == MFG_BF16 || m == MFG_BF16_SPLIT3) ? 1 : 0); }
 
-// The planes of A (M x K) and B (K x N) in one launch (p1: null for an
-// operand with one plane).
-static int convert16_pair(int m, int64_t M, int64_t N, int64_t K, const float* A, int64_t lda, const float* B,
-                          int64_t ldb, uint16_t* a0, uint16_t* a1, int64_t ldk, uint16_t* b0, uint16_t* b1, int64_t ldn,
-                          hipStream_t s) {
-    const ConvJob ja{A, a0, lda, ldk, M, K, a1 ? a1 - a0 : 0, conv_kind(m, a1 != nullptr), 0};
-    const ConvJob jb{B, b0, ldb, ldn, K, N, b1 ? b1 - b0 : 0, conv_kind(m, b1 != nullptr), 0};
+// The planes of A (M x K) and B (K x N) in one launch (a1, b1: null for an
+// operand with one plane), K padded with zeros to kp columns of A and rows of
+// B (kp == K: none).
+static int convert16_pair(int m, int64_t M, int64_t N, int64_t K, int64_t kp, const float* A, int64_t lda,
+                          const float* B, int64_t ldb, uint16_t* a0, uint16_t* a1, int64_t ldk, uint16_t* b0,
+                          uint16_t* b1, int64_t ldn, hipStream_t s) {
+    const ConvJob ja{A, a0, lda, ldk, M, K, M, kp, a1 ? a1 - a0 : 0, conv_kind(m, a1 != nullptr), 0};
+    const ConvJob jb{B, b0, ldb, ldn, K, N, kp, N, b1 ? b1 - b0 : 0, conv_kind(m, b1 != nullptr), 0};
     int st = launch_convert_pair(ja, jb, s);
-    if (st != MFG_ERR_UNSUPPORTED) return st;
+    if (st != MFG_ERR_UNSUPPORTED || kp != K) return st;
     if ((st = convert16(m, M, K, A, lda, a0, a1, ldk, a1 != nullptr, s)) != MFG_OK) return st;
     return convert16(m, K, N, B, ldb, b0, b1, ldn, b1 != nullptr, s);
 }
@@ -65,7 +66,7 @@ int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int
                      const float* B, int64_t ldb, void* wb, int64_t ldb_c, hipStream_t s) {
     if (M > 0 && N > 0 && K > 0 && kind_of(m) >= 0) {
         uint16_t *a0 = static_cast<uint16_t*>(wa), *b0 = static_cast<uint16_t*>(wb);
-        return convert16_pair(m, M, N, K, A, lda, B, ldb, a0, npa(m) == 2 ? a0 + M * lda_c : nullptr, lda_c, b0,
+        return convert16_pair(m, M, N, K, K, A, lda, B, ldb, a0, npa(m) == 2 ? a0 + M * lda_c : nullptr, lda_c, b0,
                               npb(m) == 2 ? b0 + K * ldb_c : nullptr, ldb_c, s);
     }
     const int st = mfg_convert(M, K, A, lda, wa, lda_c, m, s);
@@ -75,11 +76,12 @@ int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int
 // The tuned table is keyed by size buckets, so its entry may name a
 // configuration that does not serve this particular shape (e.g. K % 64 != 0
 // in a bucket tuned on K % 64 == 0): then the default choice is used.
-static int choose16(int m, int config, int64_t M, int64_t N, int64_t K, int64_t ldc, bool vec) {
+// kp: the K the kernel will run (K, or padded).
+static int choose16(int m, int config, int64_t M, int64_t N, int64_t K, int64_t kp, int64_t ldc, bool vec) {
     if (config >= 0) return config;
     const int t = tuned_lookup(m, M, N, K);
     if (t >= 0 && config16_ok(kind_of(m), t, M, N, K, ldc, vec)) return t;
-    return pick_config16(kind_of(m), M, N, K, vec);
+    return pick_config16(kind_of(m), M, N, kp, vec);
 }
 
 // BF16_SPLIT6 runs the BF16 kernels over K' = 6 * up(K, 64); its tuned
@@ -249,10 +251,20 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.lda = lda, a.ldb = ldb;
         const bool vec =
             al16(A) && al16(B) && lda % 8 == 0 && ldb % 8 == 0 && buffer_ldc_ok(ldc) && operand_ld_ok(lda, ldb);
-        return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
+        return launch_gemm16(kind, choose16(m, config, M, N, K, K, ldc, vec), a, 1, vec, s, config < 0);
     }
-    const int64_t ldk = up(K, 8), ldn = up(N, 8);
-    const int64_t pa_elems = M * ldk, pb_elems = K * ldn;
+    // Workspace planes of K >= 256 take K padded with zeros to whole 64-deep
+    // stages (adding zero products changes no bit of an accumulator) and rows
+    // of whole 128-byte lines, so they run on the kernels for whole stages
+    // (F16 2048^3: 22.3 us, 24.4 us on the variant for any K).  Below that the
+    // padding would be over a quarter of the conversion's writes.  Not in the
+    // fixed array, whose capacity is stated without it, nor beyond the limits
+    // of one conversion launch and of the tiled kernels.
+    const int64_t k64 = up(K, 64), n64 = N >= 256 ? up(N, 64) : up(N, 8);
+    const bool pad = !ext && K >= 256 && operand_ld_ok(k64, n64) && k64 / 8 * M < ((int64_t)1 << 31) &&
+                     cdiv(N, 8) * k64 < ((int64_t)1 << 31);
+    const int64_t kp = pad ? k64 : K, ldk = pad ? k64 : up(K, 8), ldn = pad ? n64 : up(N, 8);
+    const int64_t pa_elems = M * ldk, pb_elems = kp * ldn;
     const size_t bytes = (size_t)(npa(m) * up(pa_elems, 128) + npb(m) * up(pb_elems, 128)) * 2;
     CallWs ws;
     if ((st = call_ws(s, bytes, ext, ws)) != MFG_OK) return st;
@@ -261,12 +273,15 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     uint16_t* a1 = npa(m) == 2 ? a0 + up(pa_elems, 128) : nullptr;
     uint16_t* b0 = (a1 ? a1 : a0) + up(pa_elems, 128);
     uint16_t* b1 = npb(m) == 2 ? b0 + up(pb_elems, 128) : nullptr;
-    if ((st = convert16_pair(m, M, N, K, static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, a0, a1, ldk,
-                             b0, b1, ldn, s)) != MFG_OK)
+    if ((st = convert16_pair(m, M, N, K, kp, static_cast<const float*>(A), lda, static_cast<const float*>(B), ldb, a0, a1,
+                             ldk, b0, b1, ldn, s)) != MFG_OK)
         return st;
+    a.K = kp;
     a.A[0] = a0, a.A[1] = a1, a.B[0] = b0, a.B[1] = b1, a.lda = ldk, a.ldb = ldn;
     const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(ldk, ldn);  // workspace planes: aligned, ld a multiple of 8
-    return launch_gemm16(kind, choose16(m, config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
+    const int cfg = choose16(m, config, M, N, K, kp, ldc, vec);
+    if (config >= 0 && !config16_ok(kind, cfg, M, N, K, ldc, vec)) return MFG_ERR_UNSUPPORTED;  // judged on the caller's K
+    return launch_gemm16(kind, cfg, a, 1, vec, s, config < 0);
 }
 
 }  // namespace mfg
@@ -357,7 +372,7 @@ extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
         if (t >= n16 && t < n16 + num_configs_fused(k) && K % 64 == 0 && K > 0 && N % 8 == 0 && N >= 8 && M >= 1)
             return t;
     }
-    return choose16(m, -1, M, N, K, N, true);
+    return choose16(m, -1, M, N, K, K, N, true);
 }
 
 // -------------------------------------------------------------------- batched
@@ -433,8 +448,8 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
         const bool bsplit = npb(m) == 2;  // REFINE_A: B rounded to its FP16 head only
         st = MFG_ERR_UNSUPPORTED;
         if (tall_a && tall_b)
-            st = launch_convert_pair(ConvJob{Af, a0, lda, ldk, count * M, K, a1 - a0, conv_kind(m, true), 0},
-                                     ConvJob{Bf, b0, ldb, ldn, count * K, N, bsplit ? b1 - b0 : 0, conv_kind(m, bsplit), 0},
+            st = launch_convert_pair(ConvJob{Af, a0, lda, ldk, count * M, K, count * M, K, a1 - a0, conv_kind(m, true), 0},
+                                     ConvJob{Bf, b0, ldb, ldn, count * K, N, count * K, N, bsplit ? b1 - b0 : 0, conv_kind(m, bsplit), 0},
                                      s);
         if (st != MFG_OK && st != MFG_ERR_UNSUPPORTED) return st;
         if (st == MFG_ERR_UNSUPPORTED) {
@@ -604,9 +619,9 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
             d.A = reinterpret_cast<const uint16_t*>(base + conv_off[2 * i]);
             d.B = reinterpret_cast<const uint16_t*>(base + conv_off[2 * i + 1]);
             const ConvJob ja{static_cast<const float*>(p.A), const_cast<uint16_t*>(d.A), p.lda, d.lda, p.M, p.K,
-                             d.pa, conv_kind(m, two_a), conv_rows_per_task(p.M, p.K)};
+                             p.M, p.K, d.pa, conv_kind(m, two_a), conv_rows_per_task(p.M, p.K)};
             const ConvJob jb{static_cast<const float*>(p.B), const_cast<uint16_t*>(d.B), p.ldb, d.ldb, p.K, p.N,
-                             d.pb, conv_kind(m, two_b), conv_rows_per_task(p.K, p.N)};
+                             p.K, p.N, d.pb, conv_kind(m, two_b), conv_rows_per_task(p.K, p.N)};
             for (const ConvJob& j : {ja, jb}) {
                 if (j.rows == 0 || j.cols == 0) continue;
                 if ((int64_t)jobs.size() >= INT32_MAX) return MFG_ERR_UNSUPPORTED;

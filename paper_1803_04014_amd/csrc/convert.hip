@@ -399,10 +399,10 @@ __global__ __launch_bounds__(kEltThreads) void convert_pair_kernel(ConvJob a, Co
     const bool second = blockIdx.x >= blocks_a;
     const ConvJob& j = second ? b : a;
     const uint32_t blk = second ? blockIdx.x - blocks_a : blockIdx.x;
-    const uint32_t cpr = (uint32_t)((j.cols + 7) / 8), total = (uint32_t)j.rows * cpr;
+    const uint32_t cpr = (uint32_t)((j.ocols + 7) / 8), total = (uint32_t)j.orows * cpr;
     const float* src = j.src;
     uint16_t* dst = j.dst;
-    const int64_t lds = j.lds, ldo = j.ldo, cols = j.cols, plane = j.plane;
+    const int64_t lds = j.lds, ldo = j.ldo, rows = j.rows, cols = j.cols, plane = j.plane;
     const int kind = j.kind;
     Piece8 p[kP];
     int64_t at[kP];
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(kEltThreads) void convert_pair_kernel(ConvJob a, Co
         at[i] = -1;
         if (e < total) {
             const uint32_t r = e / cpr, c0 = (e - r * cpr) * 8;
-            p[i] = piece_load(src + (int64_t)r * lds, c0, cols);
+            p[i] = piece_load(src + (int64_t)r * lds, c0, r < rows ? cols : 0);
             at[i] = (int64_t)r * ldo + c0;
         }
     }
@@ -421,9 +421,9 @@ __global__ __launch_bounds__(kEltThreads) void convert_pair_kernel(ConvJob a, Co
         if (at[i] >= 0) piece_store(kind, p[i], dst + at[i], dst + plane + at[i]);
 }
 
-// a, b: rows, cols >= 1.
+// a, b: orows, ocols >= 1.
 int launch_convert_pair(const ConvJob& a, const ConvJob& b, hipStream_t s) {
-    const int64_t pa = a.rows * cdiv(a.cols, 8), pb = b.rows * cdiv(b.cols, 8);
+    const int64_t pa = a.orows * cdiv(a.ocols, 8), pb = b.orows * cdiv(b.ocols, 8);
     if (pa > 0x7FFFFFFF || pb > 0x7FFFFFFF) return MFG_ERR_UNSUPPORTED;
     // one piece per thread until that alone gives the chip eight workgroups per CU
     const int per = pa + pb >= (int64_t)4 * 2048 * kEltThreads ? 4 : pa + pb >= (int64_t)2 * 2048 * kEltThreads ? 2 : 1;

@@ -141,14 +141,15 @@ int launch_quantize_fp8_t(int64_t rows, int64_t cols, const float* X, int64_t ld
 // alignment) into 16-bit library planes at dst (16-byte aligned, ld ldo a
 // multiple of 8); kind 0 rne16, 1 rnebf16, 2 FP16 split (head at dst, scaled
 // residual at dst + plane, a multiple of 8), 3 BF16 split (unscaled
-// residual).  Columns from cols to the next multiple of 8 are written as 0.
+// residual).  The output is orows x ocols, at least rows x cols, zero beyond
+// the source and to the next multiple of 8 columns.
 // Job lists (grouped plans over FP32 operands): task = rpt rows of one job
 // (one workgroup), about kJobPieces eight-element pieces.
 constexpr int kJobPieces = 512;
 struct ConvJob {
     const float* src;
     uint16_t* dst;
-    int64_t lds, ldo, rows, cols, plane;
+    int64_t lds, ldo, rows, cols, orows, ocols, plane;
     int32_t kind;
     int32_t rpt;  // rows per task
 };
