@@ -132,13 +132,13 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.M = M, a.N = N, a.K = K;
         a.A = static_cast<const float*>(A), a.B = static_cast<const float*>(B), a.C = C;
         a.lda = lda, a.ldb = ldb, a.ldc = ldc, a.alpha = alpha, a.beta = beta;
-        const bool vec = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0 && buffer_ldc_ok(ldc);
+        const bool vec = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0;
         int cfg = config;
         if (cfg < 0) {
             const int t = tuned_lookup(m, M, N, K);
-            cfg = (t >= 0 && config_f32_ok(t, ldc, vec)) ? t : pick_config_f32(M, N, K, vec);
+            cfg = (t >= 0 && config_f32_ok(t, ldc, vec)) ? t : buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K) : 0;
         }
-        return launch_gemm_f32(cfg, a, 1, vec, s);
+        return launch_gemm_f32(cfg, a, 1, vec, s, config < 0);
     }
 
     if (m == MFG_FP8_E4M3) {
@@ -360,7 +360,7 @@ extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
     if (m < 0 || m >= MFG_NUM_MODES || M < 0 || N < 0 || K < 0) return MFG_ERR_INVALID_ARG;
     if (m == MFG_F32) {
         const int t = tuned_lookup(m, M, N, K);
-        return t >= 0 ? t : pick_config_f32(M, N, K, true);
+        return t >= 0 ? t : pick_config_f32(M, N, K);
     }
     if (m == MFG_FP8_E4M3) {
         const int t = tuned_lookup(m, M, N, K);
@@ -399,12 +399,12 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
         a.lda = lda, a.ldb = ldb, a.sA = strideA, a.sB = strideB, a.sC = strideC;
         const bool vec = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0 && strideA % 4 == 0 && strideB % 4 == 0 &&
                          buffer_ldc_ok(ldc);
-        const int cfg = (M >= 128 && N >= 128 && vec) ? 1 : 0;
+        const int cfg = buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K, count) : 0;
         for (int64_t b0 = 0; b0 < count; b0 += 65535) {
             a.A = static_cast<const float*>(A) + b0 * strideA;
             a.B = static_cast<const float*>(B) + b0 * strideB;
             a.C = C + b0 * strideC;
-            if ((st = launch_gemm_f32(cfg, a, std::min<int64_t>(65535, count - b0), vec, s)) != MFG_OK) return st;
+            if ((st = launch_gemm_f32(cfg, a, std::min<int64_t>(65535, count - b0), vec, s, true)) != MFG_OK) return st;
         }
         return MFG_OK;
     }

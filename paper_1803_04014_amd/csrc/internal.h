@@ -109,8 +109,12 @@ bool config_f8_ok(int cfg, int64_t M, int64_t N, int64_t K, int64_t ldc, bool ve
 
 int num_configs_f32();
 const char* config_f32_name(int cfg);
-int pick_config_f32(int64_t M, int64_t N, int64_t K, bool vec_ok);
-int launch_gemm_f32(int cfg, const GemmF32Args& a, int64_t batch, bool vec_ok, hipStream_t s);
+int pick_config_f32(int64_t M, int64_t N, int64_t K, int64_t batch = 1);
+// The tile of the ring kernels: 0 64 x 64, 1 64 x 128 (vec only), 2 128 x 128.
+int pick_ring_f32(int64_t M, int64_t N, int64_t K, int64_t batch, bool vec);
+// any_rows: cfg came from pick_config_f32, whose choices serve any row
+// alignment; an explicit or tuned cfg other than 0 needs aligned rows.
+int launch_gemm_f32(int cfg, const GemmF32Args& a, int64_t batch, bool vec_ok, hipStream_t s, bool any_rows = false);
 
 int num_configs_f8();
 const char* config_f8_name(int cfg);

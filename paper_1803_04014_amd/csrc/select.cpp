@@ -103,15 +103,35 @@ int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok) {
     return 0;
 }
 
-// FP32: the 128 x 128 tiled kernel from 128 x 128 up (two wavefronts per
-// SIMD; alternating timings against 256 x 128 at N = 4096 / 8192 / 16384:
-// 122.6 / 125.1 / 126.1 against 120.8 / 122.0 / 121.7 TFLOP/s), the simple
-// kernel otherwise (or for unaligned rows).
-int pick_config_f32(int64_t M, int64_t N, int64_t K, bool vec_ok) {
-    (void)K;
-    if (!vec_ok) return 0;
-    if (M >= 128 && N >= 128) return 1;
-    return 0;
+// FP32: the simple kernel (one wavefront per 32 x 32 block, no LDS) for a
+// block or less of short K, or a batch of such (65536-sized batches of 16^3:
+// 33 us for 40000 against 78 us on a ring of 32 x 32 tiles), else the ring.
+int pick_config_f32(int64_t M, int64_t N, int64_t K, int64_t batch) {
+    return M <= 32 && N <= 32 && (K <= 32 || batch > 1) ? 0 : 1;
+}
+
+// The ring tile with the least estimated time: a start-up, then per round of
+// 256 tiles the tile's part of C and its 32-deep stages.  All are bound by
+// the matrix cores, so tiles sharing a CU take their times one after the
+// other; the larger ones spend a little less per flop, the smaller ones
+// waste less of the last round.  us per stage measured at 4096^3 (latency
+// included: at 128 x 128 x 4096 it is 0.63 / 1.12 / 2.08).
+int pick_ring_f32(int64_t M, int64_t N, int64_t K, int64_t batch, bool vec) {
+    struct {
+        int bm, bn;
+        double vec_us, any_us;
+    } const tile[] = {{64, 64, 0.545, 0.75}, {64, 128, 1.043, 0.0}, {128, 128, 2.086, 2.63}};
+    int best = 0;
+    double least = 0.0;
+    for (int i = 0; i < 3; ++i) {
+        const double us = vec ? tile[i].vec_us : tile[i].any_us;
+        if (us == 0.0) continue;
+        const double tiles = (double)cdiv(M, tile[i].bm) * (double)cdiv(N, tile[i].bn) * (double)batch;
+        const double t = (double)(int64_t)((tiles + 255.0) / 256.0) *
+                         (tile[i].bm * tile[i].bn * 4.0 / 20000.0 + (double)cdiv(K, 32) * us);
+        if (i == 0 || t < least) least = t, best = i;
+    }
+    return best;
 }
 
 }  // namespace mfg

@@ -69,3 +69,45 @@ def test_batched_entries_are_bitwise_solo(mode, shape):
         solo = torch.empty((M, N), device=DEV)
         mfg.gemm(A[i, :M, :K], B[i, :K, :N], solo, mode=mode, preconverted=True, config=0)
         assert torch.equal(C[i].view(torch.int32), solo.view(torch.int32)), i
+
+
+# FP32: edges of the 64 / 128 tiles and of the 32-deep stages, rows 16-byte aligned and not
+F32_SHAPES = [(1, 1, 1), (33, 32, 33), (64, 64, 64), (65, 130, 31), (129, 63, 100), (200, 333, 257), (127, 1100, 40),
+              (700, 900, 515), (1300, 1500, 260), (2050, 2052, 132)]
+
+
+@pytest.mark.parametrize("aligned", [True, False], ids=["aligned", "unaligned"])
+@pytest.mark.parametrize("shape", F32_SHAPES, ids=str)
+def test_f32_default_choice_is_bitwise_the_simple_kernel(shape, aligned):
+    M, N, K = shape
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K)
+
+    def matrix(rows, cols):
+        ld = -(-cols // 4) * 4 if aligned else cols + 3
+        buf = torch.full((rows, ld), float("nan"), device=DEV)
+        buf[:, :cols] = torch.rand((rows, cols), device=DEV, generator=gen).mul_(2).sub_(1)
+        return buf[:, :cols]
+
+    A, B, C0 = matrix(M, K), matrix(K, N), torch.rand((M, N), device=DEV, generator=gen)
+    for alpha, beta in ((1.0, 0.0), (1.25, -0.5)):
+        out = []
+        for config in (0, -1):
+            C = torch.full((M, N), float("nan"), device=DEV) if beta == 0.0 else C0.clone()
+            mfg.gemm(A, B, C, alpha, beta, mode="f32", config=config)
+            out.append(C)
+        assert torch.isfinite(out[0]).all()
+        assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32)), (alpha, beta)
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 16), (33, 40, 64), (40, 65, 33)], ids=str)
+def test_f32_batched_entries_are_bitwise_solo(shape):
+    M, N, K = shape
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    A = torch.rand((29, M, K), device=DEV, generator=gen)
+    B = torch.rand((29, K, N), device=DEV, generator=gen)
+    C = torch.full((29, M, N), float("nan"), device=DEV)
+    mfg.gemm_batched(A, B, C, mode="f32")
+    for i in range(29):
+        solo = torch.empty((M, N), device=DEV)
+        mfg.gemm(A[i], B[i], solo, mode="f32", config=0)
+        assert torch.equal(C[i].view(torch.int32), solo.view(torch.int32)), i
