@@ -69,6 +69,12 @@ int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int
         return convert16_pair(m, M, N, K, K, A, lda, B, ldb, a0, npa(m) == 2 ? a0 + M * lda_c : nullptr, lda_c, b0,
                               npb(m) == 2 ? b0 + K * ldb_c : nullptr, ldb_c, s);
     }
+    if (M > 0 && N > 0 && K > 0 && m == MFG_FP8_E4M3) {
+        uint8_t *qa = static_cast<uint8_t*>(wa), *qb = static_cast<uint8_t*>(wb);
+        const QuantJob ja{A, qa, reinterpret_cast<float*>(qa + mfg_fp8_scale_offset(M, lda_c)), M, K, lda, lda_c, M, K, 0};
+        const QuantJob jb{B, qb, reinterpret_cast<float*>(qb + mfg_fp8_scale_offset(K, ldb_c)), K, N, ldb, ldb_c, K, N, 0};
+        return launch_quantize_fp8_pair(ja, &jb, s);
+    }
     const int st = mfg_convert(M, K, A, lda, wa, lda_c, m, s);
     return st != MFG_OK ? st : mfg_convert(K, N, B, ldb, wb, ldb_c, m == MFG_F16_REFINE_A ? MFG_F16 : m, s);
 }
@@ -144,13 +150,15 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     if (m == MFG_FP8_E4M3) {
         GemmF8Args a{};
         a.M = M, a.N = N, a.K = K, a.C = C, a.ldc = ldc, a.alpha = alpha, a.beta = beta;
-        auto choose = [&](bool vec) {
+        // whole: the kernel will find A's and Bt's codes zero-filled to whole
+        // 128-deep stages
+        auto choose = [&](bool vec, bool whole) {
             if (config >= 0) return config;
             const int t = tuned_lookup(m, M, N, K);
             if (t >= 0 && config_f8_ok(t, M, N, K, ldc, vec)) return t;
-            return pick_config_f8(M, N, K, vec);
+            return pick_config_f8(M, N, K, vec, whole);
         };
-        const int64_t ldt = up(K, 16);                      // ld of the transposed B codes
+        const int64_t k128 = up(K, 128), ldt = k128;         // ld of the transposed B codes
         const int64_t bT = up(N * ldt, 256);
         if (pre) {
             a.A = static_cast<const uint8_t*>(A), a.lda = lda;
@@ -158,45 +166,60 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             a.sa = reinterpret_cast<const float*>(a.A + mfg_fp8_scale_offset(M, lda));
             a.sb = reinterpret_cast<const float*>(a.B + mfg_fp8_scale_offset(K, ldb));
             const bool vec = al16(A) && lda % 16 == 0 && buffer_ldc_ok(ldc) && lda < kF8LdLimit && ldt < kF8LdLimit;
-            const int cfg = choose(vec);
+            int cfg = choose(vec, K % 128 == 0);
             if (cfg < 0 || cfg >= num_configs_f8()) return MFG_ERR_INVALID_ARG;
+            if (f8_config_needs_bt(cfg) && (!vec || (config >= 0 && K % 128 != 0))) return MFG_ERR_UNSUPPORTED;
+            // the simple kernel, which needs no Bt, where Bt's padded rows exceed the
+            // fixed array or the transpose's grid
+            if (config < 0 && K % 128 != 0 && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535)) cfg = 0;
             if (!f8_config_needs_bt(cfg)) return launch_gemm_f8(cfg, a, vec, s);
-            if (!vec || K % 128 != 0) return MFG_ERR_UNSUPPORTED;
             CallWs ws;
             if ((st = call_ws(s, (size_t)bT, ext, ws)) != MFG_OK) return st;
             uint8_t* bt = static_cast<uint8_t*>(ws.ptr);
-            if ((st = launch_transpose_b8(K, N, a.B, ldb, bt, ldt, s)) != MFG_OK) return st;
+            if ((st = launch_transpose_b8(K, k128, N, a.B, ldb, bt, ldt, s)) != MFG_OK) return st;
             a.Bt = bt, a.ldbt = ldt;
-            return launch_gemm_f8(cfg, a, vec, s);
+            return launch_gemm_f8(cfg, a, vec, s, config < 0);
         }
-        const bool vec8 = buffer_ldc_ok(ldc) && up(K, 16) < kF8LdLimit;  // workspace codes: ld = K rounded up
-        const int cfg = choose(vec8);
+        // Workspace codes: A with rows of whole 128-deep stages, zero-filled, and
+        // B quantised straight into the K-contiguous layout likewise (zero codes
+        // add nothing), so every size runs on the tiled kernels.  Explicit and
+        // tuned configurations are judged on the caller's K.
+        const float *Af = static_cast<const float*>(A), *Bf = static_cast<const float*>(B);
+        const bool vec8 = buffer_ldc_ok(ldc) && k128 < kF8LdLimit;
+        int cfg = choose(vec8, true);
         if (cfg < 0 || cfg >= num_configs_f8()) return MFG_ERR_INVALID_ARG;
-        const bool need_bt = f8_config_needs_bt(cfg);
-        if (need_bt && K % 128 != 0) return MFG_ERR_UNSUPPORTED;
-        const int64_t ldk = up(K, 16), ldn = up(N, 16);
-        const int64_t bA = mfg_convert_bytes(M, K, ldk, MFG_FP8_E4M3);
-        // B: row-major codes and their scales, or for the tiled kernels only the
-        // scales, the codes being quantised straight into the K-contiguous layout
-        const int64_t bB = need_bt ? cdiv(K, MFG_FP8_TILE) * cdiv(N, MFG_FP8_TILE) * 4
-                                   : mfg_convert_bytes(K, N, ldn, MFG_FP8_E4M3);
-        CallWs ws;
-        if ((st = call_ws(s, (size_t)(up(bA, 256) + up(bB, 256) + (need_bt ? bT : 0)), ext, ws)) != MFG_OK) return st;
-        uint8_t* qa = static_cast<uint8_t*>(ws.ptr);
-        uint8_t* qb = qa + up(bA, 256);
-        float* sa = reinterpret_cast<float*>(qa + mfg_fp8_scale_offset(M, ldk));
-        float* sb = need_bt ? reinterpret_cast<float*>(qb) : reinterpret_cast<float*>(qb + mfg_fp8_scale_offset(K, ldn));
-        if ((st = launch_quantize_fp8(M, K, static_cast<const float*>(A), lda, qa, ldk, sa, s)) != MFG_OK) return st;
-        a.A = qa, a.lda = ldk, a.sa = sa, a.sb = sb, a.ldb = ldn;
-        if (need_bt) {
-            uint8_t* bt = qb + up(bB, 256);
-            if ((st = launch_quantize_fp8_t(K, N, static_cast<const float*>(B), ldb, bt, ldt, sb, s)) != MFG_OK)
-                return st;
+        if (f8_config_needs_bt(cfg) && config >= 0 && K % 128 != 0) return MFG_ERR_UNSUPPORTED;
+        const int64_t bA = mfg_fp8_scale_offset(M, k128) + 4 * cdiv(M, MFG_FP8_TILE) * cdiv(K, MFG_FP8_TILE);
+        const int64_t bS = 4 * cdiv(K, MFG_FP8_TILE) * cdiv(N, MFG_FP8_TILE);
+        const size_t tiled_bytes = (size_t)(up(bA, 256) + up(bS, 256) + bT);
+        // the fixed array's capacity is stated for unpadded codes: a call whose
+        // padding would not fit runs on the simple kernel
+        if (config < 0 && ext && tiled_bytes > ext->cap && (K % 128 != 0 || cfg == 2)) cfg = 0;
+        if (f8_config_needs_bt(cfg)) {
+            CallWs ws;
+            if ((st = call_ws(s, tiled_bytes, ext, ws)) != MFG_OK) return st;
+            uint8_t* qa = static_cast<uint8_t*>(ws.ptr);
+            float* sa = reinterpret_cast<float*>(qa + mfg_fp8_scale_offset(M, k128));
+            float* sb = reinterpret_cast<float*>(qa + up(bA, 256));
+            uint8_t* bt = qa + up(bA, 256) + up(bS, 256);
+            const QuantJob ja{Af, qa, sa, M, K, lda, k128, M, k128, 0}, jb{Bf, bt, sb, K, N, ldb, ldt, k128, N, 1};
+            if ((st = launch_quantize_fp8_pair(ja, &jb, s)) != MFG_OK) return st;
+            a.K = k128;
+            a.A = qa, a.lda = k128, a.sa = sa, a.sb = sb, a.ldb = up(N, 16);
             a.B = nullptr, a.Bt = bt, a.ldbt = ldt;
-        } else {
-            if ((st = launch_quantize_fp8(K, N, static_cast<const float*>(B), ldb, qb, ldn, sb, s)) != MFG_OK) return st;
-            a.B = qb;
+            return launch_gemm_f8(cfg, a, vec8, s, config < 0);
         }
+        const int64_t ldk = up(K, 16), ldn = up(N, 16);
+        const int64_t cA = mfg_convert_bytes(M, K, ldk, MFG_FP8_E4M3), cB = mfg_convert_bytes(K, N, ldn, MFG_FP8_E4M3);
+        CallWs ws;
+        if ((st = call_ws(s, (size_t)(up(cA, 256) + up(cB, 256)), ext, ws)) != MFG_OK) return st;
+        uint8_t* qa = static_cast<uint8_t*>(ws.ptr);
+        uint8_t* qb = qa + up(cA, 256);
+        float* sa = reinterpret_cast<float*>(qa + mfg_fp8_scale_offset(M, ldk));
+        float* sb = reinterpret_cast<float*>(qb + mfg_fp8_scale_offset(K, ldn));
+        const QuantJob ja{Af, qa, sa, M, K, lda, ldk, M, K, 0}, jb{Bf, qb, sb, K, N, ldb, ldn, K, N, 0};
+        if ((st = launch_quantize_fp8_pair(ja, &jb, s)) != MFG_OK) return st;
+        a.A = qa, a.lda = ldk, a.sa = sa, a.sb = sb, a.B = qb, a.ldb = ldn;
         return launch_gemm_f8(cfg, a, vec8, s);
     }
 
@@ -364,7 +387,7 @@ extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
     }
     if (m == MFG_FP8_E4M3) {
         const int t = tuned_lookup(m, M, N, K);
-        return (t >= 0 && t < num_configs_f8()) ? t : pick_config_f8(M, N, K, true);
+        return (t >= 0 && t < num_configs_f8()) ? t : pick_config_f8(M, N, K, true, !(mode & MFG_IN_PRECONVERTED) || K % 128 == 0);
     }
     if (m == MFG_BF16_SPLIT6) return choose_split6(-1, M, N, K, N, true);
     if (!(mode & MFG_IN_PRECONVERTED)) {  // FP32 operands: a tuned fused kernel where the shape allows it

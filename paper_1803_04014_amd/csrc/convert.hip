@@ -464,35 +464,47 @@ int launch_convert_jobs(const ConvJob* jobs, const ConvTask* tasks, int64_t ntas
 }
 
 // ---------------------------------------------------------------- FP8 quant
-// One workgroup per 128 x 128 tile.  Thread t holds columns 4 (t % 32) .. +3
-// of rows t / 32 + 8 i, i = 0..15 (a wavefront reads two full 512-byte rows
-// per load) in registers, so the tile is read from memory once: amax over
-// the tile, the tile's power-of-two scale, then the codes.  Elements outside
-// the matrix count as 0 (they cannot raise the amax) and are not written.
-// TRANS: the codes are written transposed (the code of X[r][c] at
-// codes[c * ldo + r]) through LDS in 16-byte row pieces -- B's codes in the
-// K-contiguous layout the tiled FP8 kernels read; `scales` keep the
-// untransposed tile order.
-template <bool TRANS>
-__global__ __launch_bounds__(256) void quant_fp8_kernel(int64_t rows, int64_t cols, const float* X, int64_t ldx,
-                                                        uint8_t* codes, int64_t ldo, float* scales, int vec) {
-    const int64_t r0 = (int64_t)blockIdx.y * MFG_FP8_TILE, c0 = (int64_t)blockIdx.x * MFG_FP8_TILE;
-    const int t = threadIdx.x;
-    const int64_t cc = c0 + (t & 31) * 4;
-    const bool whole = vec && r0 + MFG_FP8_TILE <= rows && c0 + MFG_FP8_TILE <= cols;
+// One workgroup per 128 x 128 tile of one of two matrices (both operands of a
+// GEMM in one launch: workgroups below `tiles_a` take job a).  Thread t holds
+// columns 4 (t % 32) .. +3 of rows 16 (t / 32) .. +15 in registers (a
+// wavefront reads two 512-byte row pieces per load), so the tile is read from
+// memory once, all its loads in flight together: amax over the tile, the
+// tile's power-of-two scale, then the codes.  Elements outside the matrix
+// count as 0 (they cannot raise the amax).
+// trans: the codes are written transposed (the code of X[r][c] at
+// codes[c * ldo + r], the K-contiguous layout the tiled FP8 kernels read): a
+// thread's 16 rows of a column are 16 consecutive bytes there, put together
+// in registers and exchanged through LDS so that whole 128-byte rows go out;
+// `scales` keep the untransposed tile order.
+// The output covers orows x ocols source positions, zero codes beyond the
+// source.  HBM-bound: 4 B read and 1 B written per element; both 4096^2
+// operands 50 us in two launches, @Q us in one.
+__global__ __launch_bounds__(256) void quant_fp8_kernel(QuantJob ja, QuantJob jb, uint32_t tiles_a) {
+    const bool second = blockIdx.x >= tiles_a;
+    const QuantJob& j = second ? jb : ja;
+    const float* X = j.X;
+    uint8_t* codes = j.codes;
+    const int64_t rows = j.rows, cols = j.cols, ldx = j.ldx, ldo = j.ldo;
+    const uint32_t tc = (uint32_t)cdiv(cols, MFG_FP8_TILE), tile = second ? blockIdx.x - tiles_a : blockIdx.x;
+    const uint32_t ti = tile / tc, tj = tile - ti * tc;
+    const int64_t r0 = (int64_t)ti * MFG_FP8_TILE, c0 = (int64_t)tj * MFG_FP8_TILE;
+    const int t = threadIdx.x, rg = t >> 5;
+    const int64_t rb = r0 + 16 * rg, cc = c0 + (t & 31) * 4;
     f32x4 v[16];
-    if (whole) {
+    if (cc + 4 <= cols) {  // rows past the matrix read its last one, then count as 0
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            v[i] = *reinterpret_cast<const f32x4*>(X + (r0 + (t >> 5) + 8 * i) * ldx + cc);
+            v[i] = *reinterpret_cast<const f32x4_any*>(X + (rb + i < rows ? rb + i : rows - 1) * ldx + cc);
     } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int64_t r = r0 + (t >> 5) + 8 * i;
+        for (int i = 0; i < 16; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[i][j] = (r < rows && cc + j < cols) ? X[r * ldx + cc + j] : 0.0f;
-        }
+            for (int q = 0; q < 4; ++q) v[i][q] = (rb + i < rows && cc + q < cols) ? X[(rb + i) * ldx + cc + q] : 0.0f;
     }
+    if (r0 + MFG_FP8_TILE > rows)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (rb + i >= rows) v[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     float amax = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i)
@@ -507,83 +519,85 @@ __global__ __launch_bounds__(256) void quant_fp8_kernel(int64_t rows, int64_t co
     amax = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
     const int E = fp8_scale_exp(amax);
     const float inv = __builtin_ldexpf(1.0f, -E);
-    if (t == 0) scales[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = __builtin_ldexpf(1.0f, E);
-    uint32_t w[16];  // the four codes of each register
+    if (t == 0) j.scales[tile] = __builtin_ldexpf(1.0f, E);
+    uint32_t w[16];  // the four codes of each row
 #pragma unroll
     for (int i = 0; i < 16; ++i)
         w[i] = (uint32_t)f32_to_e4m3_sat(v[i][0] * inv) | ((uint32_t)f32_to_e4m3_sat(v[i][1] * inv) << 8) |
                ((uint32_t)f32_to_e4m3_sat(v[i][2] * inv) << 16) | ((uint32_t)f32_to_e4m3_sat(v[i][3] * inv) << 24);
-    if constexpr (!TRANS) {
-        const bool vec_out = whole && (((uintptr_t)codes % 4) == 0) && (ldo % 4 == 0);
+    if (!j.trans) {
+        const bool words = cc + 4 <= j.ocols && ((uintptr_t)codes % 4) == 0 && ldo % 4 == 0;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int64_t r = r0 + (t >> 5) + 8 * i;
-            uint8_t* o = codes + r * ldo;
-            if (vec_out) {
+            if (rb + i >= j.orows) continue;
+            uint8_t* o = codes + (rb + i) * ldo;
+            if (words) {
                 *reinterpret_cast<uint32_t*>(o + cc) = w[i];
-            } else if (r < rows) {
-                for (int j = 0; j < 4; ++j)
-                    if (cc + j < cols) o[cc + j] = (uint8_t)(w[i] >> (8 * j));
+            } else {
+                for (int q = 0; q < 4; ++q)
+                    if (cc + q < j.ocols) o[cc + q] = (uint8_t)(w[i] >> (8 * q));
             }
         }
     } else {
-        // tile rows (source) x 32 words; row r, word q holds columns 4q .. 4q+3
-        __shared__ uint32_t sq[MFG_FP8_TILE][33];
+        // column q of rows 4 k .. 4 k + 3 of the thread: one word of its 16 bytes
+        __shared__ u32x4 sq[MFG_FP8_TILE][8];  // [column][16-row piece, XOR-swizzled]
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sq[(t >> 5) + 8 * i][t & 31] = w[i];
-        __syncthreads();
-        // thread t: output row c0 + t / 2 (source column), source rows 64 (t % 2) .. +63
-        const int oc = t >> 1, rb = 64 * (t & 1), sh = 8 * (oc & 3), qw = oc >> 2;
-        u32x4 o[4];
+        for (int q = 0; q < 4; ++q) {
+            u32x4 o;
+            const uint32_t sel = 0x0c0c0400u + 0x0101u * q;  // byte q of the second, then of the first operand
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            uint32_t x = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) x |= ((sq[rb + 4 * q + b][qw] >> sh) & 0xFFu) << (8 * b);
-            o[q >> 2][q & 3] = x;
+            for (int k = 0; k < 4; ++k)
+                o[k] = __builtin_amdgcn_perm(w[4 * k + 1], w[4 * k], sel) |
+                       (__builtin_amdgcn_perm(w[4 * k + 3], w[4 * k + 2], sel) << 16);
+            const int col = (t & 31) * 4 + q;
+            sq[col][rg ^ ((t >> 1) & 7)] = o;  // (t >> 1) & 7 == (col >> 3) & 7
         }
-        uint8_t* d = codes + (c0 + oc) * ldo + r0 + rb;
-        if (whole && ((uintptr_t)codes % 16) == 0 && ldo % 16 == 0) {
+        __syncthreads();
+        const bool whole = ((uintptr_t)codes % 16) == 0 && ldo % 16 == 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) *reinterpret_cast<u32x4*>(d + 16 * k) = o[k];
-        } else if (c0 + oc < cols) {
-            for (int j = 0; j < 64; ++j)
-                if (r0 + rb + j < rows) d[j] = (uint8_t)(o[j >> 4][(j >> 2) & 3] >> (8 * (j & 3)));
+        for (int k = 0; k < 4; ++k) {
+            const int col = (t >> 3) + 32 * k, piece = t & 7;
+            if (c0 + col >= j.ocols) continue;
+            const u32x4 o = sq[col][piece ^ ((col >> 3) & 7)];
+            const int64_t r = r0 + 16 * piece;
+            uint8_t* d = codes + (c0 + col) * ldo + r;
+            if (whole && r + 16 <= j.orows) {
+                *reinterpret_cast<u32x4*>(d) = o;
+            } else {
+                for (int e = 0; e < 16; ++e)
+                    if (r + e < j.orows) d[e] = (uint8_t)(o[e >> 2] >> (8 * (e & 3)));
+            }
         }
     }
+}
+
+// a, b: rows, cols >= 1; the output extent within the source's tiles.  b may
+// be null.
+int launch_quantize_fp8_pair(const QuantJob& a, const QuantJob* b, hipStream_t s) {
+    const int64_t ta = cdiv(a.rows, MFG_FP8_TILE) * cdiv(a.cols, MFG_FP8_TILE);
+    const int64_t tb = b ? cdiv(b->rows, MFG_FP8_TILE) * cdiv(b->cols, MFG_FP8_TILE) : 0;
+    if (cdiv(a.rows, MFG_FP8_TILE) > 65535 || (b && cdiv(b->rows, MFG_FP8_TILE) > 65535) || ta + tb > 0x7FFFFFFF)
+        return MFG_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(quant_fp8_kernel, dim3((unsigned)(ta + tb)), dim3(256), 0, s, a, b ? *b : a, (uint32_t)ta);
+    MFG_LAUNCH_CHECK();
+    return MFG_OK;
 }
 
 int launch_quantize_fp8(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint8_t* codes, int64_t ldo,
                         float* scales, hipStream_t s) {
     if (rows == 0 || cols == 0) return MFG_OK;
-    const int64_t tr = cdiv(rows, MFG_FP8_TILE), tc = cdiv(cols, MFG_FP8_TILE);
-    if (tr > 65535) return MFG_ERR_UNSUPPORTED;
-    const int vec = aligned(X, ldx, 16, 4);
-    hipLaunchKernelGGL(quant_fp8_kernel<false>, dim3((unsigned)tc, (unsigned)tr), dim3(256), 0, s, rows, cols, X, ldx,
-                       codes, ldo, scales, vec);
-    MFG_LAUNCH_CHECK();
-    return MFG_OK;
-}
-
-int launch_quantize_fp8_t(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint8_t* codes_t, int64_t ldt,
-                          float* scales, hipStream_t s) {
-    if (rows == 0 || cols == 0) return MFG_OK;
-    const int64_t tr = cdiv(rows, MFG_FP8_TILE), tc = cdiv(cols, MFG_FP8_TILE);
-    if (tr > 65535) return MFG_ERR_UNSUPPORTED;
-    const int vec = aligned(X, ldx, 16, 4);
-    hipLaunchKernelGGL(quant_fp8_kernel<true>, dim3((unsigned)tc, (unsigned)tr), dim3(256), 0, s, rows, cols, X, ldx,
-                       codes_t, ldt, scales, vec);
-    MFG_LAUNCH_CHECK();
-    return MFG_OK;
+    return launch_quantize_fp8_pair(QuantJob{X, codes, scales, rows, cols, ldx, ldo, rows, cols, 0}, nullptr, s);
 }
 
 // ------------------------------------------------------------ byte transpose
-// dst (cols x rows, ld ldd) = src^T (src rows x cols, ld lds), bytes.  One
+// dst (cols x orows, ld ldd) = src^T (src rows x cols, ld lds), bytes, zero
+// from source row `rows` to orows.  One
 // workgroup per 64 x 64 tile through LDS: each thread reads 16 bytes of a
 // source row and writes 16 bytes of a destination row (vector path when the
 // tile is whole and both matrices have 16-byte rows), bytewise otherwise.
-__global__ __launch_bounds__(256) void transpose_b8_kernel(int64_t rows, int64_t cols, const uint8_t* src,
-                                                           int64_t lds, uint8_t* dst, int64_t ldd, int vec) {
+__global__ __launch_bounds__(256) void transpose_b8_kernel(int64_t rows, int64_t orows, int64_t cols,
+                                                           const uint8_t* src, int64_t lds, uint8_t* dst, int64_t ldd,
+                                                           int vec) {
     __shared__ uint8_t tile[64][64 + 4];
     const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
     const int t = threadIdx.x, tr = t >> 2, tc = (t & 3) * 16;
@@ -612,19 +626,19 @@ __global__ __launch_bounds__(256) void transpose_b8_kernel(int64_t rows, int64_t
     } else {
         for (int j = 0; j < 16; ++j) {
             const int64_t c = c0 + tr, r = r0 + tc + j;
-            if (c < cols && r < rows) dst[c * ldd + r] = tile[tc + j][tr];
+            if (c < cols && r < orows) dst[c * ldd + r] = tile[tc + j][tr];
         }
     }
 }
 
-int launch_transpose_b8(int64_t rows, int64_t cols, const uint8_t* src, int64_t lds, uint8_t* dst, int64_t ldd,
-                        hipStream_t s) {
+int launch_transpose_b8(int64_t rows, int64_t orows, int64_t cols, const uint8_t* src, int64_t lds, uint8_t* dst,
+                        int64_t ldd, hipStream_t s) {
     if (rows == 0 || cols == 0) return MFG_OK;
-    const int64_t gr = cdiv(rows, 64), gc = cdiv(cols, 64);
+    const int64_t gr = cdiv(orows, 64), gc = cdiv(cols, 64);
     if (gr > 65535) return MFG_ERR_UNSUPPORTED;
     const int vec = aligned(src, lds, 16, 16) && aligned(dst, ldd, 16, 16);
-    hipLaunchKernelGGL(transpose_b8_kernel, dim3((unsigned)gc, (unsigned)gr), dim3(256), 0, s, rows, cols, src, lds,
-                       dst, ldd, vec);
+    hipLaunchKernelGGL(transpose_b8_kernel, dim3((unsigned)gc, (unsigned)gr), dim3(256), 0, s, rows, orows, cols, src,
+                       lds, dst, ldd, vec);
     MFG_LAUNCH_CHECK();
     return MFG_OK;
 }

@@ -12,6 +12,7 @@
 #include "device.h"
 #include "internal.h"
 #include "pipe16.h"
+#include "ring16.h"
 #include "runtime.h"
 
 namespace mfg {
@@ -288,14 +289,170 @@ __global__ __launch_bounds__(64 * WM * WN) void gemmf8_pipe(GemmF8Args p, int ti
                        [&](int fm, int fn, int i) { return acc[fm][fn][i]; });
 }
 
+// ---------------------------------------------------------------------------
+// gemmf8_ring: the FP8 kernel for small tiles and any K.  Bound, like
+// gemm16_ring, by the latency of a stage's loads and by what each CU draws
+// from L2 (16 KB per 64 x 64 stage of 128 codes against 128 MFMA cycles).
+// Measured against the simple kernel, which served K % 128 != 0 and every
+// small problem: 777 x 1234 x 1999 93 -> 8.2 us, 1000^3 47 -> 5.5, 256^3
+// 8.4 -> 3.0; 4000 x 4000 x 4001 75 us.
+// Same layout, reads and accumulation order as gemmf8_pipe.  A's 16-byte
+// pieces at or past K come from zeros and the straddling piece is cleared in
+// LDS (A is the caller's: what lies past K may be any code, NaN included);
+// Bt is the library's, zero-filled to whole stages.
+template <int BM, int BN, int WM, int WN, int S, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemmf8_ring(GemmF8Args p, int tiles_m, int tiles_n, int group_m) {
+    using G = F8Cfg<BM, BN, WM, WN, S>;
+    constexpr int FM = G::FM, FN = G::FN, BK = G::BK;
+    __shared__ __attribute__((aligned(16))) uint8_t st0[G::STAGE];
+    __shared__ __attribute__((aligned(16))) uint8_t st1[G::STAGE];
+    __shared__ __attribute__((aligned(16))) uint8_t st2[S > 2 ? G::STAGE : 16];
+    auto stage = [&](int s) -> uint8_t* { return s == 0 ? st0 : (S == 2 || s == 1) ? st1 : st2; };
+
+    int tm, tn;
+    raster(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
+    const int64_t M = p.M, N = p.N, K = uniform64(p.K);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wid / WN, wn = wid % WN;
+    const int64_t KTN = uniform64((K + BK - 1) / BK);
+    // scales of this wave's rows and columns, by scalar loads
+    typedef __attribute__((address_space(4))) const float c_f32;
+    const int64_t ntiles = cdiv(N, MFG_FP8_TILE), mtiles = cdiv(M, MFG_FP8_TILE);
+    const int64_t mt = min((m0 + wm * G::TMW) / MFG_FP8_TILE, mtiles - 1);
+    const int64_t nt = min((n0 + wn * G::TNW) / MFG_FP8_TILE, ntiles - 1);
+    const c_f32* sa = (const c_f32*)uniform64((int64_t)(p.sa + mt * KTN));
+    const c_f32* sb = (const c_f32*)uniform64((int64_t)(p.sb + nt));
+    const int64_t nts = uniform64(ntiles);
+
+    const uint8_t* a = (const uint8_t*)uniform64((int64_t)(p.A + m0 * p.lda));
+    const uint8_t* b = (const uint8_t*)uniform64((int64_t)(p.Bt + n0 * p.ldbt));
+    uint32_t offa[G::A_INSTR], offb[G::B_INSTR];
+    int ka[G::A_INSTR];
+#pragma unroll
+    for (int i = 0; i < G::A_INSTR; ++i) {
+        const int row = (wid * G::A_INSTR + i) * 8 + (lane >> 3);
+        ka[i] = ((lane & 7) ^ swz<8>(row)) * 16;
+        offa[i] = (uint32_t)(((m0 + row < M ? m0 + row : M - 1) - m0) * p.lda + ka[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < G::B_INSTR; ++i) {
+        const int row = (wid * G::B_INSTR + i) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ swz<8>(row);
+        offb[i] = (uint32_t)(((n0 + row < N ? n0 + row : N - 1) - n0) * p.ldbt + c * 16);
+    }
+    auto load = [&](int64_t t, uint8_t* st) {  // stage t (t >= KTN: stage KTN - 1 again, never read)
+        const int64_t k0 = uniform64(min(t, KTN - 1) * BK);
+        const int kl = (int)min(uniform64(K - k0), (int64_t)BK);
+#pragma unroll
+        for (int i = 0; i < G::A_INSTR; ++i)
+            __builtin_amdgcn_global_load_lds((const void*)(ka[i] < kl ? a + k0 + offa[i] : (const uint8_t*)kZeros16),
+                                             (lds_void*)(st + (wid * G::A_INSTR + i) * 1024), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < G::B_INSTR; ++i)
+            __builtin_amdgcn_global_load_lds((const void*)(b + k0 + offb[i]),
+                                             (lds_void*)(st + G::A_PLANE + (wid * G::B_INSTR + i) * 1024), 16, 0, 0);
+    };
+
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
+    int oa[FM][4], ob[FN][4];  // byte offsets of the lane's two pieces per half stage
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int piece = (c >> 1) * 4 + (lane >> 5) * 2 + (c & 1);
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm) {
+            const int row = wm * G::TMW + fm * 32 + (lane & 31);
+            oa[fm][c] = row * 128 + ((piece ^ swz<8>(row)) << 4);
+            opaque(oa[fm][c]);
+        }
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) {
+            const int row = wn * G::TNW + fn * 32 + (lane & 31);
+            ob[fn][c] = G::A_PLANE + row * 128 + ((piece ^ swz<8>(row)) << 4);
+            opaque(ob[fn][c]);
+        }
+    }
+    auto row32 = [](const uint8_t* lo_at, const uint8_t* hi_at) {
+        const u32x4 lo = *reinterpret_cast<const u32x4*>(lo_at), hi = *reinterpret_cast<const u32x4*>(hi_at);
+        return i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+    };
+    auto multiply = [&](const uint8_t* st, int ca, int cb) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            i32x8 af[FM], bf[FN];
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm) af[fm] = row32(st + oa[fm][2 * h], st + oa[fm][2 * h + 1]);
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn) bf[fn] = row32(st + ob[fn][2 * h], st + ob[fn][2 * h + 1]);
+#pragma unroll
+            for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+                for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = mma_32x32x64_e4m3(af[fm], bf[fn], acc[fm][fn], ca, cb);
+        }
+    };
+
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) load(s, stage(s));
+    float va = sa[0], vb = sb[0];
+    auto step = [&](auto ucst, int64_t t) {  // as in gemm16_ring
+        constexpr int u = decltype(ucst)::value;
+        wait_vmcnt<G::LOADS * (S - 2)>();
+        wait_lgkm0();
+        bare_barrier();
+        load(t + S - 1, stage((u + S - 1) % S));
+        __builtin_amdgcn_sched_barrier(0);
+        const int ca = e8m0_code(va), cb = e8m0_code(vb);
+        va = sa[t + 1], vb = sb[(t + 1) * nts];  // t + 1 <= KTN - 1
+        multiply(stage(u), ca, cb);
+    };
+    const int64_t last = KTN - 1, whole = last - last % S;
+    for (int64_t t = 0; t < whole; t += S) {
+        step(std::integral_constant<int, 0>{}, t);
+        step(std::integral_constant<int, 1>{}, t + 1);
+        if constexpr (S > 2) step(std::integral_constant<int, 2>{}, t + 2);
+    }
+    if (whole < last) step(std::integral_constant<int, 0>{}, whole);
+    if constexpr (S > 2)
+        if (whole + 1 < last) step(std::integral_constant<int, 1>{}, whole + 1);
+    uint8_t* tail = stage((int)(last - whole));
+    wait_vmcnt<0>();
+    wait_lgkm0();
+    bare_barrier();
+    const int kl = (int)(K - last * BK), keep = kl & 15;
+    if (keep != 0) {  // clear A's codes at or past K in the piece that straddles it
+        for (int row = tid; row < BM; row += G::NT) {
+            u32x4* q = reinterpret_cast<u32x4*>(tail + row * 128 + (((kl >> 4) ^ swz<8>(row)) << 4));
+            u32x4 v = *q;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int left = keep - 4 * d;
+                v[d] &= left >= 4 ? 0xFFFFFFFFu : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
+            }
+            *q = v;
+        }
+        wait_lgkm0();
+        bare_barrier();
+    }
+    multiply(tail, e8m0_code(va), e8m0_code(vb));
+
+    store_tile<FM, FN>(p.C, p.ldc, M, N, m0 + wm * G::TMW, n0 + wn * G::TNW, lane, p.alpha, p.beta,
+                       [&](int fm, int fn, int i) { return acc[fm][fn][i]; });
+}
+
 struct CfgF8 {
     const char* name;
     int bm, bn, wm, wn, s, group_m;
 };
+// Index 2 is the ring kernels (tile by pick_ring_f8), faster at every size
+// measured than the pipelined 128 x 128 tile (2048^3: 14.1 against 16.9 us).
 static const CfgF8 kCfgF8[] = {
     {"simple32", 0, 0, 0, 0, 0, 0},
     {"p256x256k128s2w2x2g8", 256, 256, 2, 2, 2, 8},
-    {"p128x128k128s3w2x2g8", 128, 128, 2, 2, 3, 8},
+    {"pring-k128g8", 64, 64, 2, 2, 2, 8},
     {"p256x128k128s2w2x2g8", 256, 128, 2, 2, 2, 8},
     {"p256x256k128s2w2x2g8e", 256, 256, 2, 2, 2, 8},
 };
@@ -311,6 +468,15 @@ static int launch_f8_pipe(const GemmF8Args& a, int group_m, hipStream_t s) {
     return MFG_OK;
 }
 
+template <int BM, int BN, int S, int OCC>
+static int launch_f8_ring(const GemmF8Args& a, int group_m, hipStream_t s) {
+    const int tiles_m = (int)cdiv(a.M, BM), tiles_n = (int)cdiv(a.N, BN);
+    hipLaunchKernelGGL((gemmf8_ring<BM, BN, 2, 2, S, OCC>), dim3(tiles_m * tiles_n), dim3(256), 0, s, a, tiles_m,
+                       tiles_n, group_m);
+    MFG_LAUNCH_CHECK();
+    return MFG_OK;
+}
+
 int num_configs_f8() { return kNumF8; }
 const char* config_f8_name(int cfg) { return (cfg >= 0 && cfg < kNumF8) ? kCfgF8[cfg].name : nullptr; }
 bool f8_config_needs_bt(int cfg) { return cfg > 0 && cfg < kNumF8; }
@@ -320,8 +486,9 @@ bool config_f8_ok(int cfg, int64_t M, int64_t N, int64_t K, int64_t ldc, bool ve
     return vec_ok && K % 128 == 0 && M >= 1 && N >= 1 && buffer_ldc_ok(ldc);
 }
 
-// The tiled kernels need K % 128 == 0, 16-byte aligned rows of A and Bt.
-int launch_gemm_f8(int cfg, const GemmF8Args& a, bool vec_ok, hipStream_t s) {
+// The tiled kernels need 16-byte aligned rows of A and Bt (Bt's zero-filled to
+// whole 128-deep stages), all but the ring kernels K % 128 == 0.
+int launch_gemm_f8(int cfg, const GemmF8Args& a, bool vec_ok, hipStream_t s, bool any_k) {
     if (fault_hit(kFaultLaunch)) return hip_fail(hipErrorLaunchFailure);  // injected (tests)
     if (cfg < 0 || cfg >= kNumF8) return MFG_ERR_INVALID_ARG;
     if (cfg == 0) {
@@ -331,11 +498,17 @@ int launch_gemm_f8(int cfg, const GemmF8Args& a, bool vec_ok, hipStream_t s) {
         return MFG_OK;
     }
     const bool bt_ok = a.Bt != nullptr && ((uintptr_t)a.Bt % 16) == 0 && a.ldbt % 16 == 0;
-    if (!vec_ok || !bt_ok || a.K % 128 != 0 || a.M < 1 || a.N < 1 || !buffer_ldc_ok(a.ldc)) return MFG_ERR_UNSUPPORTED;
+    if (!vec_ok || !bt_ok || (a.K % 128 != 0 && !(any_k && cfg == 2)) || a.M < 1 || a.N < 1 || !buffer_ldc_ok(a.ldc)) return MFG_ERR_UNSUPPORTED;
     const CfgF8& c = kCfgF8[cfg];
+    if (cfg == 2) {
+        switch (pick_ring_f8(a.M, a.N, a.K)) {
+            case 1: return launch_f8_ring<64, 128, 3, 2>(a, c.group_m, s);
+            case 2: return launch_f8_ring<128, 128, 2, 2>(a, c.group_m, s);
+            default: return launch_f8_ring<64, 64, 2, 4>(a, c.group_m, s);
+        }
+    }
     if (cfg == 4) return launch_f8_pipe<256, 256, 2, 2, 2, true>(a, c.group_m, s);
     if (c.bm == 256 && c.bn == 256) return launch_f8_pipe<256, 256, 2, 2, 2>(a, c.group_m, s);
-    if (c.bm == 128 && c.bn == 128) return launch_f8_pipe<128, 128, 2, 2, 3>(a, c.group_m, s);
     if (c.bm == 256 && c.bn == 128) return launch_f8_pipe<256, 128, 2, 2, 2>(a, c.group_m, s);
     return MFG_ERR_INTERNAL;
 }

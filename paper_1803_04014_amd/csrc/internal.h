@@ -118,11 +118,18 @@ int launch_gemm_f32(int cfg, const GemmF32Args& a, int64_t batch, bool vec_ok, h
 
 int num_configs_f8();
 const char* config_f8_name(int cfg);
-int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok);
-int launch_gemm_f8(int cfg, const GemmF8Args& a, bool vec_ok, hipStream_t s);
+// vec_ok: 16-byte aligned rows of A's codes; whole: Bt and A zero-filled to
+// whole 128-deep stages (a.K a multiple of 128).
+int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool whole);
+// The ring kernels' tile: 0 64 x 64, 1 64 x 128, 2 128 x 128.
+int pick_ring_f8(int64_t M, int64_t N, int64_t K);
+// any_k: cfg came from pick_config_f8; an explicit or tuned tiled cfg needs
+// K % 128 == 0.
+int launch_gemm_f8(int cfg, const GemmF8Args& a, bool vec_ok, hipStream_t s, bool any_k = false);
 bool f8_config_needs_bt(int cfg);
-int launch_transpose_b8(int64_t rows, int64_t cols, const uint8_t* src, int64_t lds, uint8_t* dst, int64_t ldd,
-                        hipStream_t s);
+// dst (cols x orows) = src^T (rows x cols bytes), zero from row `rows` on.
+int launch_transpose_b8(int64_t rows, int64_t orows, int64_t cols, const uint8_t* src, int64_t lds, uint8_t* dst,
+                        int64_t ldd, hipStream_t s);
 
 // Conversions (convert.hip).
 int launch_round_f16(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint16_t* out,
@@ -137,10 +144,18 @@ int launch_split6_bf16(int64_t rows, int64_t cols, const float* X, int64_t ldx, 
                        int64_t kp, bool side_b, hipStream_t s);
 int launch_quantize_fp8(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint8_t* codes,
                         int64_t ldo, float* scales, hipStream_t s);
-// The same codes written transposed (code of X[r][c] at codes_t[c * ldt + r]),
-// scales in the untransposed tile order.
-int launch_quantize_fp8_t(int64_t rows, int64_t cols, const float* X, int64_t ldx, uint8_t* codes_t, int64_t ldt,
-                          float* scales, hipStream_t s);
+// One FP8 quantisation: codes (ld ldo) of X (rows x cols), transposed if
+// `trans` (code of X[r][c] at codes[c * ldo + r]), scales in the tile order of
+// X; the codes cover orows x ocols source positions (at least rows x cols,
+// within its 128 x 128 tiles), zero beyond the source.
+struct QuantJob {
+    const float* X;
+    uint8_t* codes;
+    float* scales;
+    int64_t rows, cols, ldx, ldo, orows, ocols;
+    int32_t trans;
+};
+int launch_quantize_fp8_pair(const QuantJob& a, const QuantJob* b, hipStream_t s);
 // Conversion jobs: one matrix, rows x cols FP32 at src (ld lds, any
 // alignment) into 16-bit library planes at dst (16-byte aligned, ld ldo a
 // multiple of 8); kind 0 rne16, 1 rnebf16, 2 FP16 split (head at dst, scaled

@@ -54,18 +54,28 @@ static const Cost16 kCostSplit4[] = {
     {5, 0, 128, 128, false, 5.0f, 1.12f, 1.64f},
 };
 
-static double cost16(const Cost16& c, int64_t M, int64_t N, int64_t K, int64_t batch) {
+// stages: K stages; ring_cost: factor on the ring kernels' full stages.
+static double cost16(const Cost16& c, int64_t M, int64_t N, int64_t stages, int64_t batch, double ring_cost) {
     constexpr double kCus = 256.0, kCBytesPerUs = 20000.0;  // per CU: a 256th of 5.1 TB/s
     const double tiles = (double)cdiv(M, c.bm) * (double)cdiv(N, c.bn) * (double)batch;
-    const double stages = (double)cdiv(K, 64), load = tiles < kCus ? tiles / kCus : 1.0;
+    const double load = tiles < kCus ? tiles / kCus : 1.0;
     const double n = tiles <= kCus ? 1.0 : (double)(int64_t)((tiles + kCus - 1.0) / kCus);
-    const double ctime = c.bm * c.bn * 4.0 / kCBytesPerUs * load;
+    const double ctime = c.bm * c.bn * 4.0 / kCBytesPerUs * load, full = c.full * ring_cost;
     double stage = c.lat + (c.full - c.lat) * load;
-    // rows of K % 64 != 0 are not whole 128-byte lines: the small tiles draw up
-    // to a fifth more of them (SPLIT4 3000^3: 0.69 us per stage, 4096^3: 0.55)
-    const double full = K % 64 != 0 ? 1.2 * c.full : c.full;
     if (c.shared) stage = (n * full > c.lat ? n * full : c.lat) / n;
-    return c.start + n * (ctime + stages * stage);
+    return c.start + n * (ctime + (double)stages * stage);
+}
+
+static const Cost16& least_cost(const Cost16* c, int n, int64_t M, int64_t N, int64_t stages, int64_t batch,
+                                double ring_cost, bool ring_only) {
+    int best = 0;
+    double least = cost16(c[0], M, N, stages, batch, ring_cost);
+    for (int i = 1; i < n; ++i) {
+        if (ring_only && !c[i].shared) continue;
+        const double t = cost16(c[i], M, N, stages, batch, ring_cost);
+        if (t < least) least = t, best = i;
+    }
+    return c[best];
 }
 
 static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch, bool ring_only) {
@@ -74,14 +84,9 @@ static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t b
     if (kind == K_F16 || kind == K_BF16) c = kCostPlain, n = (int)(sizeof(kCostPlain) / sizeof(Cost16));
     else if (kind == K_REFINE_A) c = kCostRefineA, n = (int)(sizeof(kCostRefineA) / sizeof(Cost16));
     else if (kind == K_SPLIT4) c = kCostSplit4, n = (int)(sizeof(kCostSplit4) / sizeof(Cost16));
-    int best = 0;
-    double least = cost16(c[0], M, N, K, batch);
-    for (int i = 1; i < n; ++i) {
-        if (ring_only && !c[i].shared) continue;
-        const double t = cost16(c[i], M, N, K, batch);
-        if (t < least) least = t, best = i;
-    }
-    return c[best];
+    // rows of K % 64 != 0 are not whole 128-byte lines: the small tiles draw up
+    // to a fifth more of them (SPLIT4 3000^3: 0.69 us per stage, 4096^3: 0.55)
+    return least_cost(c, n, M, N, cdiv(K, 64), batch, K % 64 != 0 ? 1.2 : 1.0, ring_only);
 }
 
 // Index 0, the simple kernel, where rows are not 16-byte aligned.
@@ -93,15 +98,26 @@ int pick_ring16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch) {
     return pick16(kind, M, N, K, batch, true).variant;
 }
 
-// Default: the tiled kernels once the grid fills the chip (measured sweeps,
-// square N = 1024 .. 8192), else the simple kernel.
-int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok) {
-    if (!vec_ok || K % 128 != 0 || M < 1 || N < 1) return 0;
-    if (cdiv(M, 256) * cdiv(N, 256) >= 256) return 4;  // p256x256k128s2w2x2g8e (4096^2: 1.78 vs 1.58 PF for p256x128)
-    if (cdiv(M, 256) * cdiv(N, 128) >= 256) return 3;  // p256x128
-    if (cdiv(M, 128) * cdiv(N, 128) >= 64) return 2;   // p128x128
-    return 0;
+// FP8: as for the 16-bit kinds, per 128-deep stage (start at 64 x 64 x 128,
+// lat at 128 x 128 x 4096, full at 4096^3).  The simple kernel is left with
+// rows of A that are not 16-byte aligned.
+static const Cost16 kCostF8[] = {
+    {2, 0, 64, 64, true, 2.4f, 0.27f, 0.195f},
+    {2, 1, 64, 128, true, 2.9f, 0.33f, 0.268f},
+    {2, 2, 128, 128, true, 3.6f, 0.55f, 0.41f},
+    {3, 0, 256, 128, false, 6.4f, 0.69f, 0.755f},
+    {4, 0, 256, 256, false, 9.6f, 1.10f, 1.12f},
+};
+static const Cost16& pick8(int64_t M, int64_t N, int64_t K, bool ring_only) {
+    return least_cost(kCostF8, (int)(sizeof(kCostF8) / sizeof(Cost16)), M, N, cdiv(K, 128), 1, 1.0, ring_only);
 }
+
+int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool whole) {
+    if (!vec_ok || M < 1 || N < 1 || K < 1) return 0;
+    return pick8(M, N, K, !whole).cfg;
+}
+
+int pick_ring_f8(int64_t M, int64_t N, int64_t K) { return pick8(M, N, K, true).variant; }
 
 // FP32: the simple kernel (one wavefront per 32 x 32 block, no LDS) for a
 // block or less of short K, or a batch of such (65536-sized batches of 16^3:

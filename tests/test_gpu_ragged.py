@@ -111,3 +111,34 @@ def test_f32_batched_entries_are_bitwise_solo(shape):
         solo = torch.empty((M, N), device=DEV)
         mfg.gemm(A[i], B[i], solo, mode="f32", config=0)
         assert torch.equal(C[i].view(torch.int32), solo.view(torch.int32)), i
+
+
+F8_SHAPES = [(1, 1, 1), (32, 64, 128), (33, 65, 129), (65, 7, 200), (129, 130, 64), (127, 300, 1003), (777, 610, 330),
+             (1100, 1300, 260), (2050, 2300, 515)]
+
+
+@pytest.mark.parametrize("shape", F8_SHAPES, ids=str)
+def test_fp8_default_choice_is_bitwise_the_simple_kernel(shape):
+    M, N, K = shape
+    gen = torch.Generator(device=DEV).manual_seed(M + 2 * N + K)
+    A = torch.rand((M, K), device=DEV, generator=gen).mul_(2).sub_(1)
+    B = torch.rand((K, N), device=DEV, generator=gen).mul_(2).sub_(1)
+    C0 = torch.rand((M, N), device=DEV, generator=gen)
+
+    def codes(X):  # storage form, rows padded to 16 with NaN codes
+        rows, cols = X.shape
+        ld = -(-cols // 16) * 16
+        buf = torch.full((mfg.convert_bytes(rows, cols, ld, "fp8"),), 0x7F, dtype=torch.uint8, device=DEV)
+        mfg.convert(X, buf, ld, "fp8")
+        return buf.as_strided((rows, cols), (ld, 1))
+
+    qa, qb = codes(A), codes(B)
+    for alpha, beta in ((1.0, 0.0), (1.25, -0.5)):
+        out = []
+        for config, pre in ((0, True), (-1, True), (0, False), (-1, False)):
+            C = torch.full((M, N), float("nan"), device=DEV) if beta == 0.0 else C0.clone()
+            mfg.gemm(qa if pre else A, qb if pre else B, C, alpha, beta, mode="fp8", preconverted=pre, config=config)
+            out.append(C)
+        assert torch.isfinite(out[0]).all()
+        for C in out[1:]:
+            assert torch.equal(out[0].view(torch.int32), C.view(torch.int32)), (alpha, beta)
