@@ -14,9 +14,9 @@
 //        A22 -= L21 U12 by one mfg_gemm call in the caller's mode (F32, F16,
 //        or a refined split: the precision of the factorisation).
 //   solve with the factors: the row permutation (one gather), then forward
-//        and backward substitution by blocks of kNb rows, one launch per
-//        block: the diagonal block solved in every workgroup, the rest of
-//        the right-hand side updated in the same launch.
+//        and backward substitution by blocks of kNb rows, one launch each:
+//        a wavefront per block and right-hand side, waiting for the unknowns
+//        of the blocks before it.
 //   refinement: x0 from the factors; then r = b - A x in FP64, the normwise
 //        backward error max_j |r_j|_inf / (|A|_inf |x_j|_inf + |b_j|_inf),
 //        and while it is above the tolerance a correction d solved in FP32
@@ -831,71 +831,123 @@ __global__ __launch_bounds__(kNb) void lu_trsv_block(const float* LU, int64_t ld
     if (i < w) V[(s + i) * ldv + q] = xi;
 }
 
-// One block step of the substitution, for right-hand side q = blockIdx.y:
-// the diagonal block [s, s+w) of the factors solved (unit lower, forward, or
-// upper with the diagonal, backward) from In[s:s+w, q] by the first
-// wavefront of every workgroup, as in lu_trsv_block (each workgroup solves
-// the same small system, so none waits for another); workgroup 0 writes the
-// solution to Out[s:s+w, q]; and the rows still to be solved (forward: below
-// the block, backward: above it), one per thread, are updated in place,
-// In[r, q] -= LU[r, s:s+w] . x, by multiply-adds in column order.  In and
-// Out are distinct arrays, so no workgroup overwrites right-hand sides
-// another still reads.  vec: LU's rows 16-byte aligned at column s.
-template <bool LOWER>
-__global__ __launch_bounds__(256) void lu_subst_step(const float* LU, int64_t ldlu, int64_t n, int64_t s, int w,
-                                                     float* In, int64_t ldi, float* Out, int64_t ldo, int vec) {
-    __shared__ float xs[kNb];
-    const int64_t q = blockIdx.y;
-    if (threadIdx.x < kNb) {
-        const int i = threadIdx.x;
-        const float* row = LU + (s + (i < w ? i : 0)) * ldlu + s;
-        float r[kNb];
+// A whole substitution (forward with the unit lower triangle, or backward
+// with the upper one) of nrhs right-hand sides in one launch, in place in V.
+// One wavefront per block of kNb rows and R right-hand sides, lane i holding
+// row i: as each block before it is published, it takes that block's
+// multiply-adds (its 64 entries of the row, loaded ahead of the wait, times the
+// solved unknowns, by readlane, in column order); then it solves its diagonal
+// block as lu_trsv_block does and publishes its unknowns.  The same
+// operations in the same order per element for any R, and as one launch per
+// block.
+// Bound by the chain from block to block: a publication seen, 64 multiply-adds,
+// the 64 dependent steps of the diagonal block.  At n = 2048, one right-hand
+// side, 102 us forward and 148 backward against 32 launches of 7.8 and 9.1 us.
+// R = 4 where the wavefronts of R = 1 would come in many turns: the rows'
+// entries are then loaded once for four.
+//
+// A published unknown is one 64-bit word, its value beside the launch's tag,
+// stored and polled as a relaxed agent-scope atomic, so the value needs no
+// ordering against a flag.  Z (n x nrhs words) starts as zeros, tags count up
+// from 1.  The blocks are taken in order from a ticket counter (`first`: the
+// tickets of the launches before), so a wavefront waits only for blocks whose
+// wavefronts already run: every wait ends.
+template <bool LOWER, int R>
+__global__ __launch_bounds__(kNb) void lu_chain(const float* LU, int64_t ldlu, int64_t n, int64_t nrhs, int nblk,
+                                                float* V, int64_t ldv, unsigned long long* Z, uint32_t tag,
+                                                uint32_t* ticket, uint32_t first, int vec) {
+    const int i = threadIdx.x;
+    uint32_t id = 0;
+    if (i == 0) id = atomicAdd(ticket, 1u) - first;
+    id = (uint32_t)__builtin_amdgcn_readfirstlane((int)id);
+    const uint32_t groups = (uint32_t)((nrhs + R - 1) / R);
+    const int b = (int)(id / groups);
+    const int64_t q0 = (int64_t)(id % groups) * R;
+    const int blk = LOWER ? b : nblk - 1 - b;
+    const int64_t s = (int64_t)blk * kNb;
+    const int w = (int)min(n - s, (int64_t)kNb);
+    const float* row = LU + (s + (i < w ? i : 0)) * ldlu;
+    auto load = [&](int64_t c0, int cw, float (&d)[kNb]) {  // the row's entries of columns c0 ..
+        if (vec && cw == kNb) {
 #pragma unroll
-        for (int k = 0; k < kNb; ++k) r[k] = k < w ? row[k] : 0.0f;
-        float xi = i < w ? In[(s + i) * ldi + q] : 0.0f;
-        auto lane_value = [](float v, int k) {
-            return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
-        };
-        if constexpr (LOWER) {
-#pragma unroll
-            for (int k = 0; k < kNb; ++k) {
-                if (k < w) {
-                    const float xk = lane_value(xi, k);
-                    if (i > k && i < w) xi = __builtin_fmaf(-r[k], xk, xi);
-                }
+            for (int k = 0; k < kNb; k += 4) {
+                const float4 v = *reinterpret_cast<const float4*>(row + c0 + k);
+                d[k] = v.x, d[k + 1] = v.y, d[k + 2] = v.z, d[k + 3] = v.w;
             }
         } else {
 #pragma unroll
-            for (int k = kNb - 1; k >= 0; --k) {
-                if (k < w) {
-                    if (i == k) xi = xi / r[k];
-                    const float xk = lane_value(xi, k);
-                    if (i < k) xi = __builtin_fmaf(-r[k], xk, xi);
-                }
-            }
+            for (int k = 0; k < kNb; ++k) d[k] = k < cw ? row[c0 + k] : 0.0f;
         }
-        xs[i] = xi;  // 0 for i >= w
-        if (blockIdx.x == 0 && i < w) Out[(s + i) * ldo + q] = xi;
-    }
-    __syncthreads();
-    const int64_t r0 = LOWER ? s + w : 0, r1 = LOWER ? n : s;
-    const int64_t rr = r0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (rr >= r1) return;
-    const float* lr = LU + rr * ldlu + s;
-    float acc = In[rr * ldi + q];
-    if (vec && w == kNb) {
+    };
+    // (past the last right-hand side: the last one again, not stored)
+    auto rhs = [&](int r) { return R == 1 ? q0 : min(q0 + r, nrhs - 1); };
+    float d[kNb], x[R];
 #pragma unroll
-        for (int k4 = 0; k4 < kNb / 4; ++k4) {
-            const float4 a = reinterpret_cast<const float4*>(lr)[k4];
-            acc = __builtin_fmaf(-a.x, xs[4 * k4], acc);
-            acc = __builtin_fmaf(-a.y, xs[4 * k4 + 1], acc);
-            acc = __builtin_fmaf(-a.z, xs[4 * k4 + 2], acc);
-            acc = __builtin_fmaf(-a.w, xs[4 * k4 + 3], acc);
+    for (int r = 0; r < R; ++r) x[r] = i < w ? V[(s + i) * ldv + rhs(r)] : 0.0f;
+    load(s, w, d);  // the diagonal block
+    for (int t = 0; t < b; ++t) {
+        const int kb = LOWER ? t : nblk - 1 - t;
+        const int64_t c0 = (int64_t)kb * kNb;
+        const int cw = (int)min(n - c0, (int64_t)kNb);
+        float l[kNb], u[R];
+        load(c0, cw, l);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const unsigned long long* z = Z + rhs(r) * n + c0;
+            unsigned long long v = 0;
+            for (;;) {
+                if (i < cw) v = __hip_atomic_load(z + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__all(i >= cw || (uint32_t)(v >> 32) == tag)) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            u[r] = __builtin_bit_cast(float, (uint32_t)v);
         }
-    } else {
-        for (int k = 0; k < w; ++k) acc = __builtin_fmaf(-lr[k], xs[k], acc);
+        if (cw == kNb) {
+#pragma unroll
+            for (int k = 0; k < kNb; ++k)
+#pragma unroll
+                for (int r = 0; r < R; ++r) x[r] = __builtin_fmaf(-l[k], lane_of(u[r], k), x[r]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kNb; ++k)
+                if (k < cw)
+#pragma unroll
+                    for (int r = 0; r < R; ++r) x[r] = __builtin_fmaf(-l[k], lane_of(u[r], k), x[r]);
+        }
     }
-    In[rr * ldi + q] = acc;
+    if constexpr (LOWER) {
+#pragma unroll
+        for (int k = 0; k < kNb; ++k)
+            if (k < w)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float xk = lane_of(x[r], k);
+                    if (i > k && i < w) x[r] = __builtin_fmaf(-d[k], xk, x[r]);
+                }
+    } else {
+#pragma unroll
+        for (int k = kNb - 1; k >= 0; --k)
+            if (k < w)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    if (i == k) x[r] = x[r] / d[k];
+                    const float xk = lane_of(x[r], k);
+                    if (i < k) x[r] = __builtin_fmaf(-d[k], xk, x[r]);
+                }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t q = q0 + r;
+        if (i >= w || q >= nrhs) continue;
+        const unsigned long long word = ((unsigned long long)tag << 32) | __builtin_bit_cast(uint32_t, x[r]);
+        __hip_atomic_store(Z + q * n + s + i, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        V[(s + i) * ldv + q] = x[r];
+    }
+}
+
+__global__ __launch_bounds__(256) void zero_words(int64_t n, uint32_t* p) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0;
 }
 
 // dst[i, :] = src[perm[i], :] (rows of nrhs FP32 values).
@@ -1092,29 +1144,48 @@ static int permutation(int64_t n, const int32_t* ipiv, std::vector<int32_t>& per
     return MFG_OK;
 }
 
-// V = U^-1 L^-1 V (V: n x nrhs FP32, already permuted), FP32.
-// Forward and backward substitution by blocks of kNb rows, in place in V
-// (n x nrhs).  Y (n x nrhs, ldy) is scratch: each block step reads its
-// right-hand sides from one of V and Y and writes its solution to the other
-// (forward V -> Y, backward Y -> V), with the remaining rows updated in the
-// same launch (lu_subst_step).  More right-hand sides than a grid dimension
-// holds go block by block instead: the diagonal block (lu_trsv_block), then
-// the rest of V by an FP32 mfg_gemm.
-static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, float* Y,
-                         int64_t ldy, hipStream_t s) {
-    if (nrhs <= 65535) {
+// Device words of lu_chain (n x nrhs published unknowns and the ticket
+// counter) and what its launches so far have used of them; none where the
+// grid would not hold a wavefront per block and right-hand side.
+struct ChainWords {
+    unsigned long long* z = nullptr;
+    uint32_t tag = 0, tickets = 0;
+};
+static size_t chain_words(int64_t n, int64_t nrhs) {
+    return nrhs <= 65535 && n * nrhs <= (int64_t)1 << 30 ? (size_t)(n * nrhs + 1) : 0;
+}
+// lu_chain with R = 1 up to here (both substitutions of lu_solve: n = 2048, 128
+// right-hand sides, 4096 wavefronts, 534 us against 787 with R = 4; n = 1024, 1024
+// of them, 16384: 813 against 588).
+constexpr int64_t kChainWaves = 8192;
+static int chain_clear(int64_t n, int64_t nrhs, const ChainWords& c, hipStream_t s) {
+    if (c.z == nullptr) return MFG_OK;
+    const int64_t words = 2 * (int64_t)chain_words(n, nrhs);
+    hipLaunchKernelGGL(zero_words, dim3(blocks(words, 256)), dim3(256), 0, s, words, reinterpret_cast<uint32_t*>(c.z));
+    MFG_LAUNCH_CHECK();
+    return MFG_OK;
+}
+
+// V = U^-1 L^-1 V (V: n x nrhs FP32, already permuted) in FP32, in place:
+// forward and backward substitution by blocks of kNb rows, one launch each
+// (lu_chain).  Without the words for that (too many, or no memory), block by
+// block instead: the diagonal block (lu_trsv_block), then the rest of V by an
+// FP32 mfg_gemm.
+static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, ChainWords& c,
+                         hipStream_t s) {
+    const int64_t nblk = (n + kNb - 1) / kNb;
+    if (c.z != nullptr) {
         const int vec = ldlu % 4 == 0 && reinterpret_cast<uintptr_t>(LU) % 16 == 0;
-        for (int64_t b = 0; b < n; b += kNb) {  // forward, unit lower: V -> Y
-            const int w = (int)std::min<int64_t>(kNb, n - b);
-            const dim3 g(blocks(n - b - w, 256), (unsigned)nrhs);
-            hipLaunchKernelGGL(lu_subst_step<true>, g, dim3(256), 0, s, LU, ldlu, n, b, w, V, ldv, Y, ldy, vec);
+        const int R = nblk * nrhs > kChainWaves ? 4 : 1;
+        const uint32_t grid = (uint32_t)(nblk * ((nrhs + R - 1) / R));
+        uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * nrhs);
+        for (int lower = 1; lower >= 0; --lower) {
+            auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : lu_chain<true, 1>)
+                                 : (R == 4 ? lu_chain<false, 4> : lu_chain<false, 1>);
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, nrhs, (int)nblk, V, ldv, c.z, ++c.tag,
+                               ticket, c.tickets, vec);
             MFG_LAUNCH_CHECK();
-        }
-        for (int64_t b = ((n - 1) / kNb) * kNb; b >= 0; b -= kNb) {  // backward, upper: Y -> V
-            const int w = (int)std::min<int64_t>(kNb, n - b);
-            const dim3 g(blocks(b, 256), (unsigned)nrhs);
-            hipLaunchKernelGGL(lu_subst_step<false>, g, dim3(256), 0, s, LU, ldlu, n, b, w, Y, ldy, V, ldv, vec);
-            MFG_LAUNCH_CHECK();
+            c.tickets += grid;
         }
         return MFG_OK;
     }
@@ -1142,14 +1213,12 @@ static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu,
     return MFG_OK;
 }
 
-// X = (LU)^-1 P B with B, X n x nrhs FP32 (X may not alias B).  B is
-// overwritten: once its rows are gathered into X it is the substitution's
-// scratch.
-static int lu_solve_impl(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* dperm, float* B,
-                         int64_t ldb, float* X, int64_t ldx, hipStream_t s) {
+// X = (LU)^-1 P B with B, X n x nrhs FP32 (X may not alias B).
+static int lu_solve_impl(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* dperm, const float* B,
+                         int64_t ldb, float* X, int64_t ldx, ChainWords& c, hipStream_t s) {
     hipLaunchKernelGGL(gather_rows, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, dperm, B, ldb, X, ldx);
     MFG_LAUNCH_CHECK();
-    return lu_substitute(n, nrhs, LU, ldlu, X, ldx, B, ldb, s);
+    return lu_substitute(n, nrhs, LU, ldlu, X, ldx, c, s);
 }
 
 }  // namespace mfg
@@ -1211,9 +1280,12 @@ int lu_solve_api(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const i
     Buffers buf;
     int32_t* dperm = nullptr;
     float* tmp = nullptr;
+    ChainWords chain;
     if ((st = buf.get(&dperm, (size_t)n)) != MFG_OK || (st = buf.get(&tmp, (size_t)(n * nrhs))) != MFG_OK) return st;
+    if (chain_words(n, nrhs) > 0) (void)buf.get(&chain.z, chain_words(n, nrhs));
+    if ((st = chain_clear(n, nrhs, chain, s)) != MFG_OK) return st;
     MFG_HIP_CHECK(hipMemcpyAsync(dperm, perm.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
-    if ((st = lu_solve_impl(n, nrhs, LU, ldlu, dperm, B, ldb, tmp, nrhs, s)) != MFG_OK) return st;
+    if ((st = lu_solve_impl(n, nrhs, LU, ldlu, dperm, B, ldb, tmp, nrhs, chain, s)) != MFG_OK) return st;
     MFG_HIP_CHECK(hipMemcpy2DAsync(B, (size_t)ldb * 4, tmp, (size_t)nrhs * 4, (size_t)nrhs * 4, (size_t)n,
                                    hipMemcpyDeviceToDevice, s));
     MFG_HIP_CHECK(hipStreamSynchronize(s));  // before the buffers are freed
@@ -1237,6 +1309,7 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
     char* scratch = nullptr;
     double *R = nullptr, *rows = nullptr, *nrm = nullptr;
     int32_t *ipiv = nullptr, *dperm = nullptr, *dinfo = nullptr;
+    ChainWords chain;
     int st;
     if ((st = buf.get(&A32, (size_t)(n * n))) != MFG_OK || (st = buf.get(&v, (size_t)(n * nrhs))) != MFG_OK ||
         (st = buf.get(&d, (size_t)(n * nrhs))) != MFG_OK || (st = buf.get(&R, (size_t)(n * nrhs))) != MFG_OK ||
@@ -1244,6 +1317,8 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
         (st = buf.get(&ipiv, (size_t)n)) != MFG_OK || (st = buf.get(&dperm, (size_t)n)) != MFG_OK ||
         (st = buf.get(&dinfo, 1)) != MFG_OK || (st = buf.get(&scratch, lu_scratch_bytes(n))) != MFG_OK)
         return st;
+    if (chain_words(n, nrhs) > 0) (void)buf.get(&chain.z, chain_words(n, nrhs));
+    if ((st = chain_clear(n, nrhs, chain, s)) != MFG_OK) return st;
     // the factorisation of the FP32 copy, in the given mode
     hipLaunchKernelGGL(f64_to_f32, dim3(blocks(n * n, 256)), dim3(256), 0, s, n, n, A, lda, A32, n);
     MFG_LAUNCH_CHECK();
@@ -1268,7 +1343,7 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
     // x0 from the factors
     hipLaunchKernelGGL(f64_to_f32, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, B, ldb, v, nrhs);
     MFG_LAUNCH_CHECK();
-    if ((st = lu_solve_impl(n, nrhs, A32, n, dperm, v, nrhs, d, nrhs, s)) != MFG_OK) return st;
+    if ((st = lu_solve_impl(n, nrhs, A32, n, dperm, v, nrhs, d, nrhs, chain, s)) != MFG_OK) return st;
     hipLaunchKernelGGL(accumulate_f64, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, d, nrhs, X, ldx, 1);
     MFG_LAUNCH_CHECK();
     std::vector<double> h((size_t)(3 * nrhs + 1));
@@ -1296,7 +1371,7 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
         // correction: d = (LU)^-1 P r in FP32, x += d in FP64
         hipLaunchKernelGGL(f64_to_f32, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, R, nrhs, v, nrhs);
         MFG_LAUNCH_CHECK();
-        if ((st = lu_solve_impl(n, nrhs, A32, n, dperm, v, nrhs, d, nrhs, s)) != MFG_OK) return st;
+        if ((st = lu_solve_impl(n, nrhs, A32, n, dperm, v, nrhs, d, nrhs, chain, s)) != MFG_OK) return st;
         hipLaunchKernelGGL(accumulate_f64, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, d, nrhs, X, ldx, 0);
         MFG_LAUNCH_CHECK();
     }

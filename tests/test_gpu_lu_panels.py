@@ -53,3 +53,34 @@ def test_factors_at_any_height_and_alignment(n):
     PA = torch.from_numpy(oracle.apply_pivots(piv, A).astype(np.float64)).to(DEV)
     err, scale = float((PA - L @ U).abs().max()), float((L.abs() @ U.abs()).max())
     assert err <= 4 * n * 2.0 ** -24 * scale, (err, scale)
+
+
+@pytest.mark.parametrize("n,nrhs,lda", [(1, 1, 1), (63, 2, 64), (64, 1, 64), (65, 3, 67), (200, 1, 200), (513, 5, 513),
+                                        (129, 2731, 132), (100, 5003, 100), (1030, 1, 1032)])
+def test_substitution_at_block_edges(n, nrhs, lda):
+    """Both substitutions in one chain of blocks: partial last blocks,
+    unaligned rows, one and (from 8192 wavefronts) four right-hand sides per
+    wavefront, the last of them partly filled.  The factors are taken as they
+    are, so the reference is their FP64 solve; FP32 substitution is backward
+    stable row by row: |L U x - b| <= 2 n u |L| |U| |x| to first order,
+    held to twice that."""
+    gen = torch.Generator(device=DEV).manual_seed(n + nrhs)
+    A = torch.randn((n, n), device=DEV, generator=gen)
+    V = torch.full((n, lda), float("nan"), device=DEV)[:, :n]
+    V.copy_(A)
+    ipiv, info = mfg.lu_factor(V, "f32")
+    assert info == 0
+    B = torch.randn((n, nrhs), device=DEV, generator=gen)
+    X = B.clone()
+    mfg.lu_solve(V, ipiv, X)
+    L = torch.tril(V.double(), -1) + torch.eye(n, dtype=torch.float64, device=DEV)
+    U = torch.triu(V.double())
+    PB = torch.from_numpy(oracle.apply_pivots(host(ipiv).astype(np.int64), host(B)).astype(np.float64)).to(DEV)
+    bound = 4 * (n + 1) * 2.0 ** -24 * (L.abs() @ (U.abs() @ X.double().abs()))
+    assert bool(((L @ (U @ X.double()) - PB).abs() <= bound).all())
+    again = B.clone()
+    mfg.lu_solve(V, ipiv, again)
+    assert torch.equal(X, again)
+    one = B[:, -1:].clone()  # any grouping of right-hand sides runs the same operations
+    mfg.lu_solve(V, ipiv, one)
+    assert torch.equal(one, X[:, -1:])
