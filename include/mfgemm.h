@@ -218,10 +218,11 @@ int mfg_gemm_batched(int64_t count, int64_t M, int64_t N, int64_t K,
  *     MFG_IN_PRECONVERTED is implied): 16-bit matrices, and for the refined
  *     modes head plane then residual plane, at A + M*lda and (two-sided
  *     splits) B + K*ldb elements; or
- *   - FP32 (mode | MFG_IN_FP32): the plan owns converted copies (ld rounded
- *     up to 8) and every run first converts all problems' A and B in one
- *     launch (the paper's rounding, or the Eq. R split), then runs the
- *     grouped kernel; a graph replay holds both launches.
+ *   - FP32 (mode | MFG_IN_FP32), rounded (the paper's rounding) or split (Eq.
+ *     R) by every run: in the grouped kernel itself when no problem has M or
+ *     N above 768 and no C overlaps an operand; otherwise the plan owns
+ *     converted copies (ld rounded up to 8) and a run first converts all
+ *     problems' A and B in one launch; a graph replay holds both launches.
  * Each problem's result is bitwise that of mfg_gemm on the problem alone in
  * the same mode (preconverted, or from FP32 respectively).  The descriptor array is host memory; the plan copies it
  * to the device, so it may be freed after mfg_grouped_plan_create.
@@ -267,8 +268,8 @@ int mfg_grouped_run(mfg_grouped_plan* plan, float alpha, float beta, void* strea
 int mfg_grouped_graph_launch(mfg_grouped_plan* plan, float alpha, float beta, void* stream);
 /* Total useful flops 2*sum(M*N*K) and algorithmic bytes of one run: the
  * operands read by the grouped kernel (both planes of the refined modes) and
- * C written, plus with MFG_IN_FP32 the conversion pass (FP32 read, 16-bit
- * planes written). */
+ * C written, plus with MFG_IN_FP32 a conversion pass (FP32 read, 16-bit
+ * planes written; counted alike where the kernel converts). */
 int mfg_grouped_plan_info(const mfg_grouped_plan* plan, double* flops, double* bytes,
                           int64_t* work_items);
 int mfg_grouped_plan_destroy(mfg_grouped_plan* plan);

@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "cvt.h"
 #include "runtime.h"
 #include "tile16.h"
 
@@ -286,15 +287,26 @@ __device__ __forceinline__ void grouped_barrier() {
 
 // `planes` (refined kinds only): per work item, the element offsets of the
 // residual planes of A and B from their head planes.
-template <int KIND, bool VEC, int TT>
+//
+// F32: A and B are FP32 (records point at them, `planes` is not read), any
+// 4-byte alignment of rows; they are converted or split on their way from
+// registers to LDS, so the planes never exist in memory and the results are
+// bitwise those of a conversion pass.  A piece is then two 16-byte loads (as
+// many registers as two planes); its resource ends with the tile's last row,
+// past which the hardware answers each dword with zero.  4096 problems of
+// 16..512 per side, SPLIT3: 344 us against 247 for a pass and 370 on its planes;
+// bound by the latency of a tile's few K blocks, not by the conversions.
+template <int KIND, bool VEC, int TT, bool F32>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_per_cu<KIND, TT>()))) void gemm16_grouped(
     const GroupedWork* work, const int64_t* planes, GroupedSplit split, float alpha, float beta) {
     static_assert(TT == 64 || TT == 128, "tile classes of 64 and 128");
+    static_assert(VEC || !F32, "FP32 operands take the list with 32-bit offsets");
     constexpr int TH = TT / 2;  // workgroup tile, wavefront tile
     constexpr int FM = TH / 32, FN = TH / 32;       // 32 x 32 MFMA blocks per wavefront
     constexpr int PA = TT / 32, PB = TT / 32;       // 16-byte pieces per thread and block: A, B
     constexpr int BPR = TT / 8;                     // pieces per B row
     constexpr int NA = KT<KIND>::NPA, NB = KT<KIND>::NPB;  // operand planes (head, residual)
+    constexpr int LA = F32 ? 2 : NA, LB = F32 ? 2 : NB;    // 16-byte loads of a piece
     constexpr int NR = 2;  // register sets: blocks s + 1 and s + 2 in flight while block s is multiplied
     const int64_t* off = split.off[VEC ? 0 : 1];
     // per plane and buffer: A TT rows x 64, B 4 chunks x TT/32 column slabs x (16 x 32)
@@ -333,8 +345,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_
     // Residual planes sit at element offsets pa (A) and pb (B) from the head
     // planes of the item being loaded (refined kinds; read with the item).
     int64_t pa = 0, pb = 0;
-    auto load_block = [&](const GItem& t, int kb0, u32x4 (&a)[NA][PA], u32x4 (&b)[NB][PB], int (&nv)[PA]) {
-        if constexpr (VEC) {
+    auto load_block = [&](const GItem& t, int kb0, u32x4 (&a)[LA][PA], u32x4 (&b)[LB][PB], int (&nv)[PA]) {
+        if constexpr (F32) {
+            const uint32_t lda32 = (uint32_t)t.lda, ldb32 = (uint32_t)t.ldb;
+            const int kr_n = min(t.K - kb0, kGroupedBK);  // K rows of B in this block (<= 0: none)
+            const bool any = kr_n > 0 && t.rows > 0;
+            const __amdgpu_buffer_rsrc_t rsa =
+                buffer_rsrc((const float*)t.A + kb0, any ? ((uint32_t)(t.rows - 1) * lda32 + (uint32_t)(t.K - kb0)) * 4u : 0u);
+            const __amdgpu_buffer_rsrc_t rsb = buffer_rsrc((const float*)t.B + (int64_t)kb0 * t.ldb,
+                                                           any ? ((uint32_t)(kr_n - 1) * ldb32 + (uint32_t)t.cols) * 4u : 0u);
+#pragma unroll
+            for (int j = 0; j < PA; ++j) {
+                const int p = tid + 256 * j, row = p >> 3, ka = kb0 + 8 * (p & 7);
+                const uint32_t o = ((uint32_t)row * lda32 + (uint32_t)(8 * (p & 7))) * 4u;
+                nv[j] = t.K - ka;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    a[h][j] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rsa, row < t.rows && ka + 4 * h < t.K ? o + 16u * h : kGroupedOob, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < PB; ++j) {
+                const int p = tid + 256 * j, kr = p / BPR, cb = 8 * (p % BPR);
+                const uint32_t o = ((uint32_t)kr * ldb32 + (uint32_t)cb) * 4u;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    b[h][j] = __builtin_amdgcn_raw_buffer_load_b128(
+                        rsb, kr < kr_n && cb + 4 * h < t.cols ? o + 16u * h : kGroupedOob, 0, 0);
+            }
+        } else if constexpr (VEC) {
             const uint32_t lda32 = (uint32_t)t.lda, ldb32 = (uint32_t)t.ldb;
             uint32_t oa[PA], ob[PB];
 #pragma unroll
@@ -394,16 +433,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_
             }
         }
     };
-    auto store_block = [&](int buf, const u32x4 (&a)[NA][PA], const u32x4 (&b)[NB][PB], const int (&nv)[PA]) {
+    // A piece's two loads -> its planes (F32; else the planes as they came).
+    auto planes_of = [&](const u32x4& x0, const u32x4& x1, auto split, u32x4& head, u32x4& rest) {
+        u32x2 h0, h1, r0, r1;
+        split4<KT<KIND>::BF, decltype(split)::value>(__builtin_bit_cast(f32x4, x0), h0, r0);
+        split4<KT<KIND>::BF, decltype(split)::value>(__builtin_bit_cast(f32x4, x1), h1, r1);
+        head = u32x4{h0[0], h0[1], h1[0], h1[1]}, rest = u32x4{r0[0], r0[1], r1[0], r1[1]};
+    };
+    auto store_block = [&](int buf, const u32x4 (&a)[LA][PA], const u32x4 (&b)[LB][PB], const int (&nv)[PA]) {
 #pragma unroll
         for (int j = 0; j < PA; ++j) {
             const int p = tid + 256 * j, row = p >> 3, c = p & 7;
             uint32_t m[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d) m[d] = (2 * d < nv[j] ? 0xFFFFu : 0u) | (2 * d + 1 < nv[j] ? 0xFFFF0000u : 0u);
+            u32x4 v[2];
+            if constexpr (F32) {
+                planes_of(a[0][j], a[1][j], std::bool_constant<(NA > 1)>{}, v[0], v[1]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < NA; ++q) v[q] = a[q][j];
+            }
 #pragma unroll
             for (int q = 0; q < NA; ++q) {
-                u32x4 am = a[q][j];
+                u32x4 am = v[q];
 #pragma unroll
                 for (int d = 0; d < 4; ++d) am[d] &= m[d];
                 *reinterpret_cast<u32x4*>(&As[q][buf][row * 64 + ((c ^ swz<8>(row)) * 8)]) = am;
@@ -414,13 +467,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_
             // B row kr of the block: chunk kr / 16, slab row kr % 16, column
             // slab c / 4, columns 8 (c % 4) .. +7 of the slab
             const int p = tid + 256 * j, kr = p / BPR, c = p % BPR;
+            u32x4 v[2];
+            if constexpr (F32) {
+                planes_of(b[0][j], b[1][j], std::bool_constant<(NB > 1)>{}, v[0], v[1]);
+            } else {
+#pragma unroll
+                for (int q = 0; q < NB; ++q) v[q] = b[q][j];
+            }
 #pragma unroll
             for (int q = 0; q < NB; ++q)
-                *reinterpret_cast<u32x4*>(&Bs[q][buf][kr >> 4][c >> 2][(kr & 15) * 32 + 8 * (c & 3)]) = b[q][j];
+                *reinterpret_cast<u32x4*>(&Bs[q][buf][kr >> 4][c >> 2][(kr & 15) * 32 + 8 * (c & 3)]) = v[q];
         }
     };
     auto item_planes = [&](int64_t i) {  // residual-plane offsets of this workgroup's item i
-        if constexpr (NA > 1 || NB > 1) {
+        if constexpr (!F32 && (NA > 1 || NB > 1)) {
             const int64_t it = first + i * stride;
             const c_i64* pl = (const c_i64*)planes;
             pa = pl[2 * it], pb = pl[2 * it + 1];
@@ -445,7 +505,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_
             }
         }
     };
-    u32x4 ra[NR][NA][PA], rb[NR][NB][PB];  // register sets of the blocks in flight
+    u32x4 ra[NR][LA][PA], rb[NR][LB][PB];  // register sets of the blocks in flight
     int rn[NR][PA];
     // prologue: block 0 into LDS buffer 0, blocks 1 .. NR - 1 into registers
     load_block(ld, 0, ra[0], rb[0], rn[0]);
@@ -549,7 +609,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_
 // flops); each XCD's items are then ordered by decreasing K, their cost, and
 // written out as self-contained records.
 void build_grouped_work(const GroupedDesc* descs, int64_t n, std::vector<GroupedWork>& work, GroupedSplit& split,
-                        std::vector<int64_t>* planes, int tile) {
+                        std::vector<int64_t>* planes, int tile, int elem) {
     struct Unit {
         int64_t prob, tm0, tm1;
         double flops;
@@ -597,8 +657,8 @@ void build_grouped_work(const GroupedDesc* descs, int64_t n, std::vector<Grouped
                 const GroupedDesc& d = descs[t.prob];
                 const int64_t m0 = (int64_t)t.tm * tile, n0 = (int64_t)t.tn * tile;
                 GroupedWork w;
-                w.A = d.A + m0 * d.lda;
-                w.B = d.B + n0;
+                w.A = d.A + m0 * d.lda * (elem / 2);
+                w.B = d.B + n0 * (elem / 2);
                 w.C = d.C + m0 * d.ldc + n0;
                 w.lda = d.lda, w.ldb = d.ldb, w.ldc = d.ldc;
                 w.rows = (int32_t)std::min<int64_t>(tile, d.M - m0);
@@ -633,25 +693,25 @@ int grouped_grid(const GroupedSplit& split, int list, int kind, int tile) {
 }
 
 template <int KIND, int TT>
-static void launch_grouped_kind(int list, dim3 grid, const GroupedWork* work, const int64_t* planes,
+static void launch_grouped_kind(int list, bool f32, dim3 grid, const GroupedWork* work, const int64_t* planes,
                                 const GroupedSplit& split, float alpha, float beta, hipStream_t s) {
-    if (list == 0)
-        hipLaunchKernelGGL((gemm16_grouped<KIND, true, TT>), grid, dim3(256), 0, s, work, planes, split, alpha, beta);
-    else
-        hipLaunchKernelGGL((gemm16_grouped<KIND, false, TT>), grid, dim3(256), 0, s, work, planes, split, alpha, beta);
+    auto* kernel = f32         ? gemm16_grouped<KIND, true, TT, true>
+                   : list == 0 ? gemm16_grouped<KIND, true, TT, false>
+                               : gemm16_grouped<KIND, false, TT, false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, work, planes, split, alpha, beta);
 }
 
 template <int TT>
-static void launch_grouped_tt(int kind, int list, dim3 grid, const GroupedWork* work, const int64_t* planes,
+static void launch_grouped_tt(int kind, int list, bool f32, dim3 grid, const GroupedWork* work, const int64_t* planes,
                               const GroupedSplit& split, float alpha, float beta, hipStream_t s) {
     switch (kind) {
-        case K_F16: launch_grouped_kind<K_F16, TT>(list, grid, work, planes, split, alpha, beta, s); break;
-        case K_BF16: launch_grouped_kind<K_BF16, TT>(list, grid, work, planes, split, alpha, beta, s); break;
-        case K_REFINE_A: launch_grouped_kind<K_REFINE_A, TT>(list, grid, work, planes, split, alpha, beta, s); break;
-        case K_SPLIT3: launch_grouped_kind<K_SPLIT3, TT>(list, grid, work, planes, split, alpha, beta, s); break;
-        case K_BF16_SPLIT3: launch_grouped_kind<K_BF16_SPLIT3, TT>(list, grid, work, planes, split, alpha, beta, s); break;
+        case K_F16: launch_grouped_kind<K_F16, TT>(list, f32, grid, work, planes, split, alpha, beta, s); break;
+        case K_BF16: launch_grouped_kind<K_BF16, TT>(list, f32, grid, work, planes, split, alpha, beta, s); break;
+        case K_REFINE_A: launch_grouped_kind<K_REFINE_A, TT>(list, f32, grid, work, planes, split, alpha, beta, s); break;
+        case K_SPLIT3: launch_grouped_kind<K_SPLIT3, TT>(list, f32, grid, work, planes, split, alpha, beta, s); break;
+        case K_BF16_SPLIT3: launch_grouped_kind<K_BF16_SPLIT3, TT>(list, f32, grid, work, planes, split, alpha, beta, s); break;
         default:
-            if constexpr (TT == 64) launch_grouped_kind<K_SPLIT4, TT>(list, grid, work, planes, split, alpha, beta, s);
+            if constexpr (TT == 64) launch_grouped_kind<K_SPLIT4, TT>(list, f32, grid, work, planes, split, alpha, beta, s);
             break;
     }
 }
@@ -668,17 +728,18 @@ int grouped_tiles(int kind, int* tiles) {
 }
 
 int grouped_launch(int kind, int tile, const GroupedWork* work, const int64_t* planes, const GroupedSplit& split,
-                   float alpha, float beta, hipStream_t s) {
+                   float alpha, float beta, hipStream_t s, bool f32) {
     if (kind < K_F16 || kind > K_BF16_SPLIT3 || !grouped_tile_ok(kind, tile)) return MFG_ERR_UNSUPPORTED;
-    if (kind >= K_REFINE_A && !planes) return MFG_ERR_INTERNAL;  // the refined kinds read residual planes
+    if (f32 && split.off[1][kXcds] != split.off[1][0]) return MFG_ERR_INTERNAL;  // FP32 operands: the first list only
+    if (kind >= K_REFINE_A && !planes && !f32) return MFG_ERR_INTERNAL;  // the refined kinds read residual planes
     if (fault_hit(kFaultLaunch)) return hip_fail(hipErrorLaunchFailure);  // injected (tests)
     for (int list = 0; list < 2; ++list) {
         if (split.off[list][kXcds] == split.off[list][0]) continue;  // empty list
         const dim3 grid((unsigned)grouped_grid(split, list, kind, tile));
         if (tile == 128)
-            launch_grouped_tt<128>(kind, list, grid, work, planes, split, alpha, beta, s);
+            launch_grouped_tt<128>(kind, list, f32, grid, work, planes, split, alpha, beta, s);
         else
-            launch_grouped_tt<64>(kind, list, grid, work, planes, split, alpha, beta, s);
+            launch_grouped_tt<64>(kind, list, f32, grid, work, planes, split, alpha, beta, s);
         MFG_LAUNCH_CHECK();
     }
     return MFG_OK;

@@ -518,6 +518,13 @@ extern "C" int mfg_gemm_batched(int64_t count, int64_t M, int64_t N, int64_t K, 
 }
 
 // -------------------------------------------------------------------- grouped
+// Largest M or N of a plan whose FP32 operands the grouped kernel converts
+// itself (pass and kernel -> kernel alone, SPLIT3 and F16: 4096 problems of
+// 128^3 356 -> 174 and 251 -> 160 us, 256 of 512^3 586 -> 483 and 283 -> 235,
+// 128 of 768^3 848 -> 796 and 375 -> 342; 64 of 1024^3 914 -> 906 but 375 ->
+// 397, 16 of 2048^3 1557 -> 1710 and 569 -> 658).
+constexpr int64_t kGroupedDirect = 768;
+
 struct mfg_grouped_plan {
     int mode = 0, kind = 0, device = 0;
     int64_t count = 0, nwork = 0;
@@ -533,6 +540,7 @@ struct mfg_grouped_plan {
     ConvJob* d_jobs = nullptr;
     ConvTask* d_tasks = nullptr;
     int64_t ntasks = 0;
+    bool f32 = false;  // MFG_IN_FP32 with the conversion in the grouped kernel: none of the four above
     double flops = 0.0, bytes = 0.0;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -574,6 +582,40 @@ static int grouped_class(int m, int kind, int64_t M, int64_t N, int64_t K, int f
     return (t > 0 && grouped_tile_ok(kind, t)) ? t : grouped_tile(kind);
 }
 
+// Whether a plan's FP32 operands are converted in the grouped kernel instead
+// of by a pass before it.  The pass moves 6 or 8 bytes per element at the copy
+// rate; in the kernel every tile that reads an element converts it, beside
+// loads that the tiles wait for anyway: less until a row of tiles is long.
+// Only without a C that overlaps an operand: the pass reads all of them before
+// any C is written.
+static bool grouped_direct(int64_t count, const mfg_problem* probs) {
+    struct Range {
+        uintptr_t lo, hi;
+    };
+    std::vector<Range> in, out;
+    auto add = [](std::vector<Range>& v, const void* p, int64_t rows, int64_t cols, int64_t ld) {
+        if (rows > 0 && cols > 0)
+            v.push_back({(uintptr_t)p, (uintptr_t)p + (size_t)((rows - 1) * ld + cols) * sizeof(float)});
+    };
+    for (int64_t i = 0; i < count; ++i) {
+        const mfg_problem& p = probs[i];
+        if (p.M > kGroupedDirect || p.N > kGroupedDirect || !buffer_ldc_ok(p.ldc) || !operand_ld_ok(p.lda, p.ldb)) return false;
+        if (((uintptr_t)p.A | (uintptr_t)p.B) % sizeof(float) != 0) return false;
+        add(in, p.A, p.M, p.K, p.lda), add(in, p.B, p.K, p.N, p.ldb), add(out, p.C, p.M, p.N, p.ldc);
+    }
+    auto by_lo = [](const Range& a, const Range& b) { return a.lo < b.lo; };
+    std::sort(in.begin(), in.end(), by_lo);
+    std::sort(out.begin(), out.end(), by_lo);
+    // each operand against the outputs that start before its end: the furthest end of those
+    uintptr_t reach = 0;
+    size_t c = 0;
+    for (const Range& r : in) {
+        for (; c < out.size() && out[c].lo <= r.lo; ++c) reach = std::max(reach, out[c].hi);
+        if (reach > r.lo || (c < out.size() && out[c].lo < r.hi)) return false;
+    }
+    return true;
+}
+
 static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, mfg_grouped_plan** out,
                             int force_tile = 0) {
     if (!out || count < 0 || (count > 0 && !probs)) return MFG_ERR_INVALID_ARG;
@@ -592,6 +634,14 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
     std::vector<GroupedDesc> descs((size_t)count);
     std::vector<GroupedWork> work;
     double flops = 0.0, bytes = 0.0;
+    bool direct = fp32_in;  // (decided once the arguments are checked)
+    for (int64_t i = 0; i < count && fp32_in; ++i) {
+        const mfg_problem& p = probs[i];
+        const int st = validate_gemm(p.M, p.N, p.K, p.A, p.lda, p.B, p.ldb, p.C, p.ldc, m);
+        if (st != MFG_OK) return st;
+        if (p.M > ((int64_t)1 << 24) || p.N > ((int64_t)1 << 24) || p.K > INT32_MAX) return MFG_ERR_UNSUPPORTED;
+    }
+    direct = direct && grouped_direct(count, probs);
     // MFG_IN_FP32: byte offsets of each problem's converted A and B in the
     // plan's storage (256-byte aligned, ld rounded up to 8 elements)
     std::vector<int64_t> conv_off(fp32_in ? (size_t)count * 2 : 0);
@@ -616,6 +666,10 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
             d.A = static_cast<const uint16_t*>(p.A), d.B = static_cast<const uint16_t*>(p.B);
             d.vec = (al16(p.A) && al16(p.B) && p.lda % 8 == 0 && p.ldb % 8 == 0) ? 1 : 0;
         }
+        if (direct) {
+            d.lda = p.lda, d.ldb = p.ldb;
+            d.A = static_cast<const uint16_t*>(p.A), d.B = static_cast<const uint16_t*>(p.B);
+        }
         d.pa = two_a ? p.M * d.lda : 0;
         d.pb = two_b ? p.K * d.ldb : 0;
         flops += 2.0 * (double)p.M * (double)p.N * (double)p.K;
@@ -626,7 +680,8 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
     plan->mode = m, plan->kind = kind_of(m), plan->count = count;
     plan->flops = flops, plan->bytes = bytes;
     MFG_HIP_CHECK(hipGetDevice(&plan->device));
-    if (fp32_in && conv_bytes > 0) {
+    plan->f32 = direct;
+    if (fp32_in && !direct && conv_bytes > 0) {
         if (hipMalloc(&plan->d_conv, (size_t)conv_bytes) != hipSuccess) {
             plan->d_conv = nullptr;
             (void)hipGetLastError();
@@ -686,7 +741,8 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
         std::vector<GroupedWork> w;
         std::vector<int64_t> pl;
         GroupedSplit sp{};
-        build_grouped_work(sub.data(), (int64_t)sub.size(), w, sp, two_a ? &pl : nullptr, tiles[c]);
+        build_grouped_work(sub.data(), (int64_t)sub.size(), w, sp, two_a && !direct ? &pl : nullptr, tiles[c],
+                           direct ? 4 : 2);
         const int64_t base = (int64_t)work.size();
         for (auto& o : sp.off)
             for (auto& v : o) v += base;
@@ -697,7 +753,7 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
     }
     plan->nwork = (int64_t)work.size();
     int st = upload(work, &plan->d_work);
-    if (st == MFG_OK && two_a) st = upload(planes, &plan->d_planes);
+    if (st == MFG_OK && two_a && !direct) st = upload(planes, &plan->d_planes);
     if (st != MFG_OK) return st;
     *out = plan.release();
     return MFG_OK;
@@ -712,7 +768,7 @@ static int plan_launch(mfg_grouped_plan* plan, float alpha, float beta, hipStrea
     }
     for (int c = 0; c < plan->nclass; ++c) {
         const int st = grouped_launch(plan->kind, plan->tile[c], plan->d_work, plan->d_planes, plan->split[c], alpha,
-                                      beta, s);
+                                      beta, s, plan->f32);
         if (st != MFG_OK) return st;
     }
     return MFG_OK;

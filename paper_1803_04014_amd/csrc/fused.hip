@@ -101,39 +101,6 @@ struct FusedLoader {
     }
 };
 
-// Four FP32 values -> four 16-bit heads and, with SPLIT, four residuals,
-// as the split (and rounding) passes compute each finite element: head =
-// RNE(x), residual = RNE((x - head) * 2^11) for FP16, RNE(x - head) for
-// BF16, the difference exact in FP32.  Pairs go through gfx950's packed
-// conversions (v_cvt_pk_f16_f32 / v_cvt_pk_bf16_f32, round to nearest even),
-// which write the MFMA operand's packed layout directly.  (A NaN input gives
-// a NaN head whose payload may differ from the passes' sign-keeping quiet
-// NaN; every product with it is NaN either way.)
-template <bool BF, bool SPLIT>
-__device__ __forceinline__ void split4(const f32x4& v, u32x2& h, u32x2& r) {
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    uint32_t hw[2], rw[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const f2 x = {v[2 * j], v[2 * j + 1]};
-        if constexpr (BF) {
-            const b2 hh = __builtin_convertvector(x, b2);
-            hw[j] = __builtin_bit_cast(uint32_t, hh);
-            if constexpr (SPLIT) rw[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x - __builtin_convertvector(hh, f2), b2));
-        } else {
-            const h2 hh = __builtin_convertvector(x, h2);
-            hw[j] = __builtin_bit_cast(uint32_t, hh);
-            if constexpr (SPLIT)
-                rw[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector((x - __builtin_convertvector(hh, f2)) * 2048.0f, h2));
-        }
-        if constexpr (!SPLIT) rw[j] = 0u;
-    }
-    h = u32x2{hw[0], hw[1]};
-    r = u32x2{rw[0], rw[1]};
-}
-
 // Convert the staged sources of one K step and write them into LDS stage
 // `st` (head plane, then residual plane where the kind splits the operand).
 template <int KIND, class F>

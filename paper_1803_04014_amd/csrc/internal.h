@@ -253,15 +253,18 @@ struct GroupedSplit {
 };
 // `planes` (if not null) receives two int64 per work item, in work order:
 // the problem's residual-plane offsets pa, pb.
-// `tile`: the output tile side of the kind that will run the list (grouped_tile).
+// `tile`: the output tile side of the kind that will run the list (grouped_tile);
+// `elem`: bytes of an operand element (4: FP32, A and B cast).
 void build_grouped_work(const GroupedDesc* descs, int64_t n, std::vector<GroupedWork>& work, GroupedSplit& split,
-                        std::vector<int64_t>* planes = nullptr, int tile = kGroupedTile);
+                        std::vector<int64_t>* planes = nullptr, int tile = kGroupedTile, int elem = 2);
 // One launch per non-empty list (the grid of each from grouped_grid) of the
 // tile class `tile` (the one the list was built for).  The refined kinds need
 // `planes` in device memory, as build_grouped_work wrote it; F16 / BF16
 // ignore it (may be null).
+// f32: the records' A and B are FP32 matrices (any 4-byte alignment; the
+// list's descs carry vec = 1), converted in the kernel; `planes` may be null.
 int grouped_launch(int kind, int tile, const GroupedWork* work, const int64_t* planes, const GroupedSplit& split,
-                   float alpha, float beta, hipStream_t s);
+                   float alpha, float beta, hipStream_t s, bool f32 = false);
 // Workgroups of a list's launch (a multiple of kXcds).
 int grouped_grid(const GroupedSplit& split, int list, int kind, int tile);
 
