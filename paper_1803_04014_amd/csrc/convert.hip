@@ -477,8 +477,13 @@ int launch_convert_jobs(const ConvJob* jobs, const ConvTask* tasks, int64_t ntas
 // in registers and exchanged through LDS so that whole 128-byte rows go out;
 // `scales` keep the untransposed tile order.
 // The output covers orows x ocols source positions, zero codes beyond the
-// source.  HBM-bound: 4 B read and 1 B written per element; both 4096^2
-// operands 50 us in two launches, @Q us in one.
+// source.
+// Codes come from v_cvt_pk_fp8_f32 on values clamped to +-448, the same as
+// f32_to_e4m3_sat for every float but NaN, whose sign it does not keep: a
+// wavefront that holds one takes f32_to_e4m3_sat.  (That for all, 25
+// instructions per element: both 4096^2 operands 39 us, a 128^2 pair 14; the
+// instruction: 26 and 4.3.)  HBM-bound when large: 4 B read and 1 B written per
+// element, 32 us at the copy rate.
 __global__ __launch_bounds__(256) void quant_fp8_kernel(QuantJob ja, QuantJob jb, uint32_t tiles_a) {
     const bool second = blockIdx.x >= tiles_a;
     const QuantJob& j = second ? jb : ja;
@@ -510,6 +515,11 @@ __global__ __launch_bounds__(256) void quant_fp8_kernel(QuantJob ja, QuantJob jb
     for (int i = 0; i < 16; ++i)
         amax = fmaxf(amax, fmaxf(fmaxf(__builtin_fabsf(v[i][0]), __builtin_fabsf(v[i][1])),
                                  fmaxf(__builtin_fabsf(v[i][2]), __builtin_fabsf(v[i][3]))));
+    float special = 0.0f;  // NaN where the thread holds an infinity or a NaN
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) special = __builtin_fmaf(v[i][q], 0.0f, special);
     // max over the workgroup (order-independent)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
@@ -521,10 +531,21 @@ __global__ __launch_bounds__(256) void quant_fp8_kernel(QuantJob ja, QuantJob jb
     const float inv = __builtin_ldexpf(1.0f, -E);
     if (t == 0) j.scales[tile] = __builtin_ldexpf(1.0f, E);
     uint32_t w[16];  // the four codes of each row
+    if (!__any(special != special)) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-        w[i] = (uint32_t)f32_to_e4m3_sat(v[i][0] * inv) | ((uint32_t)f32_to_e4m3_sat(v[i][1] * inv) << 8) |
-               ((uint32_t)f32_to_e4m3_sat(v[i][2] * inv) << 16) | ((uint32_t)f32_to_e4m3_sat(v[i][3] * inv) << 24);
+        for (int i = 0; i < 16; ++i) {
+            float c[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = __builtin_amdgcn_fmed3f(v[i][q] * inv, -448.0f, 448.0f);
+            const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(c[0], c[1], 0, false);
+            w[i] = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c[2], c[3], lo, true);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            w[i] = (uint32_t)f32_to_e4m3_sat(v[i][0] * inv) | ((uint32_t)f32_to_e4m3_sat(v[i][1] * inv) << 8) |
+                   ((uint32_t)f32_to_e4m3_sat(v[i][2] * inv) << 16) | ((uint32_t)f32_to_e4m3_sat(v[i][3] * inv) << 24);
+    }
     if (!j.trans) {
         const bool words = cc + 4 <= j.ocols && ((uintptr_t)codes % 4) == 0 && ldo % 4 == 0;
 #pragma unroll
