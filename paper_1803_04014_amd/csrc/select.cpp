@@ -123,7 +123,14 @@ int pick_ring_f8(int64_t M, int64_t N, int64_t K) { return pick8(M, N, K, true).
 // block or less of short K, or a batch of such (65536-sized batches of 16^3:
 // 33 us for 40000 against 78 us on a ring of 32 x 32 tiles), else the ring.
 int pick_config_f32(int64_t M, int64_t N, int64_t K, int64_t batch) {
-    return M <= 32 && N <= 32 && (K <= 32 || batch > 1) ? 0 : 1;
+    if (M <= 32 && N <= 32) return K <= 32 || batch > 1 ? 0 : 1;
+    // Many small problems that leave half of the ring's 64 x 64 tile empty, or
+    // are less than half a stage deep: 8397 of 17 x 33 x 41 43 us simple, 77 ring,
+    // of 9 x 60 x 41 41 and 72, of 40 x 40 x 8 29 and 37; but of 33 x 64 x 20 45 and
+    // 37, of 33 x 33 x 33 77 and 73, of 33 x 17 x 64 74 both; 64 of 17 x 33 x 41 10.4
+    // and 5.9, 2000 13 and 20.
+    if (batch >= 512 && K <= 64 && (M <= 32 || N <= 32 || K <= 12)) return 0;
+    return 1;
 }
 
 // The ring tile with the least estimated time: a start-up, then per round of
