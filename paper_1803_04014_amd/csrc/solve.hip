@@ -465,10 +465,12 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
         const int col = tid & (kNb - 1), r0 = tid / kNb;  // column of the panel, first row of this thread
         const bool mine = col < cw && (col < left || col >= left + w);
         float* cp = A + jj * lda + j + col;
+        const float* lp = mine ? cp : A + jj * lda + jj;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int r = r0 + u * (NT / kNb);
-            v[u] = mine && r < nm ? cp[(int64_t)(r < w ? mtop[r] : msrc[r - w]) * lda] : 0.0f;
+            const int top = mtop[min(r, w - 1)], src = msrc[min(max(r - w, 0), W - 1)];
+            v[u] = lp[(int64_t)(r >= nm ? 0 : r < w ? top : src) * lda];  // (no branch around a load)
         }
         memory_barrier();
 #pragma unroll
@@ -657,7 +659,7 @@ __global__ __launch_bounds__(256) void lu_sub_gather(int rows, const float* A, i
 // per column, lane p holding rows i = p mod 4 (of kNb, in registers); unknown
 // k reaches the quad by DPP, and the rows below it take their multiply-add:
 // the same operations in the same order per element as one thread per
-// column.  16 us per panel at n = 2048 against 5.2 + 13.7 us for the
+// column.  12 us per panel at n = 2048 against 5.2 + 13.7 us for the
 // exchanges one after the other and a thread per column.
 constexpr int kTStride = kNb + 16;  // rows 16 banks apart: the quads' reads of a column do not collide
 template <int K4>
@@ -675,15 +677,23 @@ __global__ __launch_bounds__(256) void lu_moves_trsm(int64_t n, float* A, int64_
     const int64_t cend = right ? n : j;
     const int col = tid & (kNb - 1), r0 = tid / kNb;
     const bool mine = c0 + col < cend;
+    // the moves by way of LDS and no branch around a load, so that all of a
+    // thread's rows are in flight together
+    __shared__ int from[2 * kNb], to[2 * kNb];
     const int nm = w + moves->ndisp;
+    if (tid < 2 * kNb) {
+        const int d = min(max(tid - w, 0), kNb - 1), t = min(tid, kNb - 1);
+        const int top = moves->top[t], src = moves->src[d], dst = moves->dst[d];
+        from[tid] = tid >= nm ? 0 : tid < w ? top : src;
+        to[tid] = tid >= nm ? 0 : tid < w ? tid : dst;
+    }
+    __syncthreads();
     float* cp = A + j * lda + c0 + col;
+    const float* lp = mine ? cp : A + j * lda + c0;
     constexpr int kPer = 2 * kNb * kNb / 256;
     float v[kPer];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int r = r0 + 4 * u;
-        v[u] = mine && r < nm ? cp[(int64_t)(r < w ? moves->top[r] : moves->src[r - w]) * lda] : 0.0f;
-    }
+    for (int u = 0; u < kPer; ++u) v[u] = lp[(int64_t)from[r0 + 4 * u] * lda];
     if (right) {  // (then w == kNb)
         float lv[kNb * kNb / 256];
 #pragma unroll
@@ -703,7 +713,7 @@ __global__ __launch_bounds__(256) void lu_moves_trsm(int64_t n, float* A, int64_
         const int r = r0 + 4 * u;
         if (!mine || r >= nm) continue;
         if (right && r < w) T[r * kTStride + col] = v[u];
-        else cp[(int64_t)(r < w ? r : moves->dst[r - w]) * lda] = v[u];
+        else cp[(int64_t)to[r] * lda] = v[u];
     }
     if (!right) return;
     __syncthreads();
