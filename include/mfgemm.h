@@ -308,7 +308,8 @@ int mfg_grouped_autotune(int64_t count, const mfg_problem* problems, int mode, i
  * info (host, may be NULL): 0, or the 1-based index of the first exactly
  * zero pivot (the factorisation is then complete but U is singular).  The
  * call allocates (and frees) a status word, the row moves of a panel (4 n
- * bytes and a fixed table) and, for n > 2048, a 256 KB copy of a sub-panel,
+ * bytes and a fixed table) and, for n > 2048, a copy of a sub-panel (two of
+ * them for n > 4096; 256 KB each at most),
  * and synchronises `stream` before it returns.
  * Errors: MFG_ERR_INVALID_ARG (n < 0, lda < max(1, n), NULL pointers with
  * n > 0, a mode with flags); MFG_ERR_NO_MEMORY if those allocations fail;

@@ -117,13 +117,13 @@ struct LuMoves {
 //
 // Bound by latency: one column's pivot search decides the next column.  The
 // threads' registers hold up to 64 K elements: 512 threads with 128 each
-// (2048 rows x 32, 4096 x 16, 8192 x 8), 256 (a wavefront per SIMD) for up to
-// 1024 rows x 32, so a panel of 64 columns is 2, 4 or 8 sub-panels by its height.
+// (2048 rows x 32, 4096 x 16), 256 (a wavefront per SIMD) for up to 1024 rows x
+// 32, so a panel of 64 columns is 2 or 4 sub-panels by its height.
 // At 2048 rows 54 us per 32 columns (four sub-panels of 8 with launches of
 // their own for the exchanges took 94 us and 11 gaps between launches): about
 // 10 us for the rows to arrive (256 KB at what one CU can have outstanding),
 // 0.8 us per column, 3 us per group's update, 10 us for the exchanges, the
-// solve and the stores.  4096 x 16: 38 us (two of 8: 47), 8192 x 8: 35 (28).
+// solve and the stores.  4096 x 16: 38 us (two of 8: 47).
 //
 // Thread t holds rows i = t + NT q (row jj + i), x[q][0 .. W-1].  Rows are
 // never exchanged in registers: pos[q] is the row's place after the exchanges
@@ -227,17 +227,13 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
     for (int q = 0; q < Q; ++q) {
         const int i = tid + NT * q;
         pos[q] = i < rows ? i : -1;
-        const float* rp = in + (i < rows ? i : 0) * ldin;
         if (!whole) {
+            const float* rp = in + (i < rows ? i : 0) * ldin;
 #pragma unroll
             for (int k = 0; k < W; ++k) x[q][k] = k < w ? rp[k] : 0.0f;
-        } else if constexpr (W == 8) {  // (from the copy: a wavefront's rows are whole lines)
-            const float4 a = reinterpret_cast<const float4*>(rp)[0], b = reinterpret_cast<const float4*>(rp)[1];
-            x[q][0] = a.x, x[q][1] = a.y, x[q][2] = a.z, x[q][3] = a.w;
-            x[q][4] = b.x, x[q][5] = b.y, x[q][6] = b.z, x[q][7] = b.w;
         }
     }
-    if (W > 8 && whole) {
+    if (whole) {
         floatx4 piece[Q][kRowLanes];  // (the vector type: an array of float4 stays in memory)
 #pragma unroll
         for (int q = 0; q < Q; ++q)
@@ -528,7 +524,7 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
             if (tid + NT * q < rows) org[left + pos[q]] = from[q];
     }
     // the factored rows to their places
-    if (W > 8 && whole) {
+    if (whole) {
         int* place = reinterpret_cast<int*>(&stage[wave][0][W]);  // (rows' padding)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -551,11 +547,6 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
         for (int q = 0; q < Q; ++q)
             if (pos[q] >= 0) {
                 float* rp = A + (jj + pos[q]) * lda + jj;
-                if (whole) {  // (W == 8)
-                    reinterpret_cast<float4*>(rp)[0] = make_float4(x[q][0], x[q][1], x[q][2], x[q][3]);
-                    reinterpret_cast<float4*>(rp)[1] = make_float4(x[q][4], x[q][5], x[q][6], x[q][7]);
-                    continue;
-                }
 #pragma unroll
                 for (int k = 0; k < W; ++k)
                     if (k < w) rp[k] = x[q][k];
@@ -742,6 +733,320 @@ __global__ __launch_bounds__(256) void lu_moves_trsm(int64_t n, float* A, int64_
     for (int u = 0; u < kNb / 4; ++u) {
         const int r = r0 + 4 * u;
         cp[(int64_t)r * lda] = T[r * kTStride + col];
+    }
+}
+
+// Panels of 4097 .. 8192 rows: sub-panels of 8 columns, four launches each.
+// (lu_sub with 8 columns took 35 us against 15.3 + 5 here, as its one
+// workgroup also moves the rows back: LU of 8192 36.5 ms against 32.4.)
+// A narrow panel A[j:n, j:j+w] (w <= 8), copied by lu_gather8 into the
+// contiguous rows x 8 array W, held in registers for all of its columns:
+// thread t owns panel rows i = t + kP8Threads q (row j + i), q < kP8Rows (so
+// rows = n - j <= kP8Threads kP8Rows).  One barrier per column c:
+//   - each wavefront finds its largest |value| among its rows at or below the
+//     diagonal (first row on ties; value and row then packed in one key); lane 0
+//     writes the key and the lane owning that row the row's values to the
+//     wavefront's LDS slot, and thread c (owner of the diagonal row, q = 0)
+//     writes that row;
+//   - after the barrier every thread reduces the slots by the same rule, so
+//     each knows the pivot row p and both rows to exchange; their owners swap
+//     them in registers, and every owned row below the diagonal is scaled by
+//     the pivot and gets the rank-1 update of the columns to its right.
+// The slots alternate between two LDS buffers by column parity: a buffer is
+// written again two columns later, by threads that passed the barrier of the
+// column in between, which every thread reaches only after reading it.  Rows
+// move in and out of W as two 16-byte pieces; lu_subpanel_post writes the
+// factored columns back.  Same arithmetic, operation by operation, as lu_panel.
+constexpr int kP8 = 8, kP8Threads = 512, kP8Rows = 16, kP8Waves = kP8Threads / 64;
+
+// Pivot candidates as one 64-bit key: the bits of |value| (non-negative
+// floats order as their bit patterns) above the complement of the row, so
+// the larger value wins and the lower row on ties in one unsigned compare;
+// 0 is "no candidate" (a NaN, a row above the diagonal or past the matrix).
+using P8Key = unsigned long long;
+__device__ __forceinline__ P8Key p8_key(float a, int i) {
+    return ((P8Key)__builtin_bit_cast(uint32_t, a) << 32) | (P8Key)(~(uint32_t)i);
+}
+
+// One step of the key max across lanes: the partner lane given by the DPP
+// control CTRL.
+template <int CTRL>
+__device__ __forceinline__ void p8_dpp_max(P8Key& k) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)k, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(k >> 32), CTRL, 0xF, 0xF, false);
+    const P8Key o = ((P8Key)hi << 32) | lo;
+    k = o > k ? o : k;
+}
+
+__device__ __forceinline__ P8Key p8_lane_key(P8Key k, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(k >> 32), lane);
+    return ((P8Key)hi << 32) | lo;
+}
+
+__global__ __launch_bounds__(kP8Threads) void lu_panel8(int rows, float* W, int64_t j, int w, int32_t* ipiv,
+                                                       int32_t* info) {
+    __shared__ P8Key skey[2][kP8Waves];
+    __shared__ __attribute__((aligned(16))) float srow[2][kP8Waves][kP8];
+    __shared__ __attribute__((aligned(16))) float sdiag[2][kP8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    float x[kP8Rows][kP8];
+#pragma unroll
+    for (int q = 0; q < kP8Rows; ++q) {
+        const int i = tid + kP8Threads * q;
+        float4 u = make_float4(0.0f, 0.0f, 0.0f, 0.0f), v = u;
+        if (i < rows) {
+            const float4* rp = reinterpret_cast<const float4*>(W + (int64_t)i * kP8);
+            u = rp[0], v = rp[1];
+        }
+        x[q][0] = u.x, x[q][1] = u.y, x[q][2] = u.z, x[q][3] = u.w;
+        x[q][4] = v.x, x[q][5] = v.y, x[q][6] = v.z, x[q][7] = v.w;
+    }
+#pragma unroll
+    for (int c = 0; c < kP8; ++c) {
+        if (c >= w) break;
+        const int buf = c & 1;
+        // the thread's candidate: its largest |value| at or below the diagonal
+        // (fmaxf ignores NaN; the row of slot 0 above the diagonal counts as
+        // -1), then the first of its rows holding it; rows past the matrix
+        // hold zeros and come after all real rows, so they are taken only
+        // when the thread has no real candidate, and are then rejected
+        const float v0 = tid >= c ? fabsf(x[0][c]) : -1.0f;
+        float m = v0;
+#pragma unroll
+        for (int q = 1; q < kP8Rows; ++q) m = fmaxf(m, fabsf(x[q][c]));
+        int qs = kP8Rows;
+#pragma unroll
+        for (int q = kP8Rows - 1; q > 0; --q) qs = fabsf(x[q][c]) == m ? q : qs;
+        qs = v0 == m ? 0 : qs;
+        const int is = tid + kP8Threads * qs;
+        P8Key best = (qs < kP8Rows && is < rows && m >= 0.0f) ? p8_key(m, is) : 0;
+        // wavefront reduction: DPP inside each 16-lane row (xor 1, xor 2,
+        // rotate 4, rotate 8 cover the row), then the four rows by readlane
+        p8_dpp_max<0xB1>(best);   // quad_perm [1,0,3,2]
+        p8_dpp_max<0x4E>(best);   // quad_perm [2,3,0,1]
+        p8_dpp_max<0x124>(best);  // row_ror 4
+        p8_dpp_max<0x128>(best);  // row_ror 8
+        P8Key wk = p8_lane_key(best, 0);
+#pragma unroll
+        for (int r = 1; r < 4; ++r) {
+            const P8Key o = p8_lane_key(best, 16 * r);
+            wk = o > wk ? o : wk;
+        }
+        // the wavefront's candidate key and the row's values, written by the
+        // lane owning it (slot wi / kP8Threads, uniform)
+        if (lane == 0) skey[buf][wave] = wk;
+        const int wi = (int)~(uint32_t)wk;
+        if (wk != 0 && (wi & (kP8Threads - 1)) == tid) {
+#pragma unroll
+            for (int q = 0; q < kP8Rows; ++q)
+                if (q == wi / kP8Threads)
+#pragma unroll
+                    for (int cc = 0; cc < kP8; ++cc) srow[buf][wave][cc] = x[q][cc];
+        }
+        if (tid == c)
+#pragma unroll
+            for (int cc = 0; cc < kP8; ++cc) sdiag[buf][cc] = x[0][cc];
+        __syncthreads();
+        P8Key pk = skey[buf][0];
+        int pw = 0;
+#pragma unroll
+        for (int q = 1; q < kP8Waves; ++q) {
+            const P8Key o = skey[buf][q];
+            if (o > pk) pk = o, pw = q;
+        }
+        int pi = (int)~(uint32_t)pk;
+        if (pk == 0) pi = c, pw = -1;  // no candidate (every |value| NaN): the diagonal row
+        pi = __builtin_amdgcn_readfirstlane(pi);
+        pw = __builtin_amdgcn_readfirstlane(pw);
+        // both rows read whole and at once (one LDS round trip), then chosen
+        const float4* dp = reinterpret_cast<const float4*>(sdiag[buf]);
+        const float4* sp = reinterpret_cast<const float4*>(srow[buf][pw >= 0 ? pw : 0]);
+        const float4 d0 = dp[0], d1 = dp[1], s0 = sp[0], s1 = sp[1];
+        const float dr[kP8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+        const float sr[kP8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+        float pr[kP8];
+#pragma unroll
+        for (int cc = 0; cc < kP8; ++cc) pr[cc] = pw >= 0 ? sr[cc] : dr[cc];
+        if (tid == 0) ipiv[j + c] = (int32_t)(j + pi);
+        if (pi != c) {  // two lanes exchange rows j + c (slot 0 of thread c) and j + pi
+            if (tid == (pi & (kP8Threads - 1))) {
+#pragma unroll
+                for (int q = 0; q < kP8Rows; ++q)
+                    if (q == pi / kP8Threads)
+#pragma unroll
+                        for (int cc = 0; cc < kP8; ++cc) x[q][cc] = dr[cc];
+            }
+            if (tid == c)
+#pragma unroll
+                for (int cc = 0; cc < kP8; ++cc) x[0][cc] = pr[cc];
+        }
+        const float pv = pr[c];  // the pivot row is now row j + c
+        if (tid == 0 && pv == 0.0f && *info == 0) *info = (int32_t)(j + c + 1);
+        if (pv != 0.0f) {
+            // rows below the diagonal; rows past the matrix hold zeros, take the
+            // update harmlessly (or skip it with their wavefront) and are never
+            // stored or chosen as pivots
+            const float rp = 1.0f / pv;
+#pragma unroll
+            for (int q = 0; q < kP8Rows; ++q) {
+                if (kP8Threads * q + 64 * wave >= rows) continue;  // the wavefront's rows of slot q are all past the matrix
+                const bool below = q > 0 || tid > c;
+                const float l = x[q][c] * rp;
+                x[q][c] = below ? l : x[q][c];
+#pragma unroll
+                for (int cc = c + 1; cc < kP8; ++cc) {
+                    const float u = __builtin_fmaf(-l, pr[cc], x[q][cc]);
+                    x[q][cc] = below ? u : x[q][cc];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kP8Rows; ++q) {
+        const int i = tid + kP8Threads * q;
+        if (i < rows) {
+            float4* rp = reinterpret_cast<float4*>(W + (int64_t)i * kP8);
+            rp[0] = make_float4(x[q][0], x[q][1], x[q][2], x[q][3]);
+            rp[1] = make_float4(x[q][4], x[q][5], x[q][6], x[q][7]);
+        }
+    }
+}
+
+// The sub-panel A[j:j+rows, j:j+w] (w <= kP8) copied into W (rows x kP8,
+// row-major, 16-byte aligned; columns from w on zero), one thread per row
+// over as many workgroups as it takes (lu_subpanel_post writes it back the
+// same way): A's rows are lda apart, and one workgroup fetching them all
+// (each row a separate line and page) took most of the panel kernel's time.
+// vec: w == kP8 and A's rows 16-byte aligned at column j (two 16-byte pieces
+// per row), else element by element.
+__global__ __launch_bounds__(256) void lu_gather8(const float* A, int64_t lda, int64_t j, int rows, int w, int vec,
+                                                  float* W) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= rows) return;
+    const float* rp = A + (j + i) * lda + j;
+    float4* wp = reinterpret_cast<float4*>(W + (int64_t)i * kP8);
+    if (vec) {
+        wp[0] = *reinterpret_cast<const float4*>(rp);
+        wp[1] = *reinterpret_cast<const float4*>(rp + 4);
+    } else {
+        float v[kP8];
+#pragma unroll
+        for (int c = 0; c < kP8; ++c) v[c] = c < w ? rp[c] : 0.0f;
+        wp[0] = make_float4(v[0], v[1], v[2], v[3]);
+        wp[1] = make_float4(v[4], v[5], v[6], v[7]);
+    }
+}
+
+// After lu_panel8 on the sub-panel at column jj of the panel [c0, c1):
+// blocks 0 .. nb-1 write the factored sub-panel back from W, one thread per
+// row (as lu_gather8 read it); block nb gives each column of the panel
+// outside the sub-panel one thread, which applies the sub-panel's row swaps
+// to its column in order and, right of the sub-panel, solves the 8 rows jj ..
+// jj+7 of its column with the unit lower block L11 (U12 = L11^-1 A12, L11
+// from W).  The columns are independent, so swaps and solve need no barrier
+// between them, and the write-back touches none of their elements.
+__global__ __launch_bounds__(256) void lu_subpanel_post(float* A, int64_t lda, int64_t jj, int rows, int wi, int vec,
+                                                        const float* W, const int32_t* ipiv, int64_t c0, int64_t c1,
+                                                        int nb) {
+    if ((int)blockIdx.x < nb) {
+        const int i = blockIdx.x * 256 + threadIdx.x;
+        if (i >= rows) return;
+        float* rp = A + (jj + i) * lda + jj;
+        const float4* wp = reinterpret_cast<const float4*>(W + (int64_t)i * kP8);
+        if (vec) {
+            *reinterpret_cast<float4*>(rp) = wp[0];
+            *reinterpret_cast<float4*>(rp + 4) = wp[1];
+        } else {
+            const float4 u = wp[0], v = wp[1];
+            const float e[kP8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int c = 0; c < kP8; ++c)
+                if (c < wi) rp[c] = e[c];
+        }
+        return;
+    }
+    __shared__ float L[kP8][kP8];
+    if (threadIdx.x < kP8 * kP8) L[threadIdx.x / kP8][threadIdx.x % kP8] = W[threadIdx.x];
+    __syncthreads();
+    const int64_t col = c0 + threadIdx.x;  // c1 - c0 <= kNb < 256
+    if (col >= c1 || (col >= jj && col < jj + wi)) return;
+    for (int c = 0; c < wi; ++c) {
+        const int64_t k = jj + c, p = ipiv[k];
+        if (p != k) {
+            const float t = A[k * lda + col];
+            A[k * lda + col] = A[p * lda + col];
+            A[p * lda + col] = t;
+        }
+    }
+    if (col < jj + wi) return;  // left of the sub-panel: swaps only
+    // right of it (then wi == kP8: only the panel's last sub-panel is narrower)
+    float x[kP8];
+#pragma unroll
+    for (int i = 0; i < kP8; ++i) x[i] = A[(jj + i) * lda + col];
+#pragma unroll
+    for (int i = 1; i < kP8; ++i)
+#pragma unroll
+        for (int k = 0; k < i; ++k) x[i] = __builtin_fmaf(-L[i][k], x[k], x[i]);
+#pragma unroll
+    for (int i = 0; i < kP8; ++i) A[(jj + i) * lda + col] = x[i];
+}
+
+// The rest of the panel after a factored sub-panel [jj, jj + 8): A[r, c] -=
+// sum_k L21[r, k] U12[k, c] for rows r in [jj + 8, jj + 8 + below) and
+// columns c in [jj + 8, c1), L21 from the sub-panel's copy W (its rows from 8
+// on) and U12 = A[jj:jj+8, c] (solved by lu_subpanel_post), summed over k in
+// order by fused multiply-adds.  One thread per row and group of 8 columns
+// (threads of one row adjacent, so a row's groups are read and written
+// together).  The first group is the next sub-panel: its updated values also
+// go to that sub-panel's copy Wn (row r at r - jj - 8, columns from wn on
+// zero), so it needs no gather.  vec: A's rows 16-byte aligned at these
+// columns.
+__global__ __launch_bounds__(256) void lu_subpanel_update(float* A, int64_t lda, int64_t jj, int below, int64_t c1,
+                                                          const float* W, float* Wn, int wn, int vec) {
+    __shared__ float U[kP8][kNb];
+    const int cols = (int)(c1 - jj - kP8);  // 1 .. kNb - kP8
+    for (int e = threadIdx.x; e < kP8 * cols; e += 256) U[e / cols][e % cols] = A[(jj + e / cols) * lda + jj + kP8 + e % cols];
+    __syncthreads();
+    const int groups = (cols + kP8 - 1) / kP8;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int r = (int)(t / groups), g = (int)(t % groups);
+    if (r >= below) return;
+    const int cg = g * kP8;                          // first column of the group, from jj + 8
+    const int nc = cols - cg < kP8 ? cols - cg : kP8;  // columns in the group
+    const float4* lp = reinterpret_cast<const float4*>(W + (int64_t)(kP8 + r) * kP8);
+    const float4 l0 = lp[0], l1 = lp[1];
+    const float l[kP8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+    float* cp = A + (jj + kP8 + r) * lda + jj + kP8 + cg;
+    float acc[kP8];
+    if (vec && nc == kP8) {
+        const float4 a0 = reinterpret_cast<const float4*>(cp)[0], a1 = reinterpret_cast<const float4*>(cp)[1];
+        acc[0] = a0.x, acc[1] = a0.y, acc[2] = a0.z, acc[3] = a0.w;
+        acc[4] = a1.x, acc[5] = a1.y, acc[6] = a1.z, acc[7] = a1.w;
+    } else {
+#pragma unroll
+        for (int cc = 0; cc < kP8; ++cc) acc[cc] = cc < nc ? cp[cc] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < kP8; ++k)
+#pragma unroll
+        for (int cc = 0; cc < kP8; ++cc)
+            if (cc < nc) acc[cc] = __builtin_fmaf(-l[k], U[k][cg + cc], acc[cc]);
+    if (vec && nc == kP8) {
+        reinterpret_cast<float4*>(cp)[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        reinterpret_cast<float4*>(cp)[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+    } else {
+#pragma unroll
+        for (int cc = 0; cc < kP8; ++cc)
+            if (cc < nc) cp[cc] = acc[cc];
+    }
+    if (g == 0) {
+        float4* wp = reinterpret_cast<float4*>(Wn + (int64_t)r * kP8);
+        float v[kP8];
+#pragma unroll
+        for (int cc = 0; cc < kP8; ++cc) v[cc] = cc < wn ? acc[cc] : 0.0f;
+        wp[0] = make_float4(v[0], v[1], v[2], v[3]);
+        wp[1] = make_float4(v[4], v[5], v[6], v[7]);
     }
 }
 
@@ -1038,15 +1343,20 @@ bool factor_mode_ok(int mode) {
 
 }  // namespace
 
-// The sub-panel widths by height: lu_sub's registers hold the rows.
-constexpr int64_t kSubRows = 8192, kSubFloats = kSubRows * 8;
-static int sub_width(int64_t rows) { return rows <= 2048 ? 32 : rows <= 4096 ? 16 : 8; }
+// Panels by height: up to kSubRows rows in sub-panels of 32 or 16 columns
+// (lu_sub's registers hold the rows), up to kP8Threads x kP8Rows in sub-panels
+// of 8 (lu_panel8), above that column by column (lu_panel).
+constexpr int64_t kSubRows = 4096, kRows8 = (int64_t)kP8Threads * kP8Rows;
+static int sub_width(int64_t rows) { return rows <= 2048 ? 32 : 16; }
 
-// Bytes of device scratch of lu_factor_impl: the copy of a narrow sub-panel
-// (see lu_factor_impl), the panel's row moves, the origin of each row.
-static int64_t sub_copy_floats(int64_t n) { return sub_width(n) < 32 ? kSubFloats : 0; }
+// Floats of one copy of a sub-panel, and bytes of lu_factor_impl's device
+// scratch: two copies for lu_panel8 (each at least the 8 x 8 diagonal block that
+// lu_subpanel_post reads), of which lu_sub's narrow sub-panels use the first; the
+// panel's row moves; the origin of each row.
+static int64_t lu_copy_floats(int64_t n) { return n <= 2048 ? 0 : std::min(n, kRows8) * (n > kSubRows ? 8 : 16); }
+static int64_t lu_copies(int64_t n) { return n > kSubRows ? 2 : 1; }
 size_t lu_scratch_bytes(int64_t n) {
-    return (size_t)sub_copy_floats(n) * sizeof(float) + sizeof(LuMoves) + (size_t)n * sizeof(int32_t);
+    return (size_t)(lu_copy_floats(n) * lu_copies(n)) * sizeof(float) + sizeof(LuMoves) + (size_t)n * sizeof(int32_t);
 }
 
 // One sub-panel by the workgroup whose registers hold its rows.
@@ -1056,17 +1366,52 @@ static int launch_lu_sub(int rows, const float* in, int64_t ldin, float* A, int6
 #define MFG_LU_SUB(W_, Q_, NT_)                                                                                       \
     hipLaunchKernelGGL((lu_sub<W_, Q_, NT_>), dim3(1), dim3(NT_), 0, s, rows, in, ldin, A, lda, j, jj, w, cw, vec, ipiv, \
                        info, org, moves)
-    if (W == 32) {
-        if (rows <= 512) MFG_LU_SUB(32, 2, 256);
-        else if (rows <= 1024) MFG_LU_SUB(32, 4, 256);
-        else MFG_LU_SUB(32, 4, 512);
-    } else if (W == 16) {
-        MFG_LU_SUB(16, 8, 512);
-    } else {
-        MFG_LU_SUB(8, 16, 512);
-    }
+    if (W == 16) MFG_LU_SUB(16, 8, 512);
+    else if (rows <= 512) MFG_LU_SUB(32, 2, 256);
+    else if (rows <= 1024) MFG_LU_SUB(32, 4, 256);
+    else MFG_LU_SUB(32, 4, 512);
 #undef MFG_LU_SUB
     MFG_LAUNCH_CHECK();
+    return MFG_OK;
+}
+
+// One panel [j, j + w) of at most kRows8 rows by sub-panels of 8 columns: each
+// held in a contiguous copy (the first gathered by lu_gather8, the others
+// written by the previous one's update; the two copies alternate), factored
+// there in registers (lu_panel8), written back with its swaps applied across
+// the panel and its block row solved (lu_subpanel_post), and the rest of the
+// panel updated with K = 8 (lu_subpanel_update, L21 read from the copy).
+static int lu_panel_by_8(int64_t n, float* A, int64_t lda, int64_t j, int w, int aligned, int32_t* ipiv, int32_t* info,
+                         float* copy0, float* copy1, hipStream_t s) {
+    float* const copies[2] = {copy0, copy1};
+    int cur = 0;
+    bool held = false;  // copies[cur] already holds this sub-panel
+    for (int64_t jj = j; jj < j + w; jj += kP8) {
+        const int wi = (int)std::min<int64_t>(kP8, j + w - jj);
+        const int vec = wi == kP8 && aligned;
+        const int rows = (int)(n - jj);
+        float* const Wc = copies[cur];
+        if (!held) {
+            hipLaunchKernelGGL(lu_gather8, dim3(blocks(rows, 256)), dim3(256), 0, s, A, lda, jj, rows, wi, vec, Wc);
+            MFG_LAUNCH_CHECK();
+        }
+        hipLaunchKernelGGL(lu_panel8, dim3(1), dim3(kP8Threads), 0, s, rows, Wc, jj, wi, ipiv, info);
+        MFG_LAUNCH_CHECK();
+        const unsigned nb = blocks(rows, 256);
+        hipLaunchKernelGGL(lu_subpanel_post, dim3(nb + 1), dim3(256), 0, s, A, lda, jj, rows, wi, vec, Wc, ipiv, j, j + w,
+                           (int)nb);
+        MFG_LAUNCH_CHECK();
+        const int64_t right = j + w - (jj + wi);  // columns of the panel right of the sub-panel
+        const int below = rows - wi;              // > 0 whenever right > 0 (then wi == kP8)
+        held = right > 0 && below > 0;
+        if (!held) continue;
+        const int wn = (int)std::min<int64_t>(kP8, right);
+        const int64_t threads = (int64_t)below * ((right + kP8 - 1) / kP8);
+        hipLaunchKernelGGL(lu_subpanel_update, dim3(blocks(threads, 256)), dim3(256), 0, s, A, lda, jj, below, j + w, Wc,
+                           copies[cur ^ 1], wn, aligned);
+        MFG_LAUNCH_CHECK();
+        cur ^= 1;
+    }
     return MFG_OK;
 }
 
@@ -1075,15 +1420,14 @@ static int launch_lu_sub(int rows, const float* in, int64_t ldin, float* A, int6
 // (lu_sub), each followed by the update of the panel's columns right of it
 // (lu_sub_update); the panel's row moves on all other columns and the block
 // row's solve (lu_moves_trsm); the trailing update by mfg_gemm.  Sub-panels of
-// less than 32 columns come from a copy rows x W written by the update before
-// (the panel's first by lu_sub_gather): their rows are part of a 128-byte line
-// each, and what one CU can have outstanding is lines (n = 8192: 2 ms of 45).
-// Panels taller than a sub-panel's workgroup holds go column by column
-// (lu_panel, lu_laswp, lu_trsm).
+// 16 columns come from a copy rows x 16 written by the update before (the
+// panel's first by lu_sub_gather): their rows are half of a 128-byte line, and
+// what one CU can have outstanding is lines.  Taller panels, see kSubRows,
+// swap their rows by lu_laswp and solve the block row by lu_trsm.
 int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* info, void* scratch, int mode,
                    hipStream_t s) {
-    float* const copy = sub_copy_floats(n) > 0 ? static_cast<float*>(scratch) : nullptr;
-    LuMoves* const moves = reinterpret_cast<LuMoves*>(static_cast<float*>(scratch) + sub_copy_floats(n));
+    float* const copy = static_cast<float*>(scratch);
+    LuMoves* const moves = reinterpret_cast<LuMoves*>(copy + lu_copy_floats(n) * lu_copies(n));
     int32_t* const org = reinterpret_cast<int32_t*>(moves + 1);
     const int vec = lda % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
     MFG_HIP_CHECK(hipMemsetAsync(info, 0, sizeof(int32_t), s));
@@ -1095,9 +1439,8 @@ int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* inf
             float* const next = W < 32 ? copy : nullptr;
             if (next != nullptr) {
                 const int rows = (int)(n - j);
-                const dim3 g(blocks((int64_t)rows * (W / 8), 256));
-                if (W == 16) hipLaunchKernelGGL(lu_sub_gather<16>, g, dim3(256), 0, s, rows, A, lda, j, w, vec, next);
-                else hipLaunchKernelGGL(lu_sub_gather<8>, g, dim3(256), 0, s, rows, A, lda, j, w, vec, next);
+                hipLaunchKernelGGL(lu_sub_gather<16>, dim3(blocks((int64_t)rows * 2, 256)), dim3(256), 0, s, rows, A, lda, j,
+                                   w, vec, next);
                 MFG_LAUNCH_CHECK();
             }
             for (int64_t jj = j; jj < j + w; jj += W) {
@@ -1110,8 +1453,7 @@ int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* inf
                 if (right <= 0 || below <= 0) continue;
                 const dim3 g(blocks((int64_t)below * ((right + 7) / 8), 256)), t(256);
                 if (W == 32) hipLaunchKernelGGL(lu_sub_update<32>, g, t, 0, s, A, lda, jj, below, j + w, vec, next);
-                else if (W == 16) hipLaunchKernelGGL(lu_sub_update<16>, g, t, 0, s, A, lda, jj, below, j + w, vec, next);
-                else hipLaunchKernelGGL(lu_sub_update<8>, g, t, 0, s, A, lda, jj, below, j + w, vec, next);
+                else hipLaunchKernelGGL(lu_sub_update<16>, g, t, 0, s, A, lda, jj, below, j + w, vec, next);
                 MFG_LAUNCH_CHECK();
             }
             const unsigned g = (unsigned)((j + kNb - 1) / kNb + (rest + kNb - 1) / kNb);
@@ -1120,8 +1462,13 @@ int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* inf
                 MFG_LAUNCH_CHECK();
             }
         } else {
-            hipLaunchKernelGGL(lu_panel, dim3(1), dim3(kPanelThreads), 0, s, n, A, lda, j, w, ipiv, info);
-            MFG_LAUNCH_CHECK();
+            if (n - j <= kRows8) {
+                const int st = lu_panel_by_8(n, A, lda, j, w, vec, ipiv, info, copy, copy + lu_copy_floats(n), s);
+                if (st != MFG_OK) return st;
+            } else {
+                hipLaunchKernelGGL(lu_panel, dim3(1), dim3(kPanelThreads), 0, s, n, A, lda, j, w, ipiv, info);
+                MFG_LAUNCH_CHECK();
+            }
             hipLaunchKernelGGL(lu_laswp, dim3(blocks(n, 256)), dim3(256), 0, s, n, A, lda, j, w, ipiv);
             MFG_LAUNCH_CHECK();
             if (rest > 0) {
