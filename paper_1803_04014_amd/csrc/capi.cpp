@@ -169,9 +169,11 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             int cfg = choose(vec, K % 128 == 0);
             if (cfg < 0 || cfg >= num_configs_f8()) return MFG_ERR_INVALID_ARG;
             if (f8_config_needs_bt(cfg) && (!vec || (config >= 0 && K % 128 != 0))) return MFG_ERR_UNSUPPORTED;
-            // the simple kernel, which needs no Bt, where Bt's padded rows exceed the
-            // fixed array or the transpose's grid
-            if (config < 0 && K % 128 != 0 && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535)) cfg = 0;
+            // Ragged K and grids under 64 tiles of 128 x 128 are served whatever the
+            // storage and the size: by the simple kernel, which reads B's codes as
+            // they are, where Bt would exceed the fixed array or the transpose's grid
+            const bool bare = config < 0 && (K % 128 != 0 || cdiv(M, 128) * cdiv(N, 128) < 64);
+            if (bare && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535)) cfg = 0;
             if (!f8_config_needs_bt(cfg)) return launch_gemm_f8(cfg, a, vec, s);
             CallWs ws;
             if ((st = call_ws(s, (size_t)bT, ext, ws)) != MFG_OK) return st;
