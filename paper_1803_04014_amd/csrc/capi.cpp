@@ -123,6 +123,13 @@ static int call_ws(hipStream_t s, size_t bytes, const ExtWs* ext, CallWs& w) {
     return MFG_OK;
 }
 
+static bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;  // (the default stream beside another stream's capture)
+}
+
 static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                      float* C, int64_t ldc, float alpha, float beta, int mode, int config, hipStream_t s,
                      const ExtWs* ext = nullptr) {
@@ -172,11 +179,15 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             // Ragged K and grids under 64 tiles of 128 x 128 are served whatever the
             // storage and the size: by the simple kernel, which reads B's codes as
             // they are, where Bt would exceed the fixed array or the transpose's grid
+            // or there is no memory for it, and under capture (a graph would hold the
+            // workspace's address past its next growth)
             const bool bare = config < 0 && (K % 128 != 0 || cdiv(M, 128) * cdiv(N, 128) < 64);
-            if (bare && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535)) cfg = 0;
+            if (bare && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535 || (!ext && capturing(s)))) cfg = 0;
             if (!f8_config_needs_bt(cfg)) return launch_gemm_f8(cfg, a, vec, s);
             CallWs ws;
-            if ((st = call_ws(s, (size_t)bT, ext, ws)) != MFG_OK) return st;
+            st = call_ws(s, (size_t)bT, ext, ws);
+            if (st == MFG_ERR_NO_MEMORY && bare) return launch_gemm_f8(0, a, vec, s);
+            if (st != MFG_OK) return st;
             uint8_t* bt = static_cast<uint8_t*>(ws.ptr);
             if ((st = launch_transpose_b8(K, k128, N, a.B, ldb, bt, ldt, s)) != MFG_OK) return st;
             a.Bt = bt, a.ldbt = ldt;

@@ -62,3 +62,39 @@ def test_k_beyond_the_transpose(K):
     a, b, c, ref = _both(16, 16, K)
     assert _call("mfg_gemm", 16, 16, K, a, b, c) == 0
     assert np.array_equal(host(c).view(np.uint32), host(ref).view(np.uint32))
+
+
+SMALL = [(64, 8192, 8200), (100, 300, 8192)]  # ragged K; K % 128 == 0 on few tiles
+
+
+@pytest.mark.parametrize("M,N,K", SMALL)
+def test_without_memory(M, N, K):
+    a, b, c, ref = _both(M, N, K)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    assert mfg.lib().mfg_fault_inject(0, 1) == 0  # the next allocation fails
+    try:
+        assert _call("mfg_gemm", M, N, K, a, b, c, stream=st) == 0
+    finally:
+        mfg.lib().mfg_fault_inject(0, 0)
+    assert np.array_equal(host(c).view(np.uint32), host(ref).view(np.uint32))
+
+
+@pytest.mark.parametrize("M,N,K", SMALL)
+def test_captured_and_replayed_past_the_workspace(M, N, K):
+    """A captured call holds no memory of the library: replays are right also
+    after the capture stream's workspace has been used and has grown."""
+    a, b, c, ref = _both(M, N, K)
+    st = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        assert _call("mfg_gemm", M, N, K, a, b, c) == 0
+    for n in (512, 2048, 4096):  # eager work on that stream, its workspace growing each time
+        x = torch.ones((n, n), dtype=torch.float32, device=DEV)
+        y = torch.empty_like(x)
+        torch.cuda.synchronize()
+        mfg.gemm(x, x, y, mode="split3", stream=st.cuda_stream)
+        torch.cuda.synchronize()
+        c.fill_(float("nan"))
+        graph.replay()
+        assert np.array_equal(host(c).view(np.uint32), host(ref).view(np.uint32)), n
