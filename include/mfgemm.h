@@ -414,8 +414,12 @@ int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode);
  * rounded up to 8, or to 16 for FP8) and B (ld = N rounded likewise), each
  * rounded up to 256 bytes; 0 for MFG_F32 and for empty problems, and 0 for
  * MFG_BF16_SPLIT6, which runs through mfg_gemm and its per-stream workspace
- * (12 bytes per element of A and B, outside the budget).  The fixed
- * per-slot descriptor staging is not counted.  Results are bitwise those of
+ * (12 bytes per element of A and B, outside the budget).  The memory behind
+ * the footprints is kept by the slots from group to group and given back with
+ * the server; what all slots hold, idle or running, is at most
+ * hbm_budget_bytes too: idle slots give theirs up when another needs it, and
+ * a group that does not fit beside what running slots hold waits for one of
+ * them.  The fixed per-slot descriptor staging is not counted.  Results are bitwise those of
  * mfg_gemm on the same FP32 operands, whatever a request is grouped with.
  * Config limits: 1 <= slots <= 64, 1 <= max_group <= 4096, reserved = 0.
  * Request limits: mode without flags, reserved = 0, mfg_gemm's validation.

@@ -126,7 +126,11 @@ struct Slot {
     std::vector<GroupedDesc> h_desc;  // the group's problems (host side)
     GroupedWork* h_work = nullptr;
     GroupedWork* d_work = nullptr;
-    char* arena = nullptr;  // converted operands of the running group
+    // Converted operands of the running group: `held` bytes are counted for them
+    // (the scheduler's decision, see reserve), in the arena or, where it could
+    // not be allocated, in allocations of the requests' own.
+    uint64_t held = 0;
+    char* arena = nullptr;
     size_t arena_cap = 0, arena_used = 0;
     int64_t* h_planes = nullptr;  // refined modes: residual-plane offsets, two per work item
     int64_t* d_planes = nullptr;
@@ -162,14 +166,17 @@ struct mfg_server {
     bool launch_ready(std::unique_lock<std::mutex>& lk);
     void start_group(int si, const std::vector<Req*>& g);
     void enqueue_group(int si, const std::vector<Req*>& g, std::vector<int>& status, bool& event_failed);
-    void reserve_arena(Slot& sl, const std::vector<Req*>& g);
+    bool reserve(int si, uint64_t need);
+    uint64_t held_bytes() const;
+    void release_arena(Slot& sl);
+    void allocate_arena(Slot& sl, const std::vector<Req*>& g);
     int run_request(Slot& sl, Req* q, bool grouped);
     int run_grouped(Slot& sl, const std::vector<Req*>& g);
 };
 
 int mfg_server::init_device() {
     MFG_HIP_CHECK(hipSetDevice(cfg.device));
-    int pools = 0;  // groups beyond a slot's arena take stream-ordered allocations
+    int pools = 0;  // requests without a place in an arena take stream-ordered allocations
     MFG_HIP_CHECK(hipDeviceGetAttribute(&pools, hipDeviceAttributeMemoryPoolsSupported, cfg.device));
     if (!pools) return MFG_ERR_UNSUPPORTED;
     work_cap = (int64_t)cfg.max_group * kSmallTiles;
@@ -271,6 +278,44 @@ bool mfg_server::admit() {
     return any;
 }
 
+uint64_t mfg_server::held_bytes() const {
+    uint64_t h = 0;
+    for (const Slot& sl : slots) h += sl.held;
+    return h;
+}
+
+// Storage for a group of `need` bytes on free slot si, or false if it has to
+// wait for a busy slot: what all slots hold together, idle ones too, stays
+// within the budget.  A slot keeps its arena from group to group, as an
+// allocation costs 53 us and a free 24 (a burst of 64 mixed requests took
+// 6.5-7.0 ms with both per request).  It grows to the largest group so far, up
+// to half of the slot's share of the budget, so that other groups find room
+// beside the arenas of busy slots; a larger group gets exactly what it needs.
+// Idle arenas give way when the budget would not do.  With no slot busy any
+// admitted group fits, so none waits forever.
+bool mfg_server::reserve(int si, uint64_t need) {
+    Slot& sl = slots[(size_t)si];
+    const uint64_t share = cfg.hbm_budget_bytes / (2 * (uint64_t)cfg.slots);
+    if (need == 0) {  // (an arena beyond the share is not kept through a group that has no use for it)
+        if (sl.held > share) sl.held = 0;
+        return true;
+    }
+    if (need <= sl.held && (sl.held <= share || need > share)) return true;
+    uint64_t others = held_bytes() - sl.held;
+    const uint64_t twice = sl.held <= share ? 2 * sl.held : 0;
+    uint64_t want = need > share ? need : std::min(share, std::max({need, twice, (uint64_t)32 << 20}));
+    for (Slot& o : slots) {
+        if (others + want <= cfg.hbm_budget_bytes) break;
+        if (o.busy || &o == &sl) continue;
+        others -= o.held;
+        o.held = 0;
+    }
+    if (others + want > cfg.hbm_budget_bytes) want = need;
+    if (others + want > cfg.hbm_budget_bytes) return false;
+    sl.held = want;
+    return true;
+}
+
 // Called with the mutex held.  Picks a group for every free slot (marking
 // the slot busy and its requests running), then releases the mutex while
 // it enqueues their work, and records the outcome under it again.
@@ -282,20 +327,19 @@ bool mfg_server::launch_ready(std::unique_lock<std::mutex>& lk) {
         std::vector<Req*> g;
         if (!grouped_small(head->r)) {
             g.push_back(head);
-            admitted.pop_front();
         } else {
             const mfg_request& h = head->r;
-            for (auto it = admitted.begin(); it != admitted.end() && (int)g.size() < cfg.max_group;) {
-                const mfg_request& r = (*it)->r;
-                if (r.mode == h.mode && r.alpha == h.alpha && r.beta == h.beta && grouped_small(r)) {
-                    g.push_back(*it);
-                    it = admitted.erase(it);
-                } else {
-                    ++it;
-                }
+            for (Req* q : admitted) {
+                if ((int)g.size() == cfg.max_group) break;
+                const mfg_request& r = q->r;
+                if (r.mode == h.mode && r.alpha == h.alpha && r.beta == h.beta && grouped_small(r)) g.push_back(q);
             }
         }
+        uint64_t need = 0;
+        for (const Req* q : g) need += (uint64_t)q->footprint;
+        if (!reserve(si, need)) break;  // first come, first served: the ones behind it wait too
         start_group(si, g);
+        std::erase_if(admitted, [](const Req* q) { return q->state == RUNNING; });
         picked.emplace_back(si, std::move(g));
     }
     int64_t busy = 0;
@@ -317,14 +361,16 @@ bool mfg_server::launch_ready(std::unique_lock<std::mutex>& lk) {
                     q->res.status = MFG_ERR_HIP;
             }
             if (log_enabled())
-                std::fprintf(stderr, "mfg_server: slot %d mode %d group %zu (dry run)\n", si, g.front()->r.mode,
-                             g.size());
+                std::fprintf(stderr, "mfg_server: slot %d mode %d group %zu held %llu (dry run)\n", si,
+                             g.front()->r.mode, g.size(), (unsigned long long)held_bytes());
         }
         return true;
     }
     std::vector<std::vector<int>> status(picked.size());
     std::vector<char> event_failed(picked.size(), 0);
     lk.unlock();
+    for (Slot& sl : slots)  // arenas given up or to be replaced, before any new one
+        if (sl.arena && sl.arena_cap != sl.held) release_arena(sl);
     for (size_t i = 0; i < picked.size(); ++i) {
         bool ef = false;
         enqueue_group(picked[i].first, picked[i].second, status[i], ef);
@@ -340,25 +386,34 @@ bool mfg_server::launch_ready(std::unique_lock<std::mutex>& lk) {
     return true;
 }
 
-// The slot's arena made ready for group g.  A slot runs one group at a time
-// and its previous group has completed, so the arena is free to be used (and
-// replaced) without ordering.  It grows to the largest group so far, at most
-// to the slot's share of the budget, and is given back with the server; what
-// does not fit (or could not be allocated) takes a stream-ordered allocation
-// of its own.  Those cost 53 us per request and 24 us per free, as the
-// device's pool gives its memory back at every synchronisation: a burst of
-// 64 mixed requests took 6.5-7.0 ms with them and takes 1.5 ms without.
-void mfg_server::reserve_arena(Slot& sl, const std::vector<Req*>& g) {
+// A slot runs one group at a time and its previous group has completed, so its
+// arena is free to be used or replaced without ordering.
+void mfg_server::release_arena(Slot& sl) {
+    (void)hipFree(sl.arena);
+    sl.arena = nullptr, sl.arena_cap = 0;
+}
+
+// The arena of `held` bytes for group g; the group's bytes alone if the device
+// is short of memory, then without the arenas of idle slots.  (Without one,
+// each request allocates its own.)
+void mfg_server::allocate_arena(Slot& sl, const std::vector<Req*>& g) {
     sl.arena_used = 0;
     size_t need = 0;
     for (const Req* q : g) need += (size_t)q->footprint;
-    const size_t most = (size_t)(cfg.hbm_budget_bytes / (uint64_t)cfg.slots);
-    if (need <= sl.arena_cap || need > most) return;
-    const size_t want = std::min(most, std::max({need, 2 * sl.arena_cap, (size_t)32 << 20}));
-    if (sl.arena) (void)hipFree(sl.arena);
-    sl.arena = nullptr, sl.arena_cap = 0;
-    if (hipMalloc((void**)&sl.arena, want) == hipSuccess) {
-        sl.arena_cap = want;
+    if (sl.arena || need == 0) return;
+    size_t want = (size_t)sl.held;
+    hipError_t e = hipMalloc((void**)&sl.arena, want);
+    if (e != hipSuccess) {
+        for (Slot& o : slots)
+            if (o.arena && !o.busy) {
+                release_arena(o);
+                o.held = 0;
+            }
+        want = need;
+        e = hipMalloc((void**)&sl.arena, want);
+    }
+    if (e == hipSuccess) {
+        sl.arena_cap = want, sl.held = want;
     } else {
         sl.arena = nullptr;
         (void)hipGetLastError();
@@ -455,7 +510,7 @@ void mfg_server::enqueue_group(int si, const std::vector<Req*>& g, std::vector<i
     Slot& sl = slots[si];
     status.assign(g.size(), MFG_OK);
     const bool grouped = grouped_small(g.front()->r);
-    reserve_arena(sl, g);
+    allocate_arena(sl, g);
     std::vector<Req*> small;
     std::vector<size_t> small_idx;
     for (size_t j = 0; j < g.size(); ++j) {
@@ -471,8 +526,8 @@ void mfg_server::enqueue_group(int si, const std::vector<Req*>& g, std::vector<i
             for (size_t j : small_idx) status[j] = s;
     }
     if (log_enabled())
-        std::fprintf(stderr, "mfg_server: slot %d mode %d group %zu%s\n", si, g.front()->r.mode, g.size(),
-                     grouped ? " grouped" : "");
+        std::fprintf(stderr, "mfg_server: slot %d mode %d group %zu held %llu%s\n", si, g.front()->r.mode, g.size(),
+                     (unsigned long long)held_bytes(), grouped ? " grouped" : "");
     for (Req* q : g)
         if (q->ws) {
             if (q->own_ws) (void)hipFreeAsync(q->ws, sl.stream);
