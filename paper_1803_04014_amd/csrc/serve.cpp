@@ -176,7 +176,7 @@ struct mfg_server {
 
 int mfg_server::init_device() {
     MFG_HIP_CHECK(hipSetDevice(cfg.device));
-    int pools = 0;  // requests without a place in an arena take stream-ordered allocations
+    int pools = 0;  // converted operands live in stream-ordered allocations
     MFG_HIP_CHECK(hipDeviceGetAttribute(&pools, hipDeviceAttributeMemoryPoolsSupported, cfg.device));
     if (!pools) return MFG_ERR_UNSUPPORTED;
     work_cap = (int64_t)cfg.max_group * kSmallTiles;
@@ -194,10 +194,10 @@ int mfg_server::init_device() {
 
 void mfg_server::release_device() {
     for (auto& sl : slots) {
+        if (sl.arena) release_arena(sl);
         if (sl.stream) (void)hipStreamSynchronize(sl.stream);
         if (sl.done) (void)hipEventDestroy(sl.done);
         if (sl.stream) (void)hipStreamDestroy(sl.stream);
-        if (sl.arena) (void)hipFree(sl.arena);
         if (sl.h_work) (void)hipHostFree(sl.h_work);
         if (sl.d_work) (void)hipFree(sl.d_work);
         if (sl.h_planes) (void)hipHostFree(sl.h_planes);
@@ -387,9 +387,13 @@ bool mfg_server::launch_ready(std::unique_lock<std::mutex>& lk) {
 }
 
 // A slot runs one group at a time and its previous group has completed, so its
-// arena is free to be used or replaced without ordering.
+// arena is free to be used or replaced.  Arenas come and go in the order of
+// their slot's stream: hipFree would hold up the scheduler, and every slot with
+// it, until the longest running GEMM ends.  The stream is idle, so waiting for
+// it costs nothing and has the pool give the memory back at once.
 void mfg_server::release_arena(Slot& sl) {
-    (void)hipFree(sl.arena);
+    (void)hipFreeAsync(sl.arena, sl.stream);
+    (void)hipStreamSynchronize(sl.stream);
     sl.arena = nullptr, sl.arena_cap = 0;
 }
 
@@ -402,7 +406,7 @@ void mfg_server::allocate_arena(Slot& sl, const std::vector<Req*>& g) {
     for (const Req* q : g) need += (size_t)q->footprint;
     if (sl.arena || need == 0) return;
     size_t want = (size_t)sl.held;
-    hipError_t e = hipMalloc((void**)&sl.arena, want);
+    hipError_t e = hipMallocAsync((void**)&sl.arena, want, sl.stream);
     if (e != hipSuccess) {
         for (Slot& o : slots)
             if (o.arena && !o.busy) {
@@ -410,7 +414,7 @@ void mfg_server::allocate_arena(Slot& sl, const std::vector<Req*>& g) {
                 o.held = 0;
             }
         want = need;
-        e = hipMalloc((void**)&sl.arena, want);
+        e = hipMallocAsync((void**)&sl.arena, want, sl.stream);
     }
     if (e == hipSuccess) {
         sl.arena_cap = want, sl.held = want;

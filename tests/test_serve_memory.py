@@ -99,3 +99,35 @@ def test_device_memory_of_a_large_request_beside_grown_slots():
     assert stats["failed"] == 0 and stats["completed"] == 29
     # (the runtime rounds allocations, and loads kernels on their first use)
     assert free0 - staged - least[0] <= budget + (96 << 20)
+
+
+@pytest.mark.gpu
+def test_growing_storage_does_not_wait_for_other_slots():
+    """Requests whose slot needs more storage each time finish beside a long
+    request on the other slot."""
+    need_gpu()
+    n = 16384
+    x, y = (torch.ones((n, n), dtype=torch.float32, device=DEV) for _ in range(2))
+    c = torch.empty_like(x)
+    # 520 x 520 x K in F16: 8, 40 and 120 MiB of planes, and tiles that find room
+    # beside the long request's
+    small = [tuple(torch.ones(d, dtype=torch.float32, device=DEV) for d in ((520, k), (k, 520), (520, 520)))
+             for k in (4096, 20480, 61440)]
+    s = mfg.Server(4 << 30, slots=2, max_group=1)
+    s.submit(*small[0], "f16")  # (kernels loaded, the first allocation made)
+    s.drain()
+    torch.cuda.synchronize()
+    long = s.submit(x, y, c, "f32")  # about 70 ms
+    ends = []
+    for a, b, out in small:
+        t = s.submit(a, b, out, "f16")
+        while True:
+            st, r = s.poll(t)
+            if st != mfg.capi.MFG_PENDING:
+                break
+        assert st == 0
+        ends.append(r["t_end_ns"])
+    s.drain()
+    st, r = s.poll(long)
+    s.close()
+    assert st == 0 and max(ends) < r["t_end_ns"]
