@@ -90,6 +90,26 @@ static int choose16(int m, int config, int64_t M, int64_t N, int64_t K, int64_t 
     return pick_config16(kind_of(m), M, N, kp, vec);
 }
 
+// Layout of the 16-bit planes a call converts FP32 operands into: K as the
+// kernel will run it, leading dimensions of A's and B's planes.
+// Workspace planes of K >= 256 take K padded with zeros to whole 64-deep
+// stages (adding zero products changes no bit of an accumulator) and rows
+// of whole 128-byte lines, so they run on the kernels for whole stages
+// (F16 2048^3: 22.3 us, 24.4 us on the variant for any K).  Below that the
+// padding would be over a quarter of the conversion's writes.  Not in the
+// fixed array, whose capacity is stated without it, nor beyond the limits
+// of one conversion launch and of the tiled kernels.
+struct Planes16 {
+    int64_t kp, ldk, ldn;
+};
+static Planes16 planes16(int64_t M, int64_t N, int64_t K, bool fixed) {
+    const int64_t k64 = up(K, 64), n64 = N >= 256 ? up(N, 64) : up(N, 8);
+    const bool pad = !fixed && K >= 256 && operand_ld_ok(k64, n64) && k64 / 8 * M < ((int64_t)1 << 31) &&
+                     cdiv(N, 8) * k64 < ((int64_t)1 << 31);
+    if (pad) return {k64, k64, n64};
+    return {K, up(K, 8), up(N, 8)};
+}
+
 // BF16_SPLIT6 runs the BF16 kernels over K' = 6 * up(K, 64); its tuned
 // entries are keyed by its own mode and the caller's K.
 static int choose_split6(int config, int64_t M, int64_t N, int64_t K, int64_t ldc, bool vec) {
@@ -289,17 +309,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             al16(A) && al16(B) && lda % 8 == 0 && ldb % 8 == 0 && buffer_ldc_ok(ldc) && operand_ld_ok(lda, ldb);
         return launch_gemm16(kind, choose16(m, config, M, N, K, K, ldc, vec), a, 1, vec, s, config < 0);
     }
-    // Workspace planes of K >= 256 take K padded with zeros to whole 64-deep
-    // stages (adding zero products changes no bit of an accumulator) and rows
-    // of whole 128-byte lines, so they run on the kernels for whole stages
-    // (F16 2048^3: 22.3 us, 24.4 us on the variant for any K).  Below that the
-    // padding would be over a quarter of the conversion's writes.  Not in the
-    // fixed array, whose capacity is stated without it, nor beyond the limits
-    // of one conversion launch and of the tiled kernels.
-    const int64_t k64 = up(K, 64), n64 = N >= 256 ? up(N, 64) : up(N, 8);
-    const bool pad = !ext && K >= 256 && operand_ld_ok(k64, n64) && k64 / 8 * M < ((int64_t)1 << 31) &&
-                     cdiv(N, 8) * k64 < ((int64_t)1 << 31);
-    const int64_t kp = pad ? k64 : K, ldk = pad ? k64 : up(K, 8), ldn = pad ? n64 : up(N, 8);
+    const auto [kp, ldk, ldn] = planes16(M, N, K, ext != nullptr);
     const int64_t pa_elems = M * ldk, pb_elems = kp * ldn;
     const size_t bytes = (size_t)(npa(m) * up(pa_elems, 128) + npb(m) * up(pb_elems, 128)) * 2;
     CallWs ws;
@@ -394,21 +404,22 @@ extern "C" int mfg_config_name(int mode, int config, char* buf, int n) {
 extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
     const int m = mode & MFG_MODE_MASK;
     if (m < 0 || m >= MFG_NUM_MODES || M < 0 || N < 0 || K < 0) return MFG_ERR_INVALID_ARG;
-    if (m == MFG_F32) {
-        const int t = tuned_lookup(m, M, N, K);
-        return t >= 0 ? t : pick_config_f32(M, N, K);
-    }
+    // as gemm_impl chooses, for contiguous aligned operands (preconverted: ld
+    // rounded up to whole 16-byte pieces)
+    const bool pre = (mode & MFG_IN_PRECONVERTED) != 0, cbuf = buffer_ldc_ok(N);
+    const int t = tuned_lookup(m, M, N, K);
+    if (m == MFG_F32) return (t >= 0 && config_f32_ok(t, N, true)) ? t : cbuf ? pick_config_f32(M, N, K) : 0;
     if (m == MFG_FP8_E4M3) {
-        const int t = tuned_lookup(m, M, N, K);
-        return (t >= 0 && t < num_configs_f8()) ? t : pick_config_f8(M, N, K, true, !(mode & MFG_IN_PRECONVERTED) || K % 128 == 0);
+        const bool vec = cbuf && up(K, 128) < kF8LdLimit;
+        return (t >= 0 && config_f8_ok(t, M, N, K, N, vec)) ? t : pick_config_f8(M, N, K, vec, !pre || K % 128 == 0);
     }
-    if (m == MFG_BF16_SPLIT6) return choose_split6(-1, M, N, K, N, true);
-    if (!(mode & MFG_IN_PRECONVERTED)) {  // FP32 operands: a tuned fused kernel where the shape allows it
-        const int k = kind_of(m), n16 = num_configs16(k), t = tuned_lookup(m, M, N, K);
-        if (t >= n16 && t < n16 + num_configs_fused(k) && K % 64 == 0 && K > 0 && N % 8 == 0 && N >= 8 && M >= 1)
-            return t;
-    }
-    return choose16(m, -1, M, N, K, K, N, true);
+    if (m == MFG_BF16_SPLIT6) return choose_split6(-1, M, N, K, N, cbuf && operand_ld_ok(6 * up(K, 64), up(N, 8)));
+    if (pre) return choose16(m, -1, M, N, K, K, N, cbuf && operand_ld_ok(up(K, 8), up(N, 8)));
+    // FP32 operands: a tuned fused kernel where the shape allows it
+    const int k = kind_of(m), n16 = num_configs16(k);
+    if (t >= n16 && t < n16 + num_configs_fused(k) && K % 64 == 0 && K > 0 && N % 8 == 0 && N >= 8 && M >= 1) return t;
+    const Planes16 p = planes16(M, N, K, false);
+    return choose16(m, -1, M, N, K, p.kp, N, cbuf && operand_ld_ok(p.ldk, p.ldn));
 }
 
 // -------------------------------------------------------------------- batched
