@@ -382,10 +382,13 @@ int mfg_error_norms(int64_t M, int64_t N, const float* C, int64_t ldc,
 
 /* ------------------------------------------------------------- autotuner
  * Time every tile configuration of `mode` on the caller's operands with HIP
- * events (`reps` timed runs after one warm-up each), keep the fastest whose
- * output is bitwise equal to configuration 0's, and record it in the tuned
- * table for the size bucket of (M, N, K).  best_config / best_ms (host) may
- * be NULL.  C is overwritten. */
+ * events (`reps` timed runs after one warm-up each), and the default choice
+ * where the operands (a ragged K, rows that are not 16-byte aligned) do not
+ * take it as an explicit configuration; keep the fastest whose output is
+ * bitwise equal to configuration 0's, and record it in the tuned table for
+ * the size bucket of (M, N, K).  A shape of the bucket that does not take the
+ * recorded configuration runs by the default choice.  best_config / best_ms
+ * (host) may be NULL.  C is overwritten. */
 int mfg_autotune(int64_t M, int64_t N, int64_t K,
                  const void* A, int64_t lda, const void* B, int64_t ldb,
                  float* C, int64_t ldc, int mode, int reps,

@@ -79,13 +79,20 @@ int convert_operands(int m, int64_t M, int64_t N, int64_t K, const float* A, int
     return st != MFG_OK ? st : mfg_convert(K, N, B, ldb, wb, ldb_c, m == MFG_F16_REFINE_A ? MFG_F16 : m, s);
 }
 
+// gemm_impl's `config`: an index of the mode's menu, the tuned table's entry or
+// else the default choice (-1), or the default choice whatever the table holds.
+constexpr int kConfigDefault = -2;
+static int tuned(int config, int m, int64_t M, int64_t N, int64_t K) {
+    return config == kConfigDefault ? -1 : tuned_lookup(m, M, N, K);
+}
+
 // The tuned table is keyed by size buckets, so its entry may name a
 // configuration that does not serve this particular shape (e.g. K % 64 != 0
 // in a bucket tuned on K % 64 == 0): then the default choice is used.
 // kp: the K the kernel will run (K, or padded).
 static int choose16(int m, int config, int64_t M, int64_t N, int64_t K, int64_t kp, int64_t ldc, bool vec) {
     if (config >= 0) return config;
-    const int t = tuned_lookup(m, M, N, K);
+    const int t = tuned(config, m, M, N, K);
     if (t >= 0 && config16_ok(kind_of(m), t, M, N, K, ldc, vec)) return t;
     return pick_config16(kind_of(m), M, N, kp, vec);
 }
@@ -115,7 +122,7 @@ static Planes16 planes16(int64_t M, int64_t N, int64_t K, bool fixed) {
 static int choose_split6(int config, int64_t M, int64_t N, int64_t K, int64_t ldc, bool vec) {
     if (config >= 0) return config;
     const int64_t kk = 6 * up(K, 64);
-    const int t = tuned_lookup(MFG_BF16_SPLIT6, M, N, K);
+    const int t = tuned(config, MFG_BF16_SPLIT6, M, N, K);
     if (t >= 0 && config16_ok(K_BF16, t, M, N, kk, ldc, vec)) return t;
     return pick_config16(K_BF16, M, N, kk, vec);
 }
@@ -143,6 +150,7 @@ static int call_ws(hipStream_t s, size_t bytes, const ExtWs* ext, CallWs& w) {
     return MFG_OK;
 }
 
+// Whether stream s is being captured.
 static bool capturing(hipStream_t s) {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
@@ -150,9 +158,10 @@ static bool capturing(hipStream_t s) {
     return true;  // (the default stream beside another stream's capture)
 }
 
+// ran: receives the index of the configuration that was launched.
 static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb,
                      float* C, int64_t ldc, float alpha, float beta, int mode, int config, hipStream_t s,
-                     const ExtWs* ext = nullptr) {
+                     const ExtWs* ext = nullptr, int* ran = nullptr) {
     int st = validate_gemm(M, N, K, A, lda, B, ldb, C, ldc, mode);
     if (st != MFG_OK) return st;
     const int m = mode & MFG_MODE_MASK;
@@ -168,9 +177,10 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         const bool vec = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0;
         int cfg = config;
         if (cfg < 0) {
-            const int t = tuned_lookup(m, M, N, K);
+            const int t = tuned(config, m, M, N, K);
             cfg = (t >= 0 && config_f32_ok(t, ldc, vec)) ? t : buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K) : 0;
         }
+        if (ran) *ran = cfg;
         return launch_gemm_f32(cfg, a, 1, vec, s, config < 0);
     }
 
@@ -181,7 +191,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         // 128-deep stages
         auto choose = [&](bool vec, bool whole) {
             if (config >= 0) return config;
-            const int t = tuned_lookup(m, M, N, K);
+            const int t = tuned(config, m, M, N, K);
             if (t >= 0 && config_f8_ok(t, M, N, K, ldc, vec)) return t;
             return pick_config_f8(M, N, K, vec, whole);
         };
@@ -203,10 +213,14 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             // workspace's address past its next growth)
             const bool bare = config < 0 && (K % 128 != 0 || cdiv(M, 128) * cdiv(N, 128) < 64);
             if (bare && ((ext && (size_t)bT > ext->cap) || k128 / 64 > 65535 || (!ext && capturing(s)))) cfg = 0;
+            if (ran) *ran = cfg;
             if (!f8_config_needs_bt(cfg)) return launch_gemm_f8(cfg, a, vec, s);
             CallWs ws;
             st = call_ws(s, (size_t)bT, ext, ws);
-            if (st == MFG_ERR_NO_MEMORY && bare) return launch_gemm_f8(0, a, vec, s);
+            if (st == MFG_ERR_NO_MEMORY && bare) {
+                if (ran) *ran = 0;
+                return launch_gemm_f8(0, a, vec, s);
+            }
             if (st != MFG_OK) return st;
             uint8_t* bt = static_cast<uint8_t*>(ws.ptr);
             if ((st = launch_transpose_b8(K, k128, N, a.B, ldb, bt, ldt, s)) != MFG_OK) return st;
@@ -228,6 +242,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         // the fixed array's capacity is stated for unpadded codes: a call whose
         // padding would not fit runs on the simple kernel
         if (config < 0 && ext && tiled_bytes > ext->cap && (K % 128 != 0 || cfg == 2)) cfg = 0;
+        if (ran) *ran = cfg;
         if (f8_config_needs_bt(cfg)) {
             CallWs ws;
             if ((st = call_ws(s, tiled_bytes, ext, ws)) != MFG_OK) return st;
@@ -274,7 +289,9 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.M = M, a.N = N, a.K = kk, a.C = C, a.ldc = ldc, a.alpha = alpha, a.beta = beta;
         a.A[0] = a0, a.B[0] = b0, a.lda = kk, a.ldb = ldn;
         const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(kk, ldn);
-        return launch_gemm16(K_BF16, choose_split6(config, M, N, K, ldc, vec), a, 1, vec, s, config < 0);
+        const int cfg = choose_split6(config, M, N, K, ldc, vec);
+        if (ran) *ran = cfg;
+        return launch_gemm16(K_BF16, cfg, a, 1, vec, s, config < 0);
     }
 
     // 16-bit modes
@@ -286,14 +303,17 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
                            alpha, beta};
         int fc = config >= n16 ? config - n16 : -1;
         if (config < 0) {
-            const int t = tuned_lookup(m, M, N, K);
+            const int t = tuned(config, m, M, N, K);
             if (t >= n16 && fused_ok(kind, t - n16, fa)) fc = t - n16;
             // allocation-free call whose planes would not fit its array: the
             // fused kernel needs none
             const int64_t planes = (npa(m) * up(M * up(K, 8), 128) + npb(m) * up(K * up(N, 8), 128)) * 2;
             if (fc < 0 && ext && planes > (int64_t)ext->cap && fused_ok(kind, 0, fa)) fc = 0;
         }
-        if (fc >= 0) return launch_gemm_fused(kind, fc, fa, s);
+        if (fc >= 0) {
+            if (ran) *ran = n16 + fc;
+            return launch_gemm_fused(kind, fc, fa, s);
+        }
     } else if (config >= n16) {
         return MFG_ERR_UNSUPPORTED;  // the fused kernels read FP32 operands
     }
@@ -307,7 +327,9 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         a.lda = lda, a.ldb = ldb;
         const bool vec =
             al16(A) && al16(B) && lda % 8 == 0 && ldb % 8 == 0 && buffer_ldc_ok(ldc) && operand_ld_ok(lda, ldb);
-        return launch_gemm16(kind, choose16(m, config, M, N, K, K, ldc, vec), a, 1, vec, s, config < 0);
+        const int cfg = choose16(m, config, M, N, K, K, ldc, vec);
+        if (ran) *ran = cfg;
+        return launch_gemm16(kind, cfg, a, 1, vec, s, config < 0);
     }
     const auto [kp, ldk, ldn] = planes16(M, N, K, ext != nullptr);
     const int64_t pa_elems = M * ldk, pb_elems = kp * ldn;
@@ -327,6 +349,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     const bool vec = buffer_ldc_ok(ldc) && operand_ld_ok(ldk, ldn);  // workspace planes: aligned, ld a multiple of 8
     const int cfg = choose16(m, config, M, N, K, kp, ldc, vec);
     if (config >= 0 && !config16_ok(kind, cfg, M, N, K, ldc, vec)) return MFG_ERR_UNSUPPORTED;  // judged on the caller's K
+    if (ran) *ran = cfg;
     return launch_gemm16(kind, cfg, a, 1, vec, s, config < 0);
 }
 
@@ -1066,6 +1089,7 @@ static int autotune_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t
     const int m = mode & MFG_MODE_MASK;
     const int ncfg = mfg_num_configs(m);
     if (ncfg <= 0) return MFG_ERR_INVALID_ARG;
+    std::vector<char> timed((size_t)ncfg, 0);
     float* ref = nullptr;
     unsigned long long* cnt = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1093,15 +1117,22 @@ static int autotune_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t
                          s) != hipSuccess)
         st = MFG_ERR_HIP;
     bms = 3.4e38f;
-    for (int c = 0; st == MFG_OK && c < ncfg; ++c) {
-        int r = gemm_impl(M, N, K, A, lda, B, ldb, C, ldc, 1.f, 0.f, mode, c, s);  // warm-up
-        if (r == MFG_ERR_UNSUPPORTED) continue;
+    // Every configuration the shape takes explicitly, then the default choice
+    // where it is none of them: it serves any K and row alignment, and an entry
+    // that does not serve a shape leaves that shape to it.
+    for (int i = 0; st == MFG_OK && i <= ncfg; ++i) {
+        const int c = i < ncfg ? i : kConfigDefault;
+        int index = c;
+        int r = gemm_impl(M, N, K, A, lda, B, ldb, C, ldc, 1.f, 0.f, mode, c, s, nullptr, &index);  // warm-up
+        if (r == MFG_ERR_UNSUPPORTED && i < ncfg) continue;
         if (r != MFG_OK) {
             st = r;
             break;
         }
+        if (index < 0 || timed[(size_t)index]) continue;
+        timed[(size_t)index] = 1;
         float total = 0.f;
-        for (int i = 0; i < reps && st == MFG_OK; ++i) {
+        for (int rep = 0; rep < reps && st == MFG_OK; ++rep) {
             if (hipEventRecord(e0, s) != hipSuccess) st = MFG_ERR_HIP;
             r = gemm_impl(M, N, K, A, lda, B, ldb, C, ldc, 1.f, 0.f, mode, c, s);
             if (r != MFG_OK) st = r;
@@ -1119,7 +1150,7 @@ static int autotune_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t
             break;
         }
         const float avg = total / reps;
-        if (bad == 0 && avg < bms) bms = avg, best = c;
+        if (bad == 0 && avg < bms) bms = avg, best = index;
     }
     cleanup();
     if (st != MFG_OK) return st;
