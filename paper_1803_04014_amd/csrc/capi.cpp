@@ -187,13 +187,11 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
     if (m == MFG_FP8_E4M3) {
         GemmF8Args a{};
         a.M = M, a.N = N, a.K = K, a.C = C, a.ldc = ldc, a.alpha = alpha, a.beta = beta;
-        // whole: the kernel will find A's and Bt's codes zero-filled to whole
-        // 128-deep stages
-        auto choose = [&](bool vec, bool whole) {
+        auto choose = [&](bool vec) {
             if (config >= 0) return config;
             const int t = tuned(config, m, M, N, K);
             if (t >= 0 && config_f8_ok(t, M, N, K, ldc, vec)) return t;
-            return pick_config_f8(M, N, K, vec, whole);
+            return pick_config_f8(M, N, K, vec, pre);
         };
         const int64_t k128 = up(K, 128), ldt = k128;         // ld of the transposed B codes
         const int64_t bT = up(N * ldt, 256);
@@ -203,7 +201,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
             a.sa = reinterpret_cast<const float*>(a.A + mfg_fp8_scale_offset(M, lda));
             a.sb = reinterpret_cast<const float*>(a.B + mfg_fp8_scale_offset(K, ldb));
             const bool vec = al16(A) && lda % 16 == 0 && buffer_ldc_ok(ldc) && lda < kF8LdLimit && ldt < kF8LdLimit;
-            int cfg = choose(vec, K % 128 == 0);
+            int cfg = choose(vec);
             if (cfg < 0 || cfg >= num_configs_f8()) return MFG_ERR_INVALID_ARG;
             if (f8_config_needs_bt(cfg) && (!vec || (config >= 0 && K % 128 != 0))) return MFG_ERR_UNSUPPORTED;
             // Ragged K and grids under 64 tiles of 128 x 128 are served whatever the
@@ -233,7 +231,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         // tuned configurations are judged on the caller's K.
         const float *Af = static_cast<const float*>(A), *Bf = static_cast<const float*>(B);
         const bool vec8 = buffer_ldc_ok(ldc) && k128 < kF8LdLimit;
-        int cfg = choose(vec8, true);
+        int cfg = choose(vec8);
         if (cfg < 0 || cfg >= num_configs_f8()) return MFG_ERR_INVALID_ARG;
         if (f8_config_needs_bt(cfg) && config >= 0 && K % 128 != 0) return MFG_ERR_UNSUPPORTED;
         const int64_t bA = mfg_fp8_scale_offset(M, k128) + 4 * cdiv(M, MFG_FP8_TILE) * cdiv(K, MFG_FP8_TILE);
@@ -434,7 +432,7 @@ extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
     if (m == MFG_F32) return (t >= 0 && config_f32_ok(t, N, true)) ? t : cbuf ? pick_config_f32(M, N, K) : 0;
     if (m == MFG_FP8_E4M3) {
         const bool vec = cbuf && up(K, 128) < kF8LdLimit;
-        return (t >= 0 && config_f8_ok(t, M, N, K, N, vec)) ? t : pick_config_f8(M, N, K, vec, !pre || K % 128 == 0);
+        return (t >= 0 && config_f8_ok(t, M, N, K, N, vec)) ? t : pick_config_f8(M, N, K, vec, pre);
     }
     if (m == MFG_BF16_SPLIT6) return choose_split6(-1, M, N, K, N, cbuf && operand_ld_ok(6 * up(K, 64), up(N, 8)));
     if (pre) return choose16(m, -1, M, N, K, K, N, cbuf && operand_ld_ok(up(K, 8), up(N, 8)));

@@ -118,9 +118,10 @@ int launch_gemm_f32(int cfg, const GemmF32Args& a, int64_t batch, bool vec_ok, h
 
 int num_configs_f8();
 const char* config_f8_name(int cfg);
-// vec_ok: 16-byte aligned rows of A's codes; whole: Bt and A zero-filled to
-// whole 128-deep stages (a.K a multiple of 128).
-int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool whole);
+// vec_ok: 16-byte aligned rows of A's codes; codes: the operands are the
+// caller's codes (B to be transposed, K as it is) and not quantised into the
+// workspace (B straight into Bt, both zero-filled to whole 128-deep stages).
+int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool codes);
 // The ring kernels' tile: 0 64 x 64, 1 64 x 128, 2 128 x 128.
 int pick_ring_f8(int64_t M, int64_t N, int64_t K);
 // any_k: cfg came from pick_config_f8; an explicit or tuned tiled cfg needs

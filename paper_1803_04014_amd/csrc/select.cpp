@@ -6,6 +6,8 @@
 // gemm_f8.hip and gemm_f32.hip.
 #include <cstdint>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace mfg {
@@ -112,9 +114,30 @@ static const Cost16& pick8(int64_t M, int64_t N, int64_t K, bool ring_only) {
     return least_cost(kCostF8, (int)(sizeof(kCostF8) / sizeof(Cost16)), M, N, cdiv(K, 128), 1, 1.0, ring_only);
 }
 
-int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool whole) {
-    if (!vec_ok || M < 1 || N < 1 || K < 1) return 0;
-    return pick8(M, N, K, !whole).cfg;
+// B as row-major codes: the tiled kernels need a launch that transposes it
+// first, the simple kernel reads it as it is, and is the faster one for a short
+// K.  us of a call, the GPU kept busy by the ones before: the simple kernel's
+// is its 64-deep steps' latency (a step of whole 32-byte pieces of A is half as
+// long) or, with many 32 x 32 blocks, their sum; the other two launches take
+// 6.8 at least.  64 x 64 x 64 3.8 us against 6.6, 896 x 128 x 64 3.8 and 6.8,
+// 64 x 160 x 100 5.9 and 7.5; but 64 x 128 x 256 8.3 and 6.6, 2336 x 5664 x 128
+// 28 and 17 (of 250 random shapes up to K = 420 the choice costs 0.2% on
+// average; the tiled kernels alone 25%).
+static bool simple_f8(int64_t M, int64_t N, int64_t K) {
+    const double steps = (double)cdiv(K, 64), blocks = (double)(cdiv(M, 32) * cdiv(N, 32));
+    const double tiles = (double)(cdiv(M, 64) * cdiv(N, 64));
+    double simple, tiled;
+    if (M % 32 == 0 && K % 64 == 0) simple = std::max(2.35 + 1.45 * steps, 3.3 + blocks * (0.6 + 0.7 * steps) * 1e-3);
+    else if (M % 32 == 0 && K % 32 == 0) simple = std::max(3.3 + 1.55 * steps, 3.5 + blocks * (0.5 + 1.1 * steps) * 1e-3);
+    else simple = std::max(2.4 + 2.5 * steps, 3.5 + blocks * (0.9 + 1.2 * steps) * 1e-3);
+    if (K % 128 == 0) tiled = std::max(6.8, 5.0 + tiles * 3.5e-3);
+    else tiled = (N <= 32 ? 6.8 : 7.5) + tiles * 3.4e-3;
+    return simple <= tiled;
+}
+
+int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool codes) {
+    if (!vec_ok || M < 1 || N < 1 || K < 1 || (codes && simple_f8(M, N, K))) return 0;
+    return pick8(M, N, K, codes && K % 128 != 0).cfg;
 }
 
 int pick_ring_f8(int64_t M, int64_t N, int64_t K) { return pick8(M, N, K, true).variant; }

@@ -1,0 +1,39 @@
+"""The default configuration on both sides of the rules that choose between a
+kernel without LDS for small problems (configuration 0) and the tiled ones:
+shapes timed on an MI355X, the faster one expected.  Host code alone: no GPU."""
+import pytest
+
+import paper_1803_04014_amd as mfg
+from paper_1803_04014_amd import capi
+
+
+@pytest.fixture(autouse=True)
+def _no_table():
+    mfg.lib().mfg_tune_clear()
+
+
+def _simple(mode, M, N, K, pre=False):
+    return mfg.lib().mfg_tune_lookup(M, N, K, mfg.mode_of(mode) | (capi.MFG_IN_PRECONVERTED if pre else 0)) == 0
+
+
+# us of a call: configuration 0, the tiled kernel and the transpose it needs
+@pytest.mark.parametrize("M,N,K,simple", [
+    (64, 64, 64, True),        # 3.8, 6.6
+    (896, 128, 64, True),      # 3.8, 6.8
+    (64, 192, 64, True),       # 3.8, 6.7
+    (3088, 365, 8, True),      # 6.4, 8.8
+    (39, 294, 35, True),       # 5.2, 8.7
+    (64, 160, 100, True),      # 5.9, 7.5
+    (448, 320, 128, True),     # 5.5, 6.7
+    (160, 192, 192, True),     # 6.9, 7.4
+    (2353, 3090, 22, False),   # 20.3, 14.4
+    (5088, 2304, 32, False),   # 22.9, 17.6
+    (2336, 5664, 128, False),  # 28.4, 16.5
+    (48, 25, 139, False),      # 9.8, 6.8
+    (261, 1095, 221, False),   # 13.0, 8.4
+    (64, 128, 256, False),     # 8.3, 6.6
+    (64, 64, 416, False),      # 13.6, 8.6
+])
+def test_fp8_codes(M, N, K, simple):
+    assert _simple("fp8", M, N, K, pre=True) == simple
+    assert not _simple("fp8", M, N, K)  # quantised by the call: B is written transposed
