@@ -178,7 +178,7 @@ static int gemm_impl(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda
         int cfg = config;
         if (cfg < 0) {
             const int t = tuned(config, m, M, N, K);
-            cfg = (t >= 0 && config_f32_ok(t, ldc, vec)) ? t : buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K) : 0;
+            cfg = (t >= 0 && config_f32_ok(t, ldc, vec)) ? t : buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K, vec && K % 4 == 0) : 0;
         }
         if (ran) *ran = cfg;
         return launch_gemm_f32(cfg, a, 1, vec, s, config < 0);
@@ -425,11 +425,14 @@ extern "C" int mfg_config_name(int mode, int config, char* buf, int n) {
 extern "C" int mfg_tune_lookup(int64_t M, int64_t N, int64_t K, int mode) {
     const int m = mode & MFG_MODE_MASK;
     if (m < 0 || m >= MFG_NUM_MODES || M < 0 || N < 0 || K < 0) return MFG_ERR_INVALID_ARG;
-    // as gemm_impl chooses, for contiguous aligned operands (preconverted: ld
-    // rounded up to whole 16-byte pieces)
+    // as gemm_impl chooses, for contiguous operands (preconverted: ld rounded up
+    // to whole 16-byte pieces)
     const bool pre = (mode & MFG_IN_PRECONVERTED) != 0, cbuf = buffer_ldc_ok(N);
     const int t = tuned_lookup(m, M, N, K);
-    if (m == MFG_F32) return (t >= 0 && config_f32_ok(t, N, true)) ? t : cbuf ? pick_config_f32(M, N, K) : 0;
+    if (m == MFG_F32) {
+        const bool vec = K % 4 == 0 && N % 4 == 0;
+        return (t >= 0 && config_f32_ok(t, N, vec)) ? t : cbuf ? pick_config_f32(M, N, K, vec) : 0;
+    }
     if (m == MFG_FP8_E4M3) {
         const bool vec = cbuf && up(K, 128) < kF8LdLimit;
         return (t >= 0 && config_f8_ok(t, M, N, K, N, vec)) ? t : pick_config_f8(M, N, K, vec, pre);
@@ -467,7 +470,7 @@ static int batched_impl(int64_t count, int64_t M, int64_t N, int64_t K, const vo
         a.lda = lda, a.ldb = ldb, a.sA = strideA, a.sB = strideB, a.sC = strideC;
         const bool vec = al16(A) && al16(B) && lda % 4 == 0 && ldb % 4 == 0 && strideA % 4 == 0 && strideB % 4 == 0 &&
                          buffer_ldc_ok(ldc);
-        const int cfg = buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K, count) : 0;
+        const int cfg = buffer_ldc_ok(ldc) ? pick_config_f32(M, N, K, vec && K % 4 == 0, count) : 0;
         for (int64_t b0 = 0; b0 < count; b0 += 65535) {
             a.A = static_cast<const float*>(A) + b0 * strideA;
             a.B = static_cast<const float*>(B) + b0 * strideB;

@@ -109,7 +109,8 @@ bool config_f8_ok(int cfg, int64_t M, int64_t N, int64_t K, int64_t ldc, bool ve
 
 int num_configs_f32();
 const char* config_f32_name(int cfg);
-int pick_config_f32(int64_t M, int64_t N, int64_t K, int64_t batch = 1);
+// vec: 16-byte aligned rows and K % 4 == 0.
+int pick_config_f32(int64_t M, int64_t N, int64_t K, bool vec, int64_t batch = 1);
 // The tile of the ring kernels: 0 64 x 64, 1 64 x 128 (vec only), 2 128 x 128.
 int pick_ring_f32(int64_t M, int64_t N, int64_t K, int64_t batch, bool vec);
 // any_rows: cfg came from pick_config_f32, whose choices serve any row

@@ -142,18 +142,28 @@ int pick_config_f8(int64_t M, int64_t N, int64_t K, bool vec_ok, bool codes) {
 
 int pick_ring_f8(int64_t M, int64_t N, int64_t K) { return pick8(M, N, K, true).variant; }
 
-// FP32: the simple kernel (one wavefront per 32 x 32 block, no LDS) for a
-// block or less of short K, or a batch of such (65536-sized batches of 16^3:
-// 33 us for 40000 against 78 us on a ring of 32 x 32 tiles), else the ring.
-int pick_config_f32(int64_t M, int64_t N, int64_t K, int64_t batch) {
-    if (M <= 32 && N <= 32) return K <= 32 || batch > 1 ? 0 : 1;
-    // Many small problems that leave half of the ring's 64 x 64 tile empty, or
-    // are less than half a stage deep: 8397 of 17 x 33 x 41 43 us simple, 77 ring,
-    // of 9 x 60 x 41 41 and 72, of 40 x 40 x 8 29 and 37; but of 33 x 64 x 20 45 and
-    // 37, of 33 x 33 x 33 77 and 73, of 33 x 17 x 64 74 both; 64 of 17 x 33 x 41 10.4
-    // and 5.9, 2000 13 and 20.
-    if (batch >= 512 && K <= 64 && (M <= 32 || N <= 32 || K <= 12)) return 0;
-    return 1;
+// FP32: the simple kernel (one wavefront per 32 x 32 block, no LDS) where K is
+// short, or where many thin problems would leave most of the ring's 64 x 64
+// tiles empty; else the ring.  Both estimated in us as the latency of one block
+// or tile, or their sum once the chip is full: a block takes less the emptier
+// it is (fewer of its loads are in range) and where it shares rows with others
+// of its problem, a tile of the ring does not.  vec: the ring loads 16-byte
+// pieces (aligned rows, K % 4 == 0).
+// Fitted on 999 shapes where both were timed (batches of thin ones, single ones
+// up to K = 200): 0.3% slower on average than the better of the two, where the
+// ring alone is 15%.  1055 x 18 x 4 2.7 us simple, 4.2 ring, 543 x 17 x 24 3.5
+// and 4.2, 411 of 8 x 376 x 16 7.2 and 13.3, 1130 of 14 x 591 x 96 110 and 146;
+// but 3241 x 2652 x 28 17 and 14, 34 of 360 x 32 x 152 9.7 and 6.3, 1903 of
+// 126 x 39 x 209 279 and 98.
+int pick_config_f32(int64_t M, int64_t N, int64_t K, bool vec, int64_t batch) {
+    const double mb = (double)cdiv(M, 32), nb = (double)cdiv(N, 32), fm = (double)M / (32.0 * mb), fn = (double)N / (32.0 * nb);
+    const double blocks = mb * nb * (double)batch, tiles = (double)(cdiv(M, 64) * cdiv(N, 64)) * (double)batch;
+    const double k8 = (double)(cdiv(K, 8) * 8), k32 = (double)(cdiv(K, 32) * 32);
+    const double per_k = (vec ? 0.0171 + 0.0252 * fm + 0.0193 * fn : 0.0270 + 0.0313 * fm + 0.0067 * fn) * (batch == 1 ? 0.71 : 1.0);
+    const double simple = std::max(1.83 + (vec ? 0.060 : 0.053) * k8, 2.0 + blocks * per_k * k8 * 1e-3);
+    const double latency = (vec ? 2.93 + 0.0207 * k32 : 3.43 + 0.0235 * k32) * (tiles > 256.0 ? 1.4 : 1.0);
+    const double per_tile = (K <= 64 ? 2.9 : 5.8) + (vec ? 0.0603 : 0.0714) * k32;
+    return simple <= std::max(latency, 2.0 + tiles * per_tile * 1e-3) ? 0 : 1;
 }
 
 // The ring tile with the least estimated time: a start-up, then per round of

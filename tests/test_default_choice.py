@@ -37,3 +37,25 @@ def _simple(mode, M, N, K, pre=False):
 def test_fp8_codes(M, N, K, simple):
     assert _simple("fp8", M, N, K, pre=True) == simple
     assert not _simple("fp8", M, N, K)  # quantised by the call: B is written transposed
+
+
+# us of a call: configuration 0, the ring kernel
+@pytest.mark.parametrize("M,N,K,simple", [
+    (1055, 18, 4, True),      # 2.7, 4.2
+    (2641, 56, 5, True),      # 2.7, 4.3
+    (96, 2240, 8, True),      # 2.5, 3.6
+    (386, 1918, 8, True),     # 3.4, 4.6
+    (72, 24, 16, True),       # 2.7, 3.3
+    (1825, 1793, 17, True),   # 8.1, 9.4
+    (543, 17, 24, True),      # 3.5, 4.2
+    (7, 1112, 38, True),      # 4.5, 5.1
+    (696, 18, 36, True),      # 4.5, 5.2
+    (8, 72, 56, False),       # 4.7, 3.8
+    (3241, 2652, 28, False),  # 17.0, 13.6
+    (34, 10, 64, False),      # 5.4, 4.8
+    (40, 176, 112, False),    # 7.8, 5.3
+    (256, 256, 256, False),   # 15, 7.8
+    (1000, 1000, 1000, False),
+])
+def test_f32(M, N, K, simple):
+    assert _simple("f32", M, N, K) == simple
