@@ -91,9 +91,46 @@ static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t b
     return least_cost(c, n, M, N, cdiv(K, 64), batch, K % 64 != 0 ? 1.2 : 1.0, ring_only);
 }
 
-// Index 0, the simple kernel, where rows are not 16-byte aligned.
+// Whether the simple kernel (one wavefront per 32 x 32 block, no LDS) beats the
+// ring kernels: a short K, or many thin problems that would leave most of the
+// ring's tiles empty.  As in pick_config_f32, both are estimated in us as the
+// latency of one block or tile, or their sum (ns each) once the chip is full.
+// Fitted per kind on shapes where both were timed (410 F16, 180 to 208 each of
+// the others: batches of thin problems, single ones up to K = 400): 0.2% to
+// 0.9% slower on average than the better of the two, the ring alone 9% to 19%.
+// F16 136 x 232 x 8 2.6 us simple, 3.0 ring, 4110 of 80 x 16 x 16 9.5 and 22,
+// 848 of 328 x 8 x 80 18 and 21; but 304 x 2040 x 24 3.4 and 3.3, 234 of
+// 26 x 368 x 80 9.0 and 8.2, 74 of 16 x 136 x 64 3.9 and 3.2.
+struct SimpleOrRing {
+    double start, per_k;           // simple: latency and its part per K (of 16)
+    double block, k, km, kn;       // a block, and per K by how full its rows and columns are
+    double shared;                 // factor where blocks of one problem share rows
+    double ring_start, ring_stage; // ring: latency and its part per 64-deep stage
+    double second;                 // added from two tiles per CU on
+    double tile, stage;            // a tile, and its part per stage
+};
+static bool simple16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch) {
+    static const SimpleOrRing plain{2.12, 0.0224, 0.418, 0.0122, 0.0119, 0.0138, 0.89, 2.61, 0.273, 0.51, 1.84, 1.78};
+    static const SimpleOrRing refine_a{2.58, 0.025, 0.421, 0.0116, 0.0142, 0.0137, 0.64, 3.69, 0.075, 1.59, 2.59, 1.69};
+    static const SimpleOrRing split3{2.43, 0.0395, 0.391, 0.0246, 0.0130, 0.0163, 1.0, 3.36, 0.371, 1.21, 3.92, 2.46};
+    static const SimpleOrRing split4{2.62, 0.0385, 0.385, 0.0232, 0.0188, 0.0153, 0.88, 3.42, 0.46, 2.3, 2.84, 3.2};
+    const SimpleOrRing& p = kind == K_F16 || kind == K_BF16 ? plain
+                            : kind == K_REFINE_A            ? refine_a
+                            : kind == K_SPLIT4              ? split4
+                                                            : split3;
+    const double mb = (double)cdiv(M, 32), nb = (double)cdiv(N, 32), fm = (double)M / (32.0 * mb), fn = (double)N / (32.0 * nb);
+    const double blocks = mb * nb * (double)batch, tiles = (double)(cdiv(M, 64) * cdiv(N, 64)) * (double)batch;
+    const double k16 = (double)(cdiv(K, 16) * 16), stages = (double)cdiv(K, 64);
+    const double per_block = (p.block + k16 * (p.k + p.km * fm + p.kn * fn)) * (batch == 1 ? p.shared : 1.0);
+    const double latency = p.ring_start + p.ring_stage * stages + (tiles > 256.0 ? p.second : 0.0);
+    return std::max(p.start + p.per_k * k16, 1.7 + blocks * per_block * 1e-3) <=
+           std::max(latency, 1.7 + tiles * (p.tile + p.stage * stages) * 1e-3);
+}
+
+// Index 0, the simple kernel, also where rows are not 16-byte aligned.
 int pick_config16(int kind, int64_t M, int64_t N, int64_t K, bool vec_ok, int64_t batch) {
-    return vec_ok ? pick16(kind, M, N, K, batch, false).cfg : 0;
+    if (!vec_ok || simple16(kind, M, N, K, batch)) return 0;
+    return pick16(kind, M, N, K, batch, false).cfg;
 }
 
 int pick_ring16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch) {

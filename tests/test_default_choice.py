@@ -59,3 +59,26 @@ def test_fp8_codes(M, N, K, simple):
 ])
 def test_f32(M, N, K, simple):
     assert _simple("f32", M, N, K) == simple
+
+
+# us of a call on preconverted operands: configuration 0, the ring kernel
+@pytest.mark.parametrize("mode,M,N,K,simple", [
+    ("f16", 136, 232, 8, True),        # 2.6, 3.0
+    ("bf16", 480, 32, 16, True),       # 2.3, 3.0
+    ("f16", 1936, 704, 16, True),      # 3.5, 4.2
+    ("f16", 309, 5, 21, True),         # 2.8, 3.2
+    ("f16", 16, 728, 32, True),        # 2.9, 3.1
+    ("f16", 8, 112, 40, False),        # 3.2, 2.9
+    ("f16", 16, 136, 64, False),       # 3.7, 3.0
+    ("f16", 512, 512, 512, False),
+    ("refine_a", 1040, 16, 16, True),  # 2.7, 3.5
+    ("refine_a", 401, 281, 24, True),  # 3.2, 3.5
+    ("split3", 1488, 80, 8, True),     # 3.1, 3.7
+    ("split3", 176, 2192, 16, True),   # 3.2, 3.8
+    ("split3", 128, 128, 64, False),
+    ("bf16_split3", 24, 472, 8, True),
+    ("split4", 752, 1248, 16, True),   # 3.6, 4.3
+    ("split4", 256, 256, 256, False),
+])
+def test_16_bit(mode, M, N, K, simple):
+    assert _simple(mode, M, N, K, pre=True) == simple
