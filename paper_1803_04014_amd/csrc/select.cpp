@@ -4,91 +4,125 @@
 // apart from the kernels so that the policy can change without touching
 // them.  Configuration indices refer to the menus in gemm16.hip,
 // gemm_f8.hip and gemm_f32.hip.
-#include <cstdint>
-
 #include <algorithm>
+#include <cmath>
+#include <cstdint>
 
 #include "internal.h"
 
 namespace mfg {
 
-// The default of the 16-bit kinds is the candidate with the least estimated
-// time: `start` (launch, prologue, one tile's epilogue latency), then per
-// tile its part of C at the CU's share of HBM and its 64-deep K stages.  A
-// stage costs `lat` us on a workgroup with an otherwise idle chip (latency),
-// `full` us per tile when every CU is busy (bandwidth and clock).  Kernels
-// that put one workgroup on a CU run ceil(tiles / 256) rounds, with the stage
-// between lat and full as the chip fills; the ring kernels share a CU,
-// whose n tiles take n full stages but at least one latency.  Figures
-// measured on MI355X (random operands): start at 64^3, lat at
-// 128 x 128 x 4096, full at 4096^3.  What the choice replaces (the 64 x 64
-// tiled kernel served every K % 64 != 0 and every small problem): SPLIT3
-// 777 x 1234 x 1999 128 -> 30 us, 4000 x 4000 x 4001 1472 -> 375 us, F16
-// 32 x 4096 x 4096 53 -> 18 us, 3000^3 212 -> 71 us, 1024^3 15 -> 7.6 us.
-struct Cost16 {
-    int cfg, variant;  // menu index; of the ring kernels also launch_ring's variant
+// The default of the 16-bit kinds and of FP8 is the candidate with the least
+// estimated time.  A kernel that puts one workgroup on a CU runs its tiles in
+// rounds of 256: `start` once, per round the tile's part of C at the CU's share
+// of HBM and its K stages, and `tile` between rounds (prologue and epilogue).
+// A stage of one round takes `lat`, the latency of its loads, and up to `grow`
+// more as the chip fills; of further rounds `full`, bandwidth and clock, of a
+// last one that fills part of the chip the most of the way back to the former.  The
+// ring kernels share a CU: its tiles take their parts of C, `tile` and `full`
+// stages one after the other, but no less than one latency.  Where K is not a
+// multiple of 64 a stage takes `rag` and `rag_full` times that: the pipelined
+// kernels choose an address for every load, and rows are not whole lines.
+// us, fitted per kind on 200 to 660 shapes with every candidate timed (64 to
+// 16384 x 64 to 280000 x 64 to 16000, random operands): 0.0% to 0.3% slower on
+// average than the best candidate, 0.1% to 0.9% where K % 64 != 0, FP8 0.7%.  A
+// first fit, whose latencies did not grow with the load and whose rounds cost no
+// more than their stages, lost 0.2% to 2.1% and 0.8% to 3.7% (BF16 1792 x 832 x
+// 10368 66 us on the ring, 60 on 128 x 128; F16 2752 x 42432 x 128 158 on 128 x
+// 128, 123 on 256 x 256; SPLIT4 12480 x 832 x 448 48.9 on 128 x 128, 44.4 on the
+// ring; FP8 1472 x 4096 x 2304 1.16 times 256 x 128).  What the choice replaced (a
+// 64 x 64 tiled kernel served every K % 64 != 0 and every small problem): SPLIT3
+// 777 x 1234 x 1999 128 -> 30 us, 4000 x 4000 x 4001 1472 -> 375, F16 32 x 4096
+// x 4096 53 -> 18, 3000^3 212 -> 71, 1024^3 15 -> 7.6.
+struct Cost {
+    int cfg, variant;  // menu index; of the ring kernels also their variant
     int bm, bn;
     bool shared;       // several workgroups per CU
-    float start, lat, full;  // us; us per 64-deep stage
+    float start, lat, grow, full, tile, rag, rag_full;
 };
-static const Cost16 kCostPlain[] = {
-    {6, 0, 64, 64, true, 2.6f, 0.27f, 0.19f},       // ring 64 x 64
-    {6, 1, 64, 128, true, 2.9f, 0.38f, 0.32f},      // ring 64 x 128
-    {28, 0, 128, 128, false, 4.7f, 0.42f, 0.50f},   // q128x128k64s3w2x2g8
-    {30, 0, 256, 128, false, 6.9f, 0.68f, 0.83f},   // q256x128k64s3w2x2g8e
-    {29, 0, 256, 256, false, 10.0f, 1.20f, 1.44f},  // q256x256k64s2w2x2g8e
+static const Cost kCostPlain[] = {
+    {6, 0, 64, 64, true, 2.91f, 0.235f, 0.033f, 0.182f, 0.057f, 1.00f, 1.20f},     // ring 64 x 64
+    {6, 1, 64, 128, true, 3.27f, 0.370f, 0.062f, 0.298f, 0.035f, 0.95f, 1.08f},    // ring 64 x 128
+    {28, 0, 128, 128, false, 4.37f, 0.326f, 0.137f, 0.485f, 1.26f, 1.35f, 1.06f},  // q128x128k64s3w2x2g8
+    {30, 0, 256, 128, false, 5.75f, 0.589f, 0.178f, 0.768f, 1.16f, 1.20f, 1.09f},  // q256x128k64s3w2x2g8e
+    {29, 0, 256, 256, false, 6.79f, 1.060f, 0.383f, 1.260f, 1.61f, 1.13f, 1.04f},  // q256x256k64s2w2x2g8e
 };
-static const Cost16 kCostRefineA[] = {
-    {3, 1, 32, 64, true, 2.9f, 0.36f, 0.20f},
-    {3, 0, 64, 64, true, 2.9f, 0.37f, 0.32f},
-    {7, 0, 128, 128, false, 5.0f, 0.70f, 0.96f},
-    {9, 0, 192, 128, false, 6.4f, 0.93f, 1.26f},
+static const Cost kCostRefineA[] = {
+    {3, 0, 64, 64, true, 2.76f, 0.358f, 0.018f, 0.282f, 0.024f, 1.08f, 1.01f},
+    {3, 1, 32, 64, true, 2.79f, 0.316f, 0.022f, 0.187f, 0.029f, 1.08f, 1.22f},
+    {7, 0, 128, 128, false, 3.94f, 0.697f, 0.160f, 0.962f, 0.70f, 1.02f, 1.00f},
+    {9, 0, 192, 128, false, 5.42f, 0.816f, 0.283f, 1.290f, 2.24f, 1.08f, 1.05f},
 };
-static const Cost16 kCostSplit3[] = {
-    {3, 1, 32, 64, true, 2.9f, 0.45f, 0.30f},
-    {3, 0, 64, 64, true, 2.9f, 0.48f, 0.46f},
-    {7, 0, 128, 128, false, 5.0f, 0.95f, 1.30f},
-    {9, 0, 192, 128, false, 6.4f, 1.28f, 1.68f},
+static const Cost kCostSplit3[] = {
+    {3, 0, 64, 64, true, 3.04f, 0.444f, 0.011f, 0.425f, 0.035f, 1.08f, 1.10f},
+    {3, 1, 32, 64, true, 2.86f, 0.411f, 0.020f, 0.297f, 0.254f, 1.08f, 1.08f},
+    {7, 0, 128, 128, false, 4.38f, 0.898f, 0.359f, 1.140f, 1.77f, 1.06f, 1.11f},
+    {9, 0, 192, 128, false, 5.77f, 1.130f, 0.454f, 1.540f, 2.98f, 1.08f, 1.05f},
 };
-static const Cost16 kCostSplit4[] = {
-    {2, 1, 32, 64, true, 2.9f, 0.51f, 0.33f},
-    {2, 0, 64, 64, true, 2.9f, 0.53f, 0.53f},
-    {5, 0, 128, 128, false, 5.0f, 1.12f, 1.64f},
+static const Cost kCostSplit4[] = {
+    {2, 0, 64, 64, true, 2.98f, 0.523f, 0.025f, 0.485f, 0.035f, 1.05f, 1.06f},
+    {2, 1, 32, 64, true, 2.65f, 0.475f, 0.023f, 0.331f, 0.469f, 1.06f, 1.15f},
+    {5, 0, 128, 128, false, 4.30f, 0.965f, 0.455f, 1.300f, 2.41f, 1.17f, 1.15f},
 };
 
-// stages: K stages; ring_cost: factor on the ring kernels' full stages.
-static double cost16(const Cost16& c, int64_t M, int64_t N, int64_t stages, int64_t batch, double ring_cost) {
+// What a problem adds to the candidates' figures: factors on the ring kernels'
+// full stages and on their part of C, and whether K is whole stages.
+struct ProblemCost {
+    double stage = 1.0, c = 1.0;
+    bool ragged = false;
+};
+
+static double cost_of(const Cost& c, int64_t M, int64_t N, int64_t stages, int64_t batch, const ProblemCost& add) {
     constexpr double kCus = 256.0, kCBytesPerUs = 20000.0;  // per CU: a 256th of 5.1 TB/s
-    const double tiles = (double)cdiv(M, c.bm) * (double)cdiv(N, c.bn) * (double)batch;
-    const double load = tiles < kCus ? tiles / kCus : 1.0;
-    const double n = tiles <= kCus ? 1.0 : (double)(int64_t)((tiles + kCus - 1.0) / kCus);
-    const double ctime = c.bm * c.bn * 4.0 / kCBytesPerUs * load, full = c.full * ring_cost;
-    double stage = c.lat + (c.full - c.lat) * load;
-    if (c.shared) stage = (n * full > c.lat ? n * full : c.lat) / n;
-    return c.start + n * (ctime + (double)stages * stage);
+    const double rounds = (double)cdiv(M, c.bm) * (double)cdiv(N, c.bn) * (double)batch / kCus;
+    const double load = rounds < 1.0 ? rounds : 1.0, ctime = c.bm * c.bn * 4.0 / kCBytesPerUs;
+    const double first = (c.lat + c.grow * load * load) * (add.ragged ? c.rag : 1.0), k = (double)stages;
+    const double each = c.full * (add.ragged ? c.rag_full : 1.0);
+    // rounds that are run (a fraction of many: their ends drift apart)
+    const double n = rounds <= 1.0 ? 1.0 : rounds <= 4.0 ? std::ceil(rounds) : rounds + 0.5;
+    if (c.shared) {
+        const double full = std::ceil(rounds) * each * add.stage;
+        return c.start + (ctime + c.tile) * rounds * add.c + k * (n == 1.0 || full < first ? first : full);
+    }
+    double sum = n * each;
+    if (n == 1.0) sum = first;
+    else if (rounds < n) {
+        const double part = rounds - (n - 1.0), last = (c.lat + c.grow * part * part) * (add.ragged ? c.rag : 1.0);
+        if (last < each) sum -= 0.8 * (each - last);
+    }
+    return c.start + (n - 1.0) * c.tile + n * ctime * load + k * sum;
 }
 
-static const Cost16& least_cost(const Cost16* c, int n, int64_t M, int64_t N, int64_t stages, int64_t batch,
-                                double ring_cost, bool ring_only) {
+static const Cost& least_cost(const Cost* c, int n, int64_t M, int64_t N, int64_t stages, int64_t batch,
+                              const ProblemCost& add, bool ring_only) {
     int best = 0;
-    double least = cost16(c[0], M, N, stages, batch, ring_cost);
+    double least = cost_of(c[0], M, N, stages, batch, add);
     for (int i = 1; i < n; ++i) {
         if (ring_only && !c[i].shared) continue;
-        const double t = cost16(c[i], M, N, stages, batch, ring_cost);
+        const double t = cost_of(c[i], M, N, stages, batch, add);
         if (t < least) least = t, best = i;
     }
     return c[best];
 }
 
-static const Cost16& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch, bool ring_only) {
-    const Cost16* c = kCostSplit3;
-    int n = (int)(sizeof(kCostSplit3) / sizeof(Cost16));
-    if (kind == K_F16 || kind == K_BF16) c = kCostPlain, n = (int)(sizeof(kCostPlain) / sizeof(Cost16));
-    else if (kind == K_REFINE_A) c = kCostRefineA, n = (int)(sizeof(kCostRefineA) / sizeof(Cost16));
-    else if (kind == K_SPLIT4) c = kCostSplit4, n = (int)(sizeof(kCostSplit4) / sizeof(Cost16));
-    // rows of K % 64 != 0 are not whole 128-byte lines: the small tiles draw up
-    // to a fifth more of them (SPLIT4 3000^3: 0.69 us per stage, 4096^3: 0.55)
-    return least_cost(c, n, M, N, cdiv(K, 64), batch, K % 64 != 0 ? 1.2 : 1.0, ring_only);
+static const Cost& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch, bool ring_only) {
+    const Cost* c = kCostSplit3;
+    int n = (int)(sizeof(kCostSplit3) / sizeof(Cost));
+    const bool plain = kind == K_F16 || kind == K_BF16;
+    if (plain) c = kCostPlain, n = (int)(sizeof(kCostPlain) / sizeof(Cost));
+    else if (kind == K_REFINE_A) c = kCostRefineA, n = (int)(sizeof(kCostRefineA) / sizeof(Cost));
+    else if (kind == K_SPLIT4) c = kCostSplit4, n = (int)(sizeof(kCostSplit4) / sizeof(Cost));
+    ProblemCost add;
+    add.ragged = K % 64 != 0;
+    // past the 256 MB of the last cache the small tiles' repeated reads come from
+    // HBM (F16 320 x 18176 x 13952: 0.40 us per stage, 0.31 below), and so do,
+    // beside a plain kind's few stages, the writes of C (1344 x 83200 x 192: 185 us
+    // against 148 on 256 x 256)
+    const double planes_a = plain ? 1.0 : 2.0, planes_b = plain || kind == K_REFINE_A ? 1.0 : 2.0;
+    const double operands = 2.0 * (double)batch * (double)K * (planes_a * (double)M + planes_b * (double)N);
+    if (operands > 256e6) add.stage *= 1.3;
+    if (plain && 4.0 * (double)batch * (double)M * (double)N > 256e6) add.c = 1.3;
+    return least_cost(c, n, M, N, cdiv(K, 64), batch, add, ring_only);
 }
 
 // Whether the simple kernel (one wavefront per 32 x 32 block, no LDS) beats the
@@ -137,18 +171,17 @@ int pick_ring16(int kind, int64_t M, int64_t N, int64_t K, int64_t batch) {
     return pick16(kind, M, N, K, batch, true).variant;
 }
 
-// FP8: as for the 16-bit kinds, per 128-deep stage (start at 64 x 64 x 128,
-// lat at 128 x 128 x 4096, full at 4096^3).  The simple kernel is left with
-// rows of A that are not 16-byte aligned.
-static const Cost16 kCostF8[] = {
-    {2, 0, 64, 64, true, 2.4f, 0.27f, 0.195f},
-    {2, 1, 64, 128, true, 2.9f, 0.33f, 0.268f},
-    {2, 2, 128, 128, true, 3.6f, 0.55f, 0.41f},
-    {3, 0, 256, 128, false, 6.4f, 0.69f, 0.755f},
-    {4, 0, 256, 256, false, 9.6f, 1.10f, 1.12f},
+// FP8: per 128-deep stage.  The simple kernel is left with rows of A that are
+// not 16-byte aligned.
+static const Cost kCostF8[] = {
+    {2, 0, 64, 64, true, 2.68f, 0.384f, 0.027f, 0.213f, 0.038f, 1.0f, 1.0f},
+    {2, 1, 64, 128, true, 3.05f, 0.302f, 0.017f, 0.364f, 0.044f, 1.0f, 1.0f},
+    {2, 2, 128, 128, true, 2.59f, 0.827f, 0.023f, 0.508f, 0.061f, 1.0f, 1.0f},
+    {3, 0, 256, 128, false, 5.01f, 0.831f, 0.068f, 0.963f, 1.02f, 1.0f, 1.0f},
+    {4, 0, 256, 256, false, 9.00f, 1.040f, 0.021f, 1.210f, 1.27f, 1.0f, 1.0f},
 };
-static const Cost16& pick8(int64_t M, int64_t N, int64_t K, bool ring_only) {
-    return least_cost(kCostF8, (int)(sizeof(kCostF8) / sizeof(Cost16)), M, N, cdiv(K, 128), 1, 1.0, ring_only);
+static const Cost& pick8(int64_t M, int64_t N, int64_t K, bool ring_only) {
+    return least_cost(kCostF8, (int)(sizeof(kCostF8) / sizeof(Cost)), M, N, cdiv(K, 128), 1, ProblemCost{}, ring_only);
 }
 
 // B as row-major codes: the tiled kernels need a launch that transposes it

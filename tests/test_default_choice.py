@@ -1,6 +1,7 @@
-"""The default configuration on both sides of the rules that choose between a
-kernel without LDS for small problems (configuration 0) and the tiled ones:
-shapes timed on an MI355X, the faster one expected.  Host code alone: no GPU."""
+"""The default configuration on both sides of the rules that choose it, between a
+kernel without LDS for small problems (configuration 0) and the tiled ones and
+among these: shapes timed on an MI355X, the faster one expected.  Host code
+alone: no GPU."""
 import pytest
 
 import paper_1803_04014_amd as mfg
@@ -82,3 +83,28 @@ def test_f32(M, N, K, simple):
 ])
 def test_16_bit(mode, M, N, K, simple):
     assert _simple(mode, M, N, K, pre=True) == simple
+
+
+# us of a call on preconverted operands: every configuration of the rule
+@pytest.mark.parametrize("mode,M,N,K,config", [
+    ("bf16", 1792, 832, 10368, 28),      # 6: 66, 28: 60
+    ("f16", 4860, 5751, 716, 29),        # 6: 75.6, 28: 83.7, 30: 79.7, 29: 62.8
+    ("f16", 2752, 42432, 128, 29),       # 6: 111, 28: 158, 30: 135, 29: 123
+    ("f16", 4374, 12087, 115, 6),        # 6: 51, 28: 71, 30: 68, 29: 63
+    ("bf16", 4495, 292, 2982, 6),        # 6: 24, 28: 31
+    ("f16", 4096, 4096, 4096, 29),       # 28: 143, 30: 130, 29: 119
+    ("refine_a", 4736, 6528, 192, 3),    # 3: 42.8, 7: 52.3, 9: 57.4
+    ("refine_a", 1600, 4160, 3008, 7),   # 3: 106, 7: 86, 9: 111
+    ("refine_a", 1984, 4992, 1152, 9),   # 3: 59.8, 7: 57.6, 9: 51.5
+    ("refine_a", 4941, 2914, 121, 3),    # 3: 19.1, 7: 26.0, 9: 26.3
+    ("split3", 4096, 4096, 4096, 9),     # 7: 361, 9: 356
+    ("split3", 2048, 4096, 4096, 7),     # 3: 245, 7: 181, 9: 207
+    ("split3", 777, 1234, 1999, 3),
+    ("split3", 3105, 19080, 118, 3),     # 3: 93, 7: 105, 9: 104
+    ("split4", 12480, 832, 448, 2),      # 2: 44.4, 5: 48.9
+    ("split4", 9856, 1152, 1152, 5),     # 2: 108, 5: 90
+    ("split4", 7468, 4455, 85, 2),       # 2: 58, 5: 71
+    ("fp8", 1472, 4096, 2304, 3),        # 256 x 128, 1.16 times what was chosen
+])
+def test_tiles(mode, M, N, K, config):
+    assert mfg.lib().mfg_tune_lookup(M, N, K, mfg.mode_of(mode) | capi.MFG_IN_PRECONVERTED) == config
