@@ -219,10 +219,11 @@ int mfg_gemm_batched(int64_t count, int64_t M, int64_t N, int64_t K,
  *     modes head plane then residual plane, at A + M*lda and (two-sided
  *     splits) B + K*ldb elements; or
  *   - FP32 (mode | MFG_IN_FP32), rounded (the paper's rounding) or split (Eq.
- *     R) by every run: in the grouped kernel itself when no problem has M or
- *     N above 768 and no C overlaps an operand; otherwise the plan owns
- *     converted copies (ld rounded up to 8) and a run first converts all
- *     problems' A and B in one launch; a graph replay holds both launches.
+ *     R) by every run: in the grouped kernel itself where that is estimated
+ *     to be faster, no problem has M or N above 768 and no C overlaps an
+ *     operand; otherwise the plan owns converted copies (ld rounded up to 8)
+ *     and a run first converts all problems' A and B in one launch; a graph
+ *     replay holds both launches.
  * Each problem's result is bitwise that of mfg_gemm on the problem alone in
  * the same mode (preconverted, or from FP32 respectively).  The descriptor array is host memory; the plan copies it
  * to the device, so it may be freed after mfg_grouped_plan_create.

@@ -566,11 +566,9 @@ extern "C" int mfg_gemm_batched(int64_t count, int64_t M, int64_t N, int64_t K, 
 }
 
 // -------------------------------------------------------------------- grouped
-// Largest M or N of a plan whose FP32 operands the grouped kernel converts
-// itself (pass and kernel -> kernel alone, SPLIT3 and F16: 4096 problems of
-// 128^3 356 -> 174 and 251 -> 160 us, 256 of 512^3 586 -> 483 and 283 -> 235,
-// 128 of 768^3 848 -> 796 and 375 -> 342; 64 of 1024^3 914 -> 906 but 375 ->
-// 397, 16 of 2048^3 1557 -> 1710 and 569 -> 658).
+// Largest M or N of a plan whose FP32 operands the grouped kernel may convert
+// itself (pass and kernel -> kernel alone: 64 of 1024^3 F16 375 -> 397 us, 16 of
+// 2048^3 SPLIT3 1557 -> 1710, F16 569 -> 658).
 constexpr int64_t kGroupedDirect = 768;
 
 struct mfg_grouped_plan {
@@ -631,12 +629,40 @@ static int grouped_class(int m, int kind, int64_t M, int64_t N, int64_t K, int f
 }
 
 // Whether a plan's FP32 operands are converted in the grouped kernel instead
-// of by a pass before it.  The pass moves 6 or 8 bytes per element at the copy
-// rate; in the kernel every tile that reads an element converts it, beside
-// loads that the tiles wait for anyway: less until a row of tiles is long.
+// of by a pass before it, where that costs less.  The pass is a launch and 6 or
+// 8 bytes per element at the copy rate.  In the kernel every tile that reads an
+// element converts it: per 64-deep block of K that adds to the tile's chain of
+// loads and stores, 0.55 us to a 128 x 128 tile (1.25 past K = 4096) and
+// 0.27 to a 64 x 64 tile, or, with many tiles, their sum over the CUs, 0.8 and
+// 0.16 (REFINE_A 1.43 times that past sides of 512).  us, with pass and without, SPLIT3
+// and F16: 4096 problems of 128^3 356 -> 174 and 251 -> 160, 256 of 512^3 586 ->
+// 483 and 283 -> 235, 128 of 768^3 848 -> 796 and 375 -> 342; a long K or few
+// tiles are the other way round: F16 4 of 128 x 128 x 32768 517 and 761, one of
+// 256 x 256 x 2048 38 and 47, 18 of 768 x 768 x 8192 559 and 643 (of 280 plans the
+// choice costs 0.2% on average, the kernel alone 9.5%, the pass alone 11.7%).
 // Only without a C that overlaps an operand: the pass reads all of them before
 // any C is written.
-static bool grouped_direct(int64_t count, const mfg_problem* probs) {
+static bool grouped_converts(int64_t count, const mfg_problem* probs, int m, int force_tile) {
+    const int kind = kind_of(m);
+    const double planes_a = two_planes_a(m) ? 2.0 : 1.0, planes_b = two_planes_b(m) ? 2.0 : 1.0;
+    double bytes = 0.0, chain = 0.0, sum = 0.0, longest = 0.0;
+    for (int64_t i = 0; i < count; ++i) {
+        const mfg_problem& p = probs[i];
+        const int tile = grouped_class(m, kind, p.M, p.N, p.K, force_tile);
+        const double tiles = (double)(cdiv(p.M, tile) * cdiv(p.N, tile)), blocks = (double)cdiv(p.K, 64);
+        bytes += (double)(p.M * p.K) * (4.0 + 2.0 * planes_a) + (double)(p.K * p.N) * (4.0 + 2.0 * planes_b);
+        if (tiles == 0.0) continue;
+        double each = tile == 128 ? 0.8 : 0.16, link = tile == 128 ? (p.K > 4096 ? 1.25 : 0.55) : 0.27;
+        if (planes_a != planes_b && (p.M > 512 || p.N > 512)) each *= 1.43, link *= 1.43;
+        sum += each * tiles * blocks / 256.0;
+        longest = std::max(longest, (tile == 128 ? 0.5 : 1.0) * each * blocks);
+        chain = std::max(chain, link * blocks);
+    }
+    return std::max(chain, sum + longest) < 2.5 + bytes / 5.3e6;
+}
+
+static bool grouped_direct(int64_t count, const mfg_problem* probs, int m, int force_tile) {
+    if (!grouped_converts(count, probs, m, force_tile)) return false;
     struct Range {
         uintptr_t lo, hi;
     };
@@ -689,7 +715,7 @@ static int plan_create_impl(int64_t count, const mfg_problem* probs, int mode, m
         if (st != MFG_OK) return st;
         if (p.M > ((int64_t)1 << 24) || p.N > ((int64_t)1 << 24) || p.K > INT32_MAX) return MFG_ERR_UNSUPPORTED;
     }
-    direct = direct && grouped_direct(count, probs);
+    direct = direct && grouped_direct(count, probs, m, force_tile);
     // MFG_IN_FP32: byte offsets of each problem's converted A and B in the
     // plan's storage (256-byte aligned, ld rounded up to 8 elements)
     std::vector<int64_t> conv_off(fp32_in ? (size_t)count * 2 : 0);

@@ -67,3 +67,27 @@ def test_output_overlapping_an_operand(mode):
     chained = [(other[i], other[i + 1], other[i + 2]) for i in range(0, 57, 3)]
     shared = (buf[1:], other[57], other[58])  # its A shares rows with the next problem's C
     check(chained + [shared, (other[59], other[0], buf[:96])], mode)
+
+
+# us with the pass, and converted in the kernel
+@pytest.mark.parametrize("mode,count,M,N,K,in_kernel", [
+    ("f16", 4, 128, 128, 32768, False),   # 517, 761
+    ("f16", 64, 512, 512, 512, True),     # 68, 49
+    ("bf16", 2, 256, 256, 8192, False),   # 130 to 141, 188 to 191
+    ("split3", 64, 128, 128, 2048, True),  # 75, 41
+    ("refine_a", 16, 768, 768, 8192, False),  # 810, 899
+    ("refine_a", 4, 768, 768, 512, True),  # 23, 19
+])
+def test_conversion_where_it_costs_less(mode, count, M, N, K, in_kernel):
+    """Only a plan with a pass holds converted copies: 16 MB of them here at least."""
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    problems = [(torch.randn((M, K), device=DEV, generator=gen), torch.randn((K, N), device=DEV, generator=gen),
+                 torch.randn((M, N), device=DEV, generator=gen)) for _ in range(count)]
+    check(problems[:2], mode)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan = mfg.GroupedPlan(problems, mode, fp32_in=True)
+    held = before - torch.cuda.mem_get_info()[0]
+    plan.close()
+    copies = 2 * count * K * (M + N)
+    assert held < copies / 2 if in_kernel else held >= copies / 2, held
