@@ -1501,23 +1501,26 @@ static int permutation(int64_t n, const int32_t* ipiv, std::vector<int32_t>& per
     return MFG_OK;
 }
 
-// Device words of lu_chain (n x nrhs published unknowns and the ticket
-// counter) and what its launches so far have used of them; none where the
-// grid would not hold a wavefront per block and right-hand side.
+// Device words of lu_chain for `cols` right-hand sides at a time (n x cols
+// published unknowns and the ticket counter) and what its launches so far have
+// used of them; none where lu_substitute goes block by block.
 struct ChainWords {
     unsigned long long* z = nullptr;
+    int64_t cols = 0;
     uint32_t tag = 0, tickets = 0;
 };
-static size_t chain_words(int64_t n, int64_t nrhs) {
-    return nrhs <= 65535 && n * nrhs <= (int64_t)1 << 30 ? (size_t)(n * nrhs + 1) : 0;
+static int64_t chain_cols(int64_t n, int64_t nrhs) {
+    if (nrhs > 65535) return 0;
+    return std::min(nrhs, std::max<int64_t>(1, ((int64_t)1 << 30) / n));
 }
+static size_t chain_words(int64_t n, int64_t cols) { return cols > 0 ? (size_t)(n * cols + 1) : 0; }
 // lu_chain with R = 1 up to here (both substitutions of lu_solve: n = 2048, 128
 // right-hand sides, 4096 wavefronts, 534 us against 787 with R = 4; n = 1024, 1024
 // of them, 16384: 813 against 588).
 constexpr int64_t kChainWaves = 8192;
-static int chain_clear(int64_t n, int64_t nrhs, const ChainWords& c, hipStream_t s) {
+static int chain_clear(int64_t n, const ChainWords& c, hipStream_t s) {
     if (c.z == nullptr) return MFG_OK;
-    const int64_t words = 2 * (int64_t)chain_words(n, nrhs);
+    const int64_t words = 2 * (int64_t)chain_words(n, c.cols);
     hipLaunchKernelGGL(zero_words, dim3(blocks(words, 256)), dim3(256), 0, s, words, reinterpret_cast<uint32_t*>(c.z));
     MFG_LAUNCH_CHECK();
     return MFG_OK;
@@ -1525,24 +1528,28 @@ static int chain_clear(int64_t n, int64_t nrhs, const ChainWords& c, hipStream_t
 
 // V = U^-1 L^-1 V (V: n x nrhs FP32, already permuted) in FP32, in place:
 // forward and backward substitution by blocks of kNb rows, one launch each
-// (lu_chain).  Without the words for that (too many, or no memory), block by
-// block instead: the diagonal block (lu_trsv_block), then the rest of V by an
-// FP32 mfg_gemm.
+// (lu_chain), for as many right-hand sides at a time as there are words for;
+// each one's result is the same whatever their number.  Beyond 65535 right-hand
+// sides block by block: the diagonal block (lu_trsv_block), then the rest of V by
+// an FP32 mfg_gemm.
 static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, ChainWords& c,
                          hipStream_t s) {
     const int64_t nblk = (n + kNb - 1) / kNb;
     if (c.z != nullptr) {
         const int vec = ldlu % 4 == 0 && reinterpret_cast<uintptr_t>(LU) % 16 == 0;
-        const int R = nblk * nrhs > kChainWaves ? 4 : 1;
-        const uint32_t grid = (uint32_t)(nblk * ((nrhs + R - 1) / R));
-        uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * nrhs);
-        for (int lower = 1; lower >= 0; --lower) {
-            auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : lu_chain<true, 1>)
-                                 : (R == 4 ? lu_chain<false, 4> : lu_chain<false, 1>);
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, nrhs, (int)nblk, V, ldv, c.z, ++c.tag,
-                               ticket, c.tickets, vec);
-            MFG_LAUNCH_CHECK();
-            c.tickets += grid;
+        uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * c.cols);
+        for (int64_t q = 0; q < nrhs; q += c.cols) {
+            const int64_t cols = std::min(c.cols, nrhs - q);
+            const int R = nblk * cols > kChainWaves ? 4 : 1;
+            const uint32_t grid = (uint32_t)(nblk * ((cols + R - 1) / R));
+            for (int lower = 1; lower >= 0; --lower) {
+                auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : lu_chain<true, 1>)
+                                     : (R == 4 ? lu_chain<false, 4> : lu_chain<false, 1>);
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, cols, (int)nblk, V + q, ldv, c.z,
+                                   ++c.tag, ticket, c.tickets, vec);
+                MFG_LAUNCH_CHECK();
+                c.tickets += grid;
+            }
         }
         return MFG_OK;
     }
@@ -1599,6 +1606,16 @@ struct Buffers {
         ptrs.push_back(*p);
         return MFG_OK;
     }
+    // The chain's words: without memory for all right-hand sides at once, for half
+    // of them, and so on.
+    int get_chain(int64_t n, int64_t nrhs, ChainWords& c) {
+        c.cols = chain_cols(n, nrhs);
+        if (c.cols == 0) return MFG_OK;
+        for (;; c.cols = (c.cols + 1) / 2) {
+            if (!fault_hit(kFaultAlloc) && get(&c.z, chain_words(n, c.cols)) == MFG_OK) return MFG_OK;
+            if (c.cols == 1) return MFG_ERR_NO_MEMORY;
+        }
+    }
     ~Buffers() {
         for (void* p : ptrs) (void)hipFree(p);
     }
@@ -1638,9 +1655,10 @@ int lu_solve_api(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const i
     int32_t* dperm = nullptr;
     float* tmp = nullptr;
     ChainWords chain;
-    if ((st = buf.get(&dperm, (size_t)n)) != MFG_OK || (st = buf.get(&tmp, (size_t)(n * nrhs))) != MFG_OK) return st;
-    if (chain_words(n, nrhs) > 0) (void)buf.get(&chain.z, chain_words(n, nrhs));
-    if ((st = chain_clear(n, nrhs, chain, s)) != MFG_OK) return st;
+    if ((st = buf.get(&dperm, (size_t)n)) != MFG_OK || (st = buf.get(&tmp, (size_t)(n * nrhs))) != MFG_OK ||
+        (st = buf.get_chain(n, nrhs, chain)) != MFG_OK)
+        return st;
+    if ((st = chain_clear(n, chain, s)) != MFG_OK) return st;
     MFG_HIP_CHECK(hipMemcpyAsync(dperm, perm.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
     if ((st = lu_solve_impl(n, nrhs, LU, ldlu, dperm, B, ldb, tmp, nrhs, chain, s)) != MFG_OK) return st;
     MFG_HIP_CHECK(hipMemcpy2DAsync(B, (size_t)ldb * 4, tmp, (size_t)nrhs * 4, (size_t)nrhs * 4, (size_t)n,
@@ -1672,10 +1690,10 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
         (st = buf.get(&d, (size_t)(n * nrhs))) != MFG_OK || (st = buf.get(&R, (size_t)(n * nrhs))) != MFG_OK ||
         (st = buf.get(&rows, (size_t)n)) != MFG_OK || (st = buf.get(&nrm, (size_t)(3 * nrhs + 1))) != MFG_OK ||
         (st = buf.get(&ipiv, (size_t)n)) != MFG_OK || (st = buf.get(&dperm, (size_t)n)) != MFG_OK ||
-        (st = buf.get(&dinfo, 1)) != MFG_OK || (st = buf.get(&scratch, lu_scratch_bytes(n))) != MFG_OK)
+        (st = buf.get(&dinfo, 1)) != MFG_OK || (st = buf.get(&scratch, lu_scratch_bytes(n))) != MFG_OK ||
+        (st = buf.get_chain(n, nrhs, chain)) != MFG_OK)
         return st;
-    if (chain_words(n, nrhs) > 0) (void)buf.get(&chain.z, chain_words(n, nrhs));
-    if ((st = chain_clear(n, nrhs, chain, s)) != MFG_OK) return st;
+    if ((st = chain_clear(n, chain, s)) != MFG_OK) return st;
     // the factorisation of the FP32 copy, in the given mode
     hipLaunchKernelGGL(f64_to_f32, dim3(blocks(n * n, 256)), dim3(256), 0, s, n, n, A, lda, A32, n);
     MFG_LAUNCH_CHECK();

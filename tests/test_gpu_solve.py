@@ -165,3 +165,31 @@ def test_invalid_arguments():
         mfg.capi.MFG_ERR_INVALID_ARG  # flags
     assert L.mfg_lu_factor(-1, dA.data_ptr(), 4, ipiv.data_ptr(), None, mfg.capi.MFG_F32, s) == \
         mfg.capi.MFG_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("n,nrhs", [(65, 2), (200, 3), (777, 200), (1030, 1025)])
+def test_lu_solve_in_parts_is_the_same(n, nrhs):
+    """Without memory for the words of all right-hand sides at once they are solved in parts: the same bits."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    LU = torch.randn((n, n), device=DEV, generator=gen) + 2.0 * n ** 0.5 * torch.eye(n, device=DEV)
+    B = torch.randn((n, nrhs), device=DEV, generator=gen)
+    ipiv, info = mfg.lu_factor(LU, "f32")
+    assert info == 0
+    whole, parts = B.clone(), B.clone()
+    mfg.lu_solve(LU, ipiv, whole)
+    assert mfg.lib().mfg_fault_inject(0, 1) == 0
+    mfg.lu_solve(LU, ipiv, parts)
+    one = B[:, nrhs - 1:].clone()
+    mfg.lu_solve(LU, ipiv, one)  # (the call before met the fault: this one does not)
+    assert torch.equal(whole, parts) and torch.equal(whole[:, nrhs - 1:], one)
+    assert mfg.lib().mfg_fault_inject(0, 1) == 0
+    with pytest.raises(mfg.MfgError):  # not even for one right-hand side
+        mfg.lu_solve(LU, ipiv, one)
+    A = torch.randn((n, n), device=DEV, generator=gen, dtype=torch.float64) + 2.0 * n ** 0.5 * torch.eye(n, device=DEV)
+    X = [torch.empty((n, nrhs), device=DEV, dtype=torch.float64) for _ in range(2)]
+    out = []
+    for k in (0, 1):
+        assert mfg.lib().mfg_fault_inject(0, k) == 0
+        out.append(mfg.solve_ir(A, B.double(), X[k], "f32", 3))
+    assert mfg.lib().mfg_fault_inject(0, 0) == 0
+    assert out[0] == out[1] and torch.equal(X[0], X[1])
