@@ -1158,8 +1158,8 @@ __global__ __launch_bounds__(kNb) void lu_trsv_block(const float* LU, int64_t ld
 // Bound by the chain from block to block: a publication seen, 64 multiply-adds,
 // the 64 dependent steps of the diagonal block.  At n = 2048, one right-hand
 // side, 102 us forward and 148 backward against 32 launches of 7.8 and 9.1 us.
-// R = 4 where the wavefronts of R = 1 would come in many turns: the rows'
-// entries are then loaded once for four.
+// R = 2 and 4 where the wavefronts of R = 1 would come in many turns: the rows'
+// entries are then loaded once for them (chain_rhs).
 //
 // A published unknown is one 64-bit word, its value beside the launch's tag,
 // stored and polled as a relaxed agent-scope atomic, so the value needs no
@@ -1514,10 +1514,18 @@ static int64_t chain_cols(int64_t n, int64_t nrhs) {
     return std::min(nrhs, std::max<int64_t>(1, ((int64_t)1 << 30) / n));
 }
 static size_t chain_words(int64_t n, int64_t cols) { return cols > 0 ? (size_t)(n * cols + 1) : 0; }
-// lu_chain with R = 1 up to here (both substitutions of lu_solve: n = 2048, 128
-// right-hand sides, 4096 wavefronts, 534 us against 787 with R = 4; n = 1024, 1024
-// of them, 16384: 813 against 588).
-constexpr int64_t kChainWaves = 8192;
+// Right-hand sides per wavefront of lu_chain.  One wavefront's chain is the
+// shortest with one of them; past the wavefronts that the chip holds, more share
+// the loads of the factors, and all the earlier where rows are read an element
+// at a time.  us of both substitutions with 1, 2 and 4, nrhs = 100, 400, 1000:
+// n = 500 132 151 211, 228 214 259, 338 269 305; n = 2048 481 515 754, 1054 714
+// 866, 2314 1335 1058; n = 777 239 219 308, 655 426 401, 1183 770 548; n = 2049
+// 1185 650 773, 3667 1913 1207, 8708 4367 2261 (the last two odd; one launch per
+// block of rows 302, 496, 944 and 947, 2299, 4679).
+static int chain_rhs(int64_t nblk, int64_t nrhs, bool vec) {
+    if (nrhs > std::min<int64_t>(vec ? 1200 : 700, (vec ? 22000 : 4500) / nblk)) return 4;
+    return nrhs > std::min<int64_t>(vec ? 280 : 170, (vec ? 5500 : 1300) / nblk) ? 2 : 1;
+}
 static int chain_clear(int64_t n, const ChainWords& c, hipStream_t s) {
     if (c.z == nullptr) return MFG_OK;
     const int64_t words = 2 * (int64_t)chain_words(n, c.cols);
@@ -1540,11 +1548,11 @@ static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu,
         uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * c.cols);
         for (int64_t q = 0; q < nrhs; q += c.cols) {
             const int64_t cols = std::min(c.cols, nrhs - q);
-            const int R = nblk * cols > kChainWaves ? 4 : 1;
+            const int R = chain_rhs(nblk, cols, vec != 0);
             const uint32_t grid = (uint32_t)(nblk * ((cols + R - 1) / R));
             for (int lower = 1; lower >= 0; --lower) {
-                auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : lu_chain<true, 1>)
-                                     : (R == 4 ? lu_chain<false, 4> : lu_chain<false, 1>);
+                auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : R == 2 ? lu_chain<true, 2> : lu_chain<true, 1>)
+                                     : (R == 4 ? lu_chain<false, 4> : R == 2 ? lu_chain<false, 2> : lu_chain<false, 1>);
                 hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, cols, (int)nblk, V + q, ldv, c.z,
                                    ++c.tag, ticket, c.tickets, vec);
                 MFG_LAUNCH_CHECK();

@@ -193,3 +193,16 @@ def test_lu_solve_in_parts_is_the_same(n, nrhs):
         out.append(mfg.solve_ir(A, B.double(), X[k], "f32", 3))
     assert mfg.lib().mfg_fault_inject(0, 0) == 0
     assert out[0] == out[1] and torch.equal(X[0], X[1])
+
+
+@pytest.mark.parametrize("n,nrhs,alone", [(100, 400, 7), (127, 301, 300), (1030, 1500, 100), (777, 400, 30), (1028, 1500, 400)])
+def test_lu_solve_right_hand_sides_are_independent(n, nrhs, alone):
+    """However many right-hand sides a wavefront or a launch takes, each one's bits are those of a solve of fewer."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    LU = torch.randn((n, n), device=DEV, generator=gen) + 2.0 * n ** 0.5 * torch.eye(n, device=DEV)
+    B = torch.randn((n, nrhs), device=DEV, generator=gen)
+    ipiv, info = mfg.lu_factor(LU, "f32")
+    few = B[:, nrhs - alone:].clone()
+    mfg.lu_solve(LU, ipiv, B)
+    mfg.lu_solve(LU, ipiv, few)
+    assert torch.equal(B[:, nrhs - alone:], few)
