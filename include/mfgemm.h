@@ -318,13 +318,14 @@ int mfg_grouped_autotune(int64_t count, const mfg_problem* problems, int mode, i
 int mfg_lu_factor(int64_t n, float* A, int64_t lda, int32_t* ipiv, int64_t* info, int mode, void* stream);
 /* mfg_lu_solve -- B = (L U)^-1 P B in place for the n x nrhs FP32 B (device,
  * ldb >= max(1, nrhs)) with the factors and pivots of mfg_lu_factor: the
- * permutation, then forward and backward substitution by 64-row blocks
- * (one launch each; beyond 65535 right-hand sides block by block with the
- * updates by FP32 mfg_gemm).  Allocates an n x nrhs FP32 work array, the
- * permutation and, up to 65535 right-hand sides, n x nrhs 8-byte words (2^30
- * at most, and fewer where memory is short: the right-hand sides are then
- * solved in parts, with the same results).  B's contents are unspecified after
- * an error.  Synchronises `stream`.
+ * permutation, then forward and backward substitution by 64-row blocks, one
+ * launch each (n < 128 with more than 300 right-hand sides, and some n < 192,
+ * one per block; beyond 65535 right-hand sides block by block with the updates
+ * by FP32 mfg_gemm).  Allocates an n x nrhs FP32 work array, the permutation
+ * and, where the substitution is one launch of more than one block, n x nrhs
+ * 8-byte words (2^30 at most, and fewer where memory is short: the right-hand
+ * sides are then solved in parts, with the same results).  B's contents are
+ * unspecified after an error.  Synchronises `stream`.
  * Errors: MFG_ERR_INVALID_ARG (negative sizes, ldlu < max(1, n), ldb < max(1,
  * nrhs), NULL pointers, ipiv not of a factorisation); MFG_ERR_UNSUPPORTED for
  * nrhs > 2^31 - 1; MFG_ERR_NO_MEMORY without memory for one right-hand side's

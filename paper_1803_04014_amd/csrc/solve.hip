@@ -1260,15 +1260,81 @@ __global__ __launch_bounds__(kNb) void lu_chain(const float* LU, int64_t ldlu, i
     }
 }
 
-__global__ __launch_bounds__(256) void zero_words(int64_t n, uint32_t* p) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0;
+// One block step of the substitution, for right-hand side q = blockIdx.y:
+// the diagonal block [s, s+w) of the factors solved (unit lower, forward, or
+// upper with the diagonal, backward) from In[s:s+w, q] by the first
+// wavefront of every workgroup, as in lu_trsv_block (each workgroup solves
+// the same small system, so none waits for another); workgroup 0 writes the
+// solution to Out[s:s+w, q]; and the rows still to be solved (forward: below
+// the block, backward: above it), one per thread, are updated in place,
+// In[r, q] -= LU[r, s:s+w] . x, by multiply-adds in column order.  In and
+// Out are distinct arrays, so no workgroup overwrites right-hand sides
+// another still reads.  vec: LU's rows 16-byte aligned at column s.
+template <bool LOWER>
+__global__ __launch_bounds__(256) void lu_subst_step(const float* LU, int64_t ldlu, int64_t n, int64_t s, int w,
+                                                     float* In, int64_t ldi, float* Out, int64_t ldo, int vec) {
+    __shared__ float xs[kNb];
+    const int64_t q = blockIdx.y;
+    if (threadIdx.x < kNb) {
+        const int i = threadIdx.x;
+        const float* row = LU + (s + (i < w ? i : 0)) * ldlu + s;
+        float r[kNb];
+#pragma unroll
+        for (int k = 0; k < kNb; ++k) r[k] = k < w ? row[k] : 0.0f;
+        float xi = i < w ? In[(s + i) * ldi + q] : 0.0f;
+        auto lane_value = [](float v, int k) {
+            return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), k));
+        };
+        if constexpr (LOWER) {
+#pragma unroll
+            for (int k = 0; k < kNb; ++k) {
+                if (k < w) {
+                    const float xk = lane_value(xi, k);
+                    if (i > k && i < w) xi = __builtin_fmaf(-r[k], xk, xi);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int k = kNb - 1; k >= 0; --k) {
+                if (k < w) {
+                    if (i == k) xi = xi / r[k];
+                    const float xk = lane_value(xi, k);
+                    if (i < k) xi = __builtin_fmaf(-r[k], xk, xi);
+                }
+            }
+        }
+        xs[i] = xi;  // 0 for i >= w
+        if (blockIdx.x == 0 && i < w) Out[(s + i) * ldo + q] = xi;
+    }
+    __syncthreads();
+    const int64_t r0 = LOWER ? s + w : 0, r1 = LOWER ? n : s;
+    const int64_t rr = r0 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (rr >= r1) return;
+    const float* lr = LU + rr * ldlu + s;
+    float acc = In[rr * ldi + q];
+    if (vec && w == kNb) {
+#pragma unroll
+        for (int k4 = 0; k4 < kNb / 4; ++k4) {
+            const float4 a = reinterpret_cast<const float4*>(lr)[k4];
+            acc = __builtin_fmaf(-a.x, xs[4 * k4], acc);
+            acc = __builtin_fmaf(-a.y, xs[4 * k4 + 1], acc);
+            acc = __builtin_fmaf(-a.z, xs[4 * k4 + 2], acc);
+            acc = __builtin_fmaf(-a.w, xs[4 * k4 + 3], acc);
+        }
+    } else {
+        for (int k = 0; k < w; ++k) acc = __builtin_fmaf(-lr[k], xs[k], acc);
+    }
+    In[rr * ldi + q] = acc;
 }
 
-// dst[i, :] = src[perm[i], :] (rows of nrhs FP32 values).
+// dst[i, :] = src[perm[i], :] (rows of nrhs FP32 values); and zeros into the
+// first `words` <= n x nrhs + 1 of Z.
 __global__ __launch_bounds__(256) void gather_rows(int64_t n, int64_t nrhs, const int32_t* perm, const float* src,
-                                                   int64_t lds, float* dst, int64_t ldd) {
+                                                   int64_t lds, float* dst, int64_t ldd, unsigned long long* Z,
+                                                   int64_t words) {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e + 1 < words) Z[e + 1] = 0;
+    if (e == 0 && words > 0) Z[0] = 0;
     if (e >= n * nrhs) return;
     const int64_t i = e / nrhs, q = e % nrhs;
     dst[i * ldd + q] = src[(int64_t)perm[i] * lds + q];
@@ -1509,8 +1575,18 @@ struct ChainWords {
     int64_t cols = 0;
     uint32_t tag = 0, tickets = 0;
 };
+// Two blocks, the second not whole, and many right-hand sides: one launch per
+// block (lu_subst_step); also of three, where only the words would take more
+// than the 2 MB past which an allocation is 40 us.  us of mfg_lu_solve: n = 65
+// with 400, 1000 and 3000 of them 71, 75, 103 against 75, 85, 144 of lu_chain,
+// n = 100 74, 82, 121 and 78, 92, 152; n = 129 with 3000 175 and 212; but n = 128
+// with 400 and 1000 85, 103 and 82, 97.
+static bool subst_by_steps(int64_t n, int64_t nrhs) {
+    if (n <= kNb || n >= 3 * kNb || nrhs > 65535) return false;
+    return n < 2 * kNb ? nrhs > 300 : n * nrhs > (1 << 18) && n * nrhs <= (1 << 19);
+}
 static int64_t chain_cols(int64_t n, int64_t nrhs) {
-    if (nrhs > 65535) return 0;
+    if (n <= kNb || nrhs > 65535 || subst_by_steps(n, nrhs)) return 0;
     return std::min(nrhs, std::max<int64_t>(1, ((int64_t)1 << 30) / n));
 }
 static size_t chain_words(int64_t n, int64_t cols) { return cols > 0 ? (size_t)(n * cols + 1) : 0; }
@@ -1526,25 +1602,17 @@ static int chain_rhs(int64_t nblk, int64_t nrhs, bool vec) {
     if (nrhs > std::min<int64_t>(vec ? 1200 : 700, (vec ? 22000 : 4500) / nblk)) return 4;
     return nrhs > std::min<int64_t>(vec ? 280 : 170, (vec ? 5500 : 1300) / nblk) ? 2 : 1;
 }
-static int chain_clear(int64_t n, const ChainWords& c, hipStream_t s) {
-    if (c.z == nullptr) return MFG_OK;
-    const int64_t words = 2 * (int64_t)chain_words(n, c.cols);
-    hipLaunchKernelGGL(zero_words, dim3(blocks(words, 256)), dim3(256), 0, s, words, reinterpret_cast<uint32_t*>(c.z));
-    MFG_LAUNCH_CHECK();
-    return MFG_OK;
-}
-
 // V = U^-1 L^-1 V (V: n x nrhs FP32, already permuted) in FP32, in place:
-// forward and backward substitution by blocks of kNb rows, one launch each
-// (lu_chain), for as many right-hand sides at a time as there are words for;
-// each one's result is the same whatever their number.  Beyond 65535 right-hand
-// sides block by block: the diagonal block (lu_trsv_block), then the rest of V by
-// an FP32 mfg_gemm.
-static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, ChainWords& c,
-                         hipStream_t s) {
+// with Y as large as scratch; forward and backward substitution by blocks of kNb
+// rows, one launch each (lu_chain), for as many right-hand sides at a time as there are words for;
+// each one's result is the same whatever their number.  One block of rows needs
+// no words; beyond 65535 right-hand sides block by block: the diagonal block
+// (lu_trsv_block), then the rest of V by an FP32 mfg_gemm.
+static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, float* Y,
+                         int64_t ldy, ChainWords& c, hipStream_t s) {
     const int64_t nblk = (n + kNb - 1) / kNb;
+    const int vec = ldlu % 4 == 0 && reinterpret_cast<uintptr_t>(LU) % 16 == 0;
     if (c.z != nullptr) {
-        const int vec = ldlu % 4 == 0 && reinterpret_cast<uintptr_t>(LU) % 16 == 0;
         uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * c.cols);
         for (int64_t q = 0; q < nrhs; q += c.cols) {
             const int64_t cols = std::min(c.cols, nrhs - q);
@@ -1558,6 +1626,21 @@ static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu,
                 MFG_LAUNCH_CHECK();
                 c.tickets += grid;
             }
+        }
+        return MFG_OK;
+    }
+    if (subst_by_steps(n, nrhs)) {
+        for (int64_t b = 0; b < n; b += kNb) {  // forward, unit lower: V -> Y
+            const int w = (int)std::min<int64_t>(kNb, n - b);
+            hipLaunchKernelGGL(lu_subst_step<true>, dim3(blocks(n - b - w, 256), (unsigned)nrhs), dim3(256), 0, s, LU,
+                               ldlu, n, b, w, V, ldv, Y, ldy, vec);
+            MFG_LAUNCH_CHECK();
+        }
+        for (int64_t b = ((n - 1) / kNb) * kNb; b >= 0; b -= kNb) {  // backward, upper: Y -> V
+            const int w = (int)std::min<int64_t>(kNb, n - b);
+            hipLaunchKernelGGL(lu_subst_step<false>, dim3(blocks(b, 256), (unsigned)nrhs), dim3(256), 0, s, LU, ldlu, n,
+                               b, w, Y, ldy, V, ldv, vec);
+            MFG_LAUNCH_CHECK();
         }
         return MFG_OK;
     }
@@ -1585,12 +1668,15 @@ static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu,
     return MFG_OK;
 }
 
-// X = (LU)^-1 P B with B, X n x nrhs FP32 (X may not alias B).
-static int lu_solve_impl(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* dperm, const float* B,
+// X = (LU)^-1 P B with B, X n x nrhs FP32 (X may not alias B); B's contents are
+// unspecified afterwards.  The chain's words are cleared the first time.
+static int lu_solve_impl(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* dperm, float* B,
                          int64_t ldb, float* X, int64_t ldx, ChainWords& c, hipStream_t s) {
-    hipLaunchKernelGGL(gather_rows, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, dperm, B, ldb, X, ldx);
+    const int64_t words = c.tag == 0 ? (int64_t)chain_words(n, c.cols) : 0;
+    hipLaunchKernelGGL(gather_rows, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, dperm, B, ldb, X, ldx, c.z,
+                       words);
     MFG_LAUNCH_CHECK();
-    return lu_substitute(n, nrhs, LU, ldlu, X, ldx, c, s);
+    return lu_substitute(n, nrhs, LU, ldlu, X, ldx, B, ldb, c, s);
 }
 
 }  // namespace mfg
@@ -1614,14 +1700,26 @@ struct Buffers {
         ptrs.push_back(*p);
         return MFG_OK;
     }
-    // The chain's words: without memory for all right-hand sides at once, for half
-    // of them, and so on.
-    int get_chain(int64_t n, int64_t nrhs, ChainWords& c) {
-        c.cols = chain_cols(n, nrhs);
-        if (c.cols == 0) return MFG_OK;
-        for (;; c.cols = (c.cols + 1) / 2) {
-            if (!fault_hit(kFaultAlloc) && get(&c.z, chain_words(n, c.cols)) == MFG_OK) return MFG_OK;
-            if (c.cols == 1) return MFG_ERR_NO_MEMORY;
+    // `lead` bytes and the chain's words, these without memory for all right-hand
+    // sides at once for half of them, and so on.  One allocation, as a second one
+    // and its free are 6 of the 55 us of a small mfg_lu_solve; but two where that
+    // keeps the words within 2 MB, past which an allocation is 40 us (n = 192, 1000
+    // right-hand sides: 157 us with one, 120 with two).
+    int get_with_chain(char** p, size_t lead, int64_t n, int64_t nrhs, ChainWords& c) {
+        constexpr size_t kSmall = (size_t)2 << 20;
+        lead = (lead + 255) / 256 * 256;
+        *p = nullptr;
+        for (c.cols = chain_cols(n, nrhs);; c.cols = (c.cols + 1) / 2) {
+            const size_t words = chain_words(n, c.cols) * sizeof(*c.z);
+            const bool two = lead + words > kSmall && words <= kSmall && words > 0;
+            int st = fault_hit(kFaultAlloc) ? MFG_ERR_NO_MEMORY : MFG_OK;
+            if (st == MFG_OK && (!two || *p == nullptr)) st = get(p, two ? lead : lead + words);
+            if (st == MFG_OK && words > 0) {
+                if (two) st = get(&c.z, (size_t)(n * c.cols + 1));
+                else c.z = reinterpret_cast<unsigned long long*>(*p + lead);
+            }
+            if (st == MFG_OK) return MFG_OK;
+            if (c.cols <= 1) return st;
         }
     }
     ~Buffers() {
@@ -1660,13 +1758,11 @@ int lu_solve_api(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const i
     int st = permutation(n, ipiv, perm, s);
     if (st != MFG_OK) return st;
     Buffers buf;
-    int32_t* dperm = nullptr;
-    float* tmp = nullptr;
+    char* base = nullptr;
     ChainWords chain;
-    if ((st = buf.get(&dperm, (size_t)n)) != MFG_OK || (st = buf.get(&tmp, (size_t)(n * nrhs))) != MFG_OK ||
-        (st = buf.get_chain(n, nrhs, chain)) != MFG_OK)
-        return st;
-    if ((st = chain_clear(n, chain, s)) != MFG_OK) return st;
+    if ((st = buf.get_with_chain(&base, (size_t)(n * nrhs + n) * 4, n, nrhs, chain)) != MFG_OK) return st;
+    float* tmp = reinterpret_cast<float*>(base);
+    int32_t* dperm = reinterpret_cast<int32_t*>(tmp + n * nrhs);
     MFG_HIP_CHECK(hipMemcpyAsync(dperm, perm.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
     if ((st = lu_solve_impl(n, nrhs, LU, ldlu, dperm, B, ldb, tmp, nrhs, chain, s)) != MFG_OK) return st;
     MFG_HIP_CHECK(hipMemcpy2DAsync(B, (size_t)ldb * 4, tmp, (size_t)nrhs * 4, (size_t)nrhs * 4, (size_t)n,
@@ -1692,16 +1788,17 @@ int solve_ir_api(int64_t n, int64_t nrhs, const double* A, int64_t lda, const do
     char* scratch = nullptr;
     double *R = nullptr, *rows = nullptr, *nrm = nullptr;
     int32_t *ipiv = nullptr, *dperm = nullptr, *dinfo = nullptr;
+    char* base = nullptr;
     ChainWords chain;
     int st;
     if ((st = buf.get(&A32, (size_t)(n * n))) != MFG_OK || (st = buf.get(&v, (size_t)(n * nrhs))) != MFG_OK ||
-        (st = buf.get(&d, (size_t)(n * nrhs))) != MFG_OK || (st = buf.get(&R, (size_t)(n * nrhs))) != MFG_OK ||
+        (st = buf.get_with_chain(&base, (size_t)(n * nrhs) * 4, n, nrhs, chain)) != MFG_OK ||
+        (st = buf.get(&R, (size_t)(n * nrhs))) != MFG_OK ||
         (st = buf.get(&rows, (size_t)n)) != MFG_OK || (st = buf.get(&nrm, (size_t)(3 * nrhs + 1))) != MFG_OK ||
         (st = buf.get(&ipiv, (size_t)n)) != MFG_OK || (st = buf.get(&dperm, (size_t)n)) != MFG_OK ||
-        (st = buf.get(&dinfo, 1)) != MFG_OK || (st = buf.get(&scratch, lu_scratch_bytes(n))) != MFG_OK ||
-        (st = buf.get_chain(n, nrhs, chain)) != MFG_OK)
+        (st = buf.get(&dinfo, 1)) != MFG_OK || (st = buf.get(&scratch, lu_scratch_bytes(n))) != MFG_OK)
         return st;
-    if ((st = chain_clear(n, chain, s)) != MFG_OK) return st;
+    d = reinterpret_cast<float*>(base);
     // the factorisation of the FP32 copy, in the given mode
     hipLaunchKernelGGL(f64_to_f32, dim3(blocks(n * n, 256)), dim3(256), 0, s, n, n, A, lda, A32, n);
     MFG_LAUNCH_CHECK();

@@ -195,7 +195,7 @@ def test_lu_solve_in_parts_is_the_same(n, nrhs):
     assert out[0] == out[1] and torch.equal(X[0], X[1])
 
 
-@pytest.mark.parametrize("n,nrhs,alone", [(100, 400, 7), (127, 301, 300), (1030, 1500, 100), (777, 400, 30), (1028, 1500, 400)])
+@pytest.mark.parametrize("n,nrhs,alone", [(100, 400, 7), (127, 301, 300), (130, 2100, 60), (1030, 1500, 100), (777, 400, 30), (1028, 1500, 400)])
 def test_lu_solve_right_hand_sides_are_independent(n, nrhs, alone):
     """However many right-hand sides a wavefront or a launch takes, each one's bits are those of a solve of fewer."""
     gen = torch.Generator(device=DEV).manual_seed(n)
@@ -206,3 +206,17 @@ def test_lu_solve_right_hand_sides_are_independent(n, nrhs, alone):
     mfg.lu_solve(LU, ipiv, B)
     mfg.lu_solve(LU, ipiv, few)
     assert torch.equal(B[:, nrhs - alone:], few)
+
+
+@pytest.mark.parametrize("n,nrhs", [(64, 5), (37, 400), (1, 3)])
+def test_lu_solve_of_one_block_as_part_of_a_larger_one(n, nrhs):
+    """One block of rows goes without the words of the chain: the same bits as beside an identity."""
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    LU = torch.randn((n, n), device=DEV, generator=gen) + 16.0 * torch.eye(n, device=DEV)
+    B = torch.randn((n, nrhs), device=DEV, generator=gen)
+    ipiv, info = mfg.lu_factor(LU, "f32")
+    big, more, piv = torch.eye(130, device=DEV), torch.ones((130, nrhs), device=DEV), torch.arange(130, dtype=torch.int32, device=DEV)
+    big[:n, :n], more[:n], piv[:n] = LU, B, ipiv[:n]
+    mfg.lu_solve(LU, ipiv, B)
+    mfg.lu_solve(big, piv, more)
+    assert torch.equal(more[:n], B) and torch.equal(more[n:], torch.ones_like(more[n:]))
