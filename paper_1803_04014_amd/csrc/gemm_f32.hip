@@ -206,7 +206,7 @@ struct F32Cfg {
     static constexpr int A_INSTR = A_TILE / (64 * E) / NW, B_INSTR = B_TILE / (64 * E) / NW;
     static constexpr int LOADS = A_INSTR + B_INSTR;
     static_assert(A_TILE % (64 * 4 * NW) == 0 && B_TILE % (64 * 4 * NW) == 0, "tile must split into loads");
-    static_assert(BN == 32 || BN == 64 || BN == 128, "B rows of 128 to 512 bytes");
+    static_assert(BN == 64 || BN == 128, "B rows of 256 or 512 bytes");
     static_assert(S >= 2 && S <= 3 && S * STAGE * 4 <= 160 * 1024, "LDS budget");
     static_assert(LOADS * (S - 1) <= 63, "vmcnt range");
 };
@@ -215,8 +215,7 @@ struct F32Cfg {
 template <int BN>
 __device__ __forceinline__ int f32_b_at(int k, int n) {
     const int h = (k >> 2) & 1;
-    if constexpr (BN == 32) return (k ^ h) * 32 + n;
-    else return k * BN + (n ^ (h << 5));
+    return k * BN + (n ^ (h << 5));
 }
 
 template <int BM, int BN, int WM, int WN, int S, bool VEC, int OCC>
@@ -254,8 +253,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemmf32_ring(GemmF32Args p,
     for (int i = 0; i < G::B_INSTR; ++i) {
         const int at = ((wid * G::B_INSTR + i) * 64 + lane) * E, row = at / BN, n = at % BN;
         const int h = (row >> 2) & 1;
-        kb[i] = BN == 32 ? row ^ h : row;
-        const int64_t gn = n0 + (BN == 32 ? n : n ^ (h << 5));
+        kb[i] = row;
+        const int64_t gn = n0 + (n ^ (h << 5));
         offb[i] = (kb[i] * ldb + (gn < nlast ? gn : nlast) - n0) * 4;
     }
     auto load_lds = [](const char* src, float* dst) {

@@ -194,7 +194,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemmf8_pipe(GemmF8Args p, int ti
     using F = F8Frags<FM, FN>;
     __shared__ __attribute__((aligned(16))) uint8_t st0[G::STAGE];
     __shared__ __attribute__((aligned(16))) uint8_t st1[G::STAGE];
-    __shared__ __attribute__((aligned(16))) uint8_t st2[S == 3 ? G::STAGE : 16];
+    static_assert(S == 2, "two stages");
 
     int tm, tn;
     raster(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemmf8_pipe(GemmF8Args p, int ti
     const int wm = wid / WN, wn = wid % WN;
     const int64_t KTN = uniform64(K / BK);  // >= 1
     auto kclamp = [&](int64_t t) { return (t < KTN ? t : KTN - 1) * BK; };
-    auto stage = [&](int s) -> uint8_t* { return s == 0 ? st0 : s == 1 ? st1 : st2; };
+    auto stage = [&](int s) -> uint8_t* { return s == 0 ? st0 : st1; };
     // this wave's scale tiles (rows clamped like the operand rows)
     const int64_t ktiles = cdiv(K, MFG_FP8_TILE), ntiles = cdiv(N, MFG_FP8_TILE), mtiles = cdiv(M, MFG_FP8_TILE);
     int64_t mt = (m0 + wm * G::TMW) / MFG_FP8_TILE, nt = (n0 + wn * G::TNW) / MFG_FP8_TILE;
@@ -278,11 +278,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemmf8_pipe(GemmF8Args p, int ti
     for (int64_t t0 = 0; t0 < KFULL; t0 += S) {
         step(std::integral_constant<int, 0>{}, t0);
         step(std::integral_constant<int, 1>{}, t0 + 1);
-        if constexpr (S == 3) step(std::integral_constant<int, 2>{}, t0 + 2);
     }
     if (KFULL < KTN) step(std::integral_constant<int, 0>{}, KFULL);
-    if constexpr (S == 3)
-        if (KFULL + 1 < KTN) step(std::integral_constant<int, 1>{}, KFULL + 1);
 
     wait_vmcnt<0>();
     store_tile<FM, FN>(p.C, p.ldc, M, N, m0 + wm * G::TMW, n0 + wn * G::TNW, lane, p.alpha, p.beta,

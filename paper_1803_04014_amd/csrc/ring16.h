@@ -35,8 +35,7 @@ namespace mfg {
 // each of four consecutive rows; these place the four in different banks.
 template <int BN>
 __device__ __forceinline__ int ring_swz_b(int k) {
-    if constexpr (BN == 32) return k & 2;             // F = {0, 0, 2, 2}: rows of 4 chunks
-    else if constexpr (BN == 64) return (k & 3) * 2;  // F = {0, 2, 4, 6}: rows of 8
+    if constexpr (BN == 64) return (k & 3) * 2;  // F = {0, 2, 4, 6}: rows of 8
     else return swzB(k);
 }
 
@@ -77,8 +76,8 @@ struct RingCfg {
     static constexpr int LOADS = NPA * A_INSTR + NPB * B_INSTR;
     static constexpr int B_ROWS_PER_INSTR = 512 / BN, B_CPR = BN / 8;
     static_assert(A_PLANE % (512 * NW) == 0 && B_PLANE % (512 * NW) == 0, "tile must split into 1 KB loads");
-    static_assert(BN == 32 || BN == 64 || BN == 128, "B rows of 64, 128 or 256 bytes");
-    static_assert(S >= 2 && S <= 4, "2 to 4 stages");
+    static_assert(BN == 64 || BN == 128, "B rows of 128 or 256 bytes");
+    static_assert(S == 2 || S == 3, "2 or 3 stages");
     static_assert(S * STAGE * 2 <= 160 * 1024, "LDS budget");
     static_assert(LOADS * (S - 1) <= 63, "vmcnt range");
 };
@@ -155,7 +154,6 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm16_ring(Gemm16Args p, i
     __shared__ __attribute__((aligned(16))) uint16_t st0[G::STAGE];
     __shared__ __attribute__((aligned(16))) uint16_t st1[G::STAGE];
     __shared__ __attribute__((aligned(16))) uint16_t st2[S > 2 ? G::STAGE : 8];
-    __shared__ __attribute__((aligned(16))) uint16_t st3[S > 3 ? G::STAGE : 8];
 
     int tm, tn;
     raster(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, group_m, tm, tn);
@@ -173,7 +171,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm16_ring(Gemm16Args p, i
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid / WN, wn = wid % WN;
     const int64_t KTN = uniform64((K + 63) / 64);
-    auto stage = [&](int s) -> uint16_t* { return s == 0 ? st0 : (S == 2 || s == 1) ? st1 : (S == 3 || s == 2) ? st2 : st3; };
+    auto stage = [&](int s) -> uint16_t* { return s == 0 ? st0 : (S == 2 || s == 1) ? st1 : st2; };
 
     f32x16 hi[FM][FN], lo[FM][FN], rr[FM][FN];
 #pragma unroll
@@ -245,13 +243,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm16_ring(Gemm16Args p, i
         step(std::integral_constant<int, 0>{}, t);
         step(std::integral_constant<int, 1>{}, t + 1);
         if constexpr (S > 2) step(std::integral_constant<int, 2>{}, t + 2);
-        if constexpr (S > 3) step(std::integral_constant<int, 3>{}, t + 3);
     }
     if (whole < last) step(std::integral_constant<int, 0>{}, whole);
     if constexpr (S > 2)
         if (whole + 1 < last) step(std::integral_constant<int, 1>{}, whole + 1);
-    if constexpr (S > 3)
-        if (whole + 2 < last) step(std::integral_constant<int, 2>{}, whole + 2);
 
     // the last stage: nothing left to load, and the piece that straddles K to
     // clear (here and not in the loop: a divergent branch there made the

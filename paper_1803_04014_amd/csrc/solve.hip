@@ -181,14 +181,12 @@ __device__ __forceinline__ void memory_barrier() {
     __syncthreads();
 }
 
-// Over N = 4, 8 or 16 values held by lanes 0 .. N-1 and repeated by the lanes
-// after them: inside a 16-lane row by quad_perm xor 1, xor 2, then
-// row_half_mirror, row_mirror.
+// Over N = 4 or 8 values held by lanes 0 .. N-1 and repeated by the lanes after
+// them: by quad_perm xor 1, xor 2, then row_half_mirror.
 template <int N>
 __device__ __forceinline__ int keys_max_i32(int v) {
     v = dpp_max_i32<0x4E>(dpp_max_i32<0xB1>(v));
     if constexpr (N > 4) v = dpp_max_i32<0x141>(v);
-    if constexpr (N > 8) v = dpp_max_i32<0x140>(v);
     return __builtin_amdgcn_readfirstlane(v);
 }
 
@@ -207,6 +205,7 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
                                               LuMoves* moves) {
     static_assert(W % 8 == 0 && W <= kNb, "groups of eight columns");
     constexpr int NW = NT / 64, G = 8, NG = W / G;
+    static_assert(NW == 4 || NW == 8, "the wavefronts' candidate rows fit one register");
     __shared__ __attribute__((aligned(16))) int2 skey[2][NW];             // |value| bits (-1: none), place
     __shared__ __attribute__((aligned(16))) float srow[2][NW + 1][G];     // candidates, then the diagonal row
     __shared__ __attribute__((aligned(16))) float spiv[2][G][W];          // a group's pivot rows
@@ -294,10 +293,7 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
             // every wavefront's key and row with one LDS read each: lane q (and
             // q + NW, ...) holds key q, lane 8 q + k entry k of row q
             const int2 key = skey[buf][lane % NW];
-            constexpr int kRowRegs = (NW * G + 63) / 64;
-            float cand[kRowRegs];
-#pragma unroll
-            for (int e = 0; e < kRowRegs; ++e) cand[e] = (&srow[buf][0][0])[64 * e + (NW * G < 64 ? lane % (NW * G) : lane)];
+            const float cand = (&srow[buf][0][0])[lane % (NW * G)];
             const int pm = keys_max_i32<NW>(key.x);
             const float ra = 1.0f / __builtin_bit_cast(float, pm);
             int pi = c;
@@ -311,11 +307,7 @@ __global__ __launch_bounds__(NT, 1) void lu_sub(int rows, const float* in, int64
                 const int pw = __builtin_ctzll(best);
                 pi = __builtin_amdgcn_readlane(key.y, pw);
 #pragma unroll
-                for (int k = cc; k < G; ++k) {
-                    float v = lane_of(cand[0], pw * G % 64 + k);
-                    if constexpr (kRowRegs > 1) v = pw * G < 64 ? v : lane_of(cand[1], pw * G % 64 + k);
-                    pr[k] = v;
-                }
+                for (int k = cc; k < G; ++k) pr[k] = lane_of(cand, pw * G + k);
             } else {  // no candidate (every |value| NaN): the diagonal row
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
