@@ -1408,9 +1408,10 @@ constexpr int64_t kSubRows = 4096, kRows8 = (int64_t)kP8Threads * kP8Rows;
 static int sub_width(int64_t rows) { return rows <= 2048 ? 32 : 16; }
 
 // Floats of one copy of a sub-panel, and bytes of lu_factor_impl's device
-// scratch: two copies for lu_panel8 (each at least the 8 x 8 diagonal block that
-// lu_subpanel_post reads), of which lu_sub's narrow sub-panels use the first; the
-// panel's row moves; the origin of each row.
+// scratch: for lu_panel8 two copies of 8 columns (each at least the 8 x 8 diagonal
+// block that lu_subpanel_post reads), over which, as one of 16, lu_sub's narrow
+// sub-panels go once the rows left are few enough; the panel's row moves; the
+// origin of each row.
 static int64_t lu_copy_floats(int64_t n) { return n <= 2048 ? 0 : std::min(n, kRows8) * (n > kSubRows ? 8 : 16); }
 static int64_t lu_copies(int64_t n) { return n > kSubRows ? 2 : 1; }
 size_t lu_scratch_bytes(int64_t n) {
@@ -1497,6 +1498,7 @@ int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* inf
             float* const next = W < 32 ? copy : nullptr;
             if (next != nullptr) {
                 const int rows = (int)(n - j);
+                if (W != 16 || (int64_t)rows * W > lu_copy_floats(n) * lu_copies(n)) return MFG_ERR_INTERNAL;
                 hipLaunchKernelGGL(lu_sub_gather<16>, dim3(blocks((int64_t)rows * 2, 256)), dim3(256), 0, s, rows, A, lda, j,
                                    w, vec, next);
                 MFG_LAUNCH_CHECK();
@@ -1521,6 +1523,7 @@ int lu_factor_impl(int64_t n, float* A, int64_t lda, int32_t* ipiv, int32_t* inf
             }
         } else {
             if (n - j <= kRows8) {
+                if ((n - j) * 8 > lu_copy_floats(n) || lu_copies(n) < 2) return MFG_ERR_INTERNAL;
                 const int st = lu_panel_by_8(n, A, lda, j, w, vec, ipiv, info, copy, copy + lu_copy_floats(n), s);
                 if (st != MFG_OK) return st;
             } else {
