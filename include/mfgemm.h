@@ -265,12 +265,13 @@ int mfg_grouped_plan_create(int64_t count, const mfg_problem* problems, int mode
 /* Run the plan once on `stream` (one persistent kernel launch). */
 int mfg_grouped_run(mfg_grouped_plan* plan, float alpha, float beta, void* stream);
 /* Run the plan through a HIP graph: captured on first use for (alpha, beta,
- * stream), replayed afterwards.  The graph holds the plan's launch only. */
+ * stream), replayed afterwards.  The graph holds the plan's launches only. */
 int mfg_grouped_graph_launch(mfg_grouped_plan* plan, float alpha, float beta, void* stream);
 /* Total useful flops 2*sum(M*N*K) and algorithmic bytes of one run: the
  * operands read by the grouped kernel (both planes of the refined modes) and
  * C written, plus with MFG_IN_FP32 a conversion pass (FP32 read, 16-bit
- * planes written; counted alike where the kernel converts). */
+ * planes written).  By convention that pass is counted also for a plan whose
+ * kernel converts: what such a run moves is the FP32 operands and C. */
 int mfg_grouped_plan_info(const mfg_grouped_plan* plan, double* flops, double* bytes,
                           int64_t* work_items);
 int mfg_grouped_plan_destroy(mfg_grouped_plan* plan);
