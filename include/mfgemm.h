@@ -26,7 +26,8 @@
  *     alpha == 0 gives C = beta * C; when beta == 0, C is never read (NaN or
  *     Inf already in C do not propagate).  C must not overlap A or B.
  *   - Calls are thread-safe.  The library keeps one workspace per
- *     (device, stream) for the operands it converts, grown on demand with
+ *     (device, stream) for the operands it converts (preconverted FP8: for B's
+ *     codes laid out K-contiguous, where it can have it), grown on demand with
  *     hipMalloc and released at process exit.
  */
 #ifndef MFGEMM_H
@@ -163,7 +164,8 @@ int mfg_gemm_config(int64_t M, int64_t N, int64_t K,
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments and results (bitwise) as mfg_gemm.  The
  * operands the call converts (the FP32 inputs of the 16-bit, refined and
- * FP8 modes) go into a fixed per-device array of MFG_NOALLOC_SCRATCH_BYTES
+ * FP8 modes; preconverted FP8: B's codes laid out K-contiguous, if they fit)
+ * go into a fixed per-device array of MFG_NOALLOC_SCRATCH_BYTES
  * that the library holds on every device it runs on until the process
  * ends, instead of the per-stream workspace: the call makes no hipMalloc,
  * hipFree or other allocating call.  A call whose converted operands need
@@ -262,7 +264,8 @@ typedef struct mfg_grouped_plan mfg_grouped_plan;
  * `out` receives the plan (host). */
 int mfg_grouped_plan_create(int64_t count, const mfg_problem* problems, int mode,
                             mfg_grouped_plan** out);
-/* Run the plan once on `stream` (one persistent kernel launch). */
+/* Run the plan once on `stream`: one persistent kernel launch per tile class,
+ * after the conversion launch of a plan that has one. */
 int mfg_grouped_run(mfg_grouped_plan* plan, float alpha, float beta, void* stream);
 /* Run the plan through a HIP graph: captured on first use for (alpha, beta,
  * stream), replayed afterwards.  The graph holds the plan's launches only. */

@@ -294,8 +294,10 @@ __device__ __forceinline__ void grouped_barrier() {
 // bitwise those of a conversion pass.  A piece is then two 16-byte loads (as
 // many registers as two planes); its resource ends with the tile's last row,
 // past which the hardware answers each dword with zero.  4096 problems of
-// 16..512 per side, SPLIT3: 344 us against 247 for a pass and 370 on its planes;
-// bound by the latency of a tile's few K blocks, not by the conversions.
+// 16..512 per side, SPLIT3: 341 us against 579 with a pass (240, and 342 on its
+// planes), F16 258 against 369.  Bound by mixed reads and writes (3.5 TB/s,
+// two thirds of a copy's rate) together with the conversions, which every tile
+// that reads an element makes: 45% of the wavefronts' cycles issue, on planes 28%.
 template <int KIND, bool VEC, int TT, bool F32>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(grouped_wg_per_cu<KIND, TT>()))) void gemm16_grouped(
     const GroupedWork* work, const int64_t* planes, GroupedSplit split, float alpha, float beta) {

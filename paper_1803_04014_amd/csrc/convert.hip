@@ -483,7 +483,8 @@ int launch_convert_jobs(const ConvJob* jobs, const ConvTask* tasks, int64_t ntas
 // wavefront that holds one takes f32_to_e4m3_sat.  (That for all, 25
 // instructions per element: both 4096^2 operands 39 us, a 128^2 pair 14; the
 // instruction: 26 and 4.3.)  HBM-bound when large: 4 B read and 1 B written per
-// element, 32 us at the copy rate.
+// element; those 26 us are 6.4 TB/s, above the 5.2 of a large copy, as part of
+// the 134 MB read is still in the last cache.
 __global__ __launch_bounds__(256) void quant_fp8_kernel(QuantJob ja, QuantJob jb, uint32_t tiles_a) {
     const bool second = blockIdx.x >= tiles_a;
     const QuantJob& j = second ? jb : ja;
