@@ -66,9 +66,10 @@ static const Cost kCostSplit4[] = {
 };
 
 // What a problem adds to the candidates' figures: factors on the ring kernels'
-// full stages and on their part of C, and whether K is whole stages.
+// full stages, on their part of C and on their whole time, and whether K is
+// whole stages.
 struct ProblemCost {
-    double stage = 1.0, c = 1.0;
+    double stage = 1.0, c = 1.0, ring = 1.0;
     bool ragged = false;
 };
 
@@ -82,7 +83,7 @@ static double cost_of(const Cost& c, int64_t M, int64_t N, int64_t stages, int64
     const double n = rounds <= 1.0 ? 1.0 : rounds <= 4.0 ? std::ceil(rounds) : rounds + 0.5;
     if (c.shared) {
         const double full = std::ceil(rounds) * each * add.stage;
-        return c.start + (ctime + c.tile) * rounds * add.c + k * (n == 1.0 || full < first ? first : full);
+        return add.ring * (c.start + (ctime + c.tile) * rounds * add.c + k * (n == 1.0 || full < first ? first : full));
     }
     double sum = n * each;
     if (n == 1.0) sum = first;
@@ -122,6 +123,10 @@ static const Cost& pick16(int kind, int64_t M, int64_t N, int64_t K, int64_t bat
     const double operands = 2.0 * (double)batch * (double)K * (planes_a * (double)M + planes_b * (double)N);
     if (operands > 256e6) add.stage *= 1.3;
     if (plain && 4.0 * (double)batch * (double)M * (double)N > 256e6) add.c = 1.3;
+    // a long K: the pipelined kernels where the two are as good as equal, as the
+    // ring's time varies more from shape to shape (F16 1920 x 1024 x 6400, estimated
+    // 41.0 and 41.5 us, 46.8 on the ring and 43.1 on 128 x 128)
+    if (plain && K >= 24 * 64) add.ring = 1.03;
     return least_cost(c, n, M, N, cdiv(K, 64), batch, add, ring_only);
 }
 

@@ -88,6 +88,7 @@ def test_16_bit(mode, M, N, K, simple):
 # us of a call on preconverted operands: every configuration of the rule
 @pytest.mark.parametrize("mode,M,N,K,config", [
     ("bf16", 1792, 832, 10368, 28),      # 6: 66, 28: 60
+    ("f16", 1920, 1024, 6400, 28),       # 6: 46.8, 28: 43.1
     ("f16", 4860, 5751, 716, 29),        # 6: 75.6, 28: 83.7, 30: 79.7, 29: 62.8
     ("f16", 2752, 42432, 128, 29),       # 6: 111, 28: 158, 30: 135, 29: 123
     ("f16", 4374, 12087, 115, 6),        # 6: 51, 28: 71, 30: 68, 29: 63
