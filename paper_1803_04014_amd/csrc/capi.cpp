@@ -629,17 +629,17 @@ static int grouped_class(int m, int kind, int64_t M, int64_t N, int64_t K, int f
 }
 
 // Whether a plan's FP32 operands are converted in the grouped kernel instead
-// of by a pass before it, where that costs less.  The pass is a launch and 6 or
-// 8 bytes per element at the copy rate.  In the kernel every tile that reads an
-// element converts it: per 64-deep block of K that adds to the tile's chain of
-// loads and stores, 0.55 us to a 128 x 128 tile (1.25 past K = 4096) and
+// of by a pass before it, where that costs less.  The pass is a launch (3.5 us)
+// and 6 or 8 bytes per element at the copy rate.  In the kernel every tile that
+// reads an element converts it: per 64-deep block of K that adds to the tile's
+// chain of loads and stores, 0.55 us to a 128 x 128 tile (1.25 past K = 4096) and
 // 0.27 to a 64 x 64 tile, or, with many tiles, their sum over the CUs, 0.8 and
-// 0.16 (REFINE_A 1.43 times that past sides of 512).  us, with pass and without, SPLIT3
-// and F16: 4096 problems of 128^3 356 -> 174 and 251 -> 160, 256 of 512^3 586 ->
-// 483 and 283 -> 235, 128 of 768^3 848 -> 796 and 375 -> 342; a long K or few
-// tiles are the other way round: F16 4 of 128 x 128 x 32768 517 and 761, one of
-// 256 x 256 x 2048 38 and 47, 18 of 768 x 768 x 8192 559 and 643 (of 280 plans the
-// choice costs 0.2% on average, the kernel alone 9.5%, the pass alone 11.7%).
+// 0.16 (REFINE_A 1.43 times that past sides of 512).  us, with pass and without,
+// SPLIT3 and F16: 4096 problems of 128^3 356 -> 174 and 251 -> 160, 256 of 512^3
+// 586 -> 483 and 283 -> 235, 128 of 768^3 848 -> 796 and 375 -> 342; a long K or
+// few tiles are the other way round: F16 4 of 128 x 128 x 32768 517 and 761, one
+// of 256 x 256 x 2048 38 and 47, 18 of 768 x 768 x 8192 559 and 643 (of 280 plans
+// the choice costs 0.1% on average, the kernel alone 9.5%, the pass alone 11.7%).
 // Only without a C that overlaps an operand: the pass reads all of them before
 // any C is written.
 static bool grouped_converts(int64_t count, const mfg_problem* probs, int m, int force_tile) {
@@ -658,7 +658,7 @@ static bool grouped_converts(int64_t count, const mfg_problem* probs, int m, int
         longest = std::max(longest, (tile == 128 ? 0.5 : 1.0) * each * blocks);
         chain = std::max(chain, link * blocks);
     }
-    return std::max(chain, sum + longest) < 2.5 + bytes / 5.3e6;
+    return std::max(chain, sum + longest) < 3.5 + bytes / 5.3e6;
 }
 
 static bool grouped_direct(int64_t count, const mfg_problem* probs, int m, int force_tile) {

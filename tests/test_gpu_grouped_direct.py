@@ -73,6 +73,7 @@ def test_output_overlapping_an_operand(mode):
 @pytest.mark.parametrize("mode,count,M,N,K,in_kernel", [
     ("f16", 4, 128, 128, 32768, False),   # 517, 761
     ("f16", 64, 512, 512, 512, True),     # 68, 49
+    ("f16", 16, 768, 768, 512, True),     # 39, 36
     ("bf16", 2, 256, 256, 8192, False),   # 130 to 141, 188 to 191
     ("split3", 64, 128, 128, 2048, True),  # 75, 41
     ("refine_a", 16, 768, 768, 8192, False),  # 810, 899
