@@ -323,17 +323,16 @@ int mfg_lu_factor(int64_t n, float* A, int64_t lda, int32_t* ipiv, int64_t* info
 /* mfg_lu_solve -- B = (L U)^-1 P B in place for the n x nrhs FP32 B (device,
  * ldb >= max(1, nrhs)) with the factors and pivots of mfg_lu_factor: the
  * permutation, then forward and backward substitution by 64-row blocks, one
- * launch each (n < 128 with more than 300 right-hand sides, and some n < 192,
- * one per block; beyond 65535 right-hand sides block by block with the updates
- * by FP32 mfg_gemm).  Allocates an n x nrhs FP32 work array, the permutation
- * and, where the substitution is one launch of more than one block, n x nrhs
- * 8-byte words (2^30 at most, and fewer where memory is short: the right-hand
- * sides are then solved in parts, with the same results).  B's contents are
- * unspecified after an error.  Synchronises `stream`.
+ * launch each (n < 128 with more than 300 right-hand sides, some n < 192, more
+ * than 2^30 elements of B, or without memory for the words below: one per
+ * block, with the same results; beyond 65535 right-hand sides block by block
+ * with the updates by FP32 mfg_gemm).  Allocates an n x nrhs FP32 work array,
+ * the permutation and, where the substitution is one launch of more than one
+ * block, n x nrhs 8-byte words.  B's contents are unspecified after an error.
+ * Synchronises `stream`.
  * Errors: MFG_ERR_INVALID_ARG (negative sizes, ldlu < max(1, n), ldb < max(1,
  * nrhs), NULL pointers, ipiv not of a factorisation); MFG_ERR_UNSUPPORTED for
- * nrhs > 2^31 - 1; MFG_ERR_NO_MEMORY without memory for one right-hand side's
- * words beside the rest. */
+ * nrhs > 2^31 - 1; MFG_ERR_NO_MEMORY. */
 int mfg_lu_solve(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* ipiv, float* B, int64_t ldb,
                  void* stream);
 /* mfg_solve_ir -- X (n x nrhs FP64, device, ldx >= max(1, nrhs)) solving
@@ -519,8 +518,8 @@ int mfg_probe_mfma(int shape, const void* operands, int64_t workgroups, int64_t 
  * launch_n-th GEMM kernel launch (mfg_gemm, batched, grouped; conversions
  * are not counted) fails with MFG_ERR_HIP (hipErrorLaunchFailure) without
  * launching, and the alloc_n-th device allocation (a workspace growing, a
- * served request's operand storage, the words of mfg_lu_solve and
- * mfg_solve_ir) fails with MFG_ERR_NO_MEMORY, each once;
+ * served request's operand storage; the words of mfg_lu_solve and
+ * mfg_solve_ir, which then do without) fails with MFG_ERR_NO_MEMORY, each once;
  * 0 disarms.  Process-wide.  The environment variable
  * MFG_FAULT=launch:<n>,alloc:<n> arms the same at the library's first call
  * and at every mfg_server_create.  The dry-run server (device = -1) meets

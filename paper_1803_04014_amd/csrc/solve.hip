@@ -1562,12 +1562,11 @@ static int permutation(int64_t n, const int32_t* ipiv, std::vector<int32_t>& per
     return MFG_OK;
 }
 
-// Device words of lu_chain for `cols` right-hand sides at a time (n x cols
-// published unknowns and the ticket counter) and what its launches so far have
-// used of them; none where lu_substitute goes block by block.
+// Device words of lu_chain (n x nrhs published unknowns and the ticket
+// counter) and what its launches so far have used of them; none where
+// lu_substitute does without.
 struct ChainWords {
     unsigned long long* z = nullptr;
-    int64_t cols = 0;
     uint32_t tag = 0, tickets = 0;
 };
 // Two blocks, the second not whole, and many right-hand sides: one launch per
@@ -1580,11 +1579,10 @@ static bool subst_by_steps(int64_t n, int64_t nrhs) {
     if (n <= kNb || n >= 3 * kNb || nrhs > 65535) return false;
     return n < 2 * kNb ? nrhs > 300 : n * nrhs > (1 << 18) && n * nrhs <= (1 << 19);
 }
-static int64_t chain_cols(int64_t n, int64_t nrhs) {
-    if (n <= kNb || nrhs > 65535 || subst_by_steps(n, nrhs)) return 0;
-    return std::min(nrhs, std::max<int64_t>(1, ((int64_t)1 << 30) / n));
+static size_t chain_words(int64_t n, int64_t nrhs) {
+    if (n <= kNb || nrhs > 65535 || n * nrhs > (int64_t)1 << 30 || subst_by_steps(n, nrhs)) return 0;
+    return (size_t)(n * nrhs + 1);
 }
-static size_t chain_words(int64_t n, int64_t cols) { return cols > 0 ? (size_t)(n * cols + 1) : 0; }
 // Right-hand sides per wavefront of lu_chain.  One wavefront's chain is the
 // shortest with one of them; past the wavefronts that the chip holds, more share
 // the loads of the factors, and all the earlier where rows are read an element
@@ -1599,32 +1597,29 @@ static int chain_rhs(int64_t nblk, int64_t nrhs, bool vec) {
 }
 // V = U^-1 L^-1 V (V: n x nrhs FP32, already permuted) in FP32, in place:
 // with Y as large as scratch; forward and backward substitution by blocks of kNb
-// rows, one launch each (lu_chain), for as many right-hand sides at a time as there are words for;
-// each one's result is the same whatever their number.  One block of rows needs
-// no words; beyond 65535 right-hand sides block by block: the diagonal block
-// (lu_trsv_block), then the rest of V by an FP32 mfg_gemm.
+// rows, one launch each (lu_chain) or, without its words, one per block
+// (lu_subst_step), with the same results.  One block of rows needs neither; beyond
+// 65535 right-hand sides block by block: the diagonal block (lu_trsv_block), then
+// the rest of V by an FP32 mfg_gemm.
 static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, float* V, int64_t ldv, float* Y,
                          int64_t ldy, ChainWords& c, hipStream_t s) {
     const int64_t nblk = (n + kNb - 1) / kNb;
     const int vec = ldlu % 4 == 0 && reinterpret_cast<uintptr_t>(LU) % 16 == 0;
     if (c.z != nullptr) {
-        uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * c.cols);
-        for (int64_t q = 0; q < nrhs; q += c.cols) {
-            const int64_t cols = std::min(c.cols, nrhs - q);
-            const int R = chain_rhs(nblk, cols, vec != 0);
-            const uint32_t grid = (uint32_t)(nblk * ((cols + R - 1) / R));
-            for (int lower = 1; lower >= 0; --lower) {
-                auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : R == 2 ? lu_chain<true, 2> : lu_chain<true, 1>)
-                                     : (R == 4 ? lu_chain<false, 4> : R == 2 ? lu_chain<false, 2> : lu_chain<false, 1>);
-                hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, cols, (int)nblk, V + q, ldv, c.z,
-                                   ++c.tag, ticket, c.tickets, vec);
-                MFG_LAUNCH_CHECK();
-                c.tickets += grid;
-            }
+        const int R = chain_rhs(nblk, nrhs, vec != 0);
+        const uint32_t grid = (uint32_t)(nblk * ((nrhs + R - 1) / R));
+        uint32_t* ticket = reinterpret_cast<uint32_t*>(c.z + n * nrhs);
+        for (int lower = 1; lower >= 0; --lower) {
+            auto* kernel = lower ? (R == 4 ? lu_chain<true, 4> : R == 2 ? lu_chain<true, 2> : lu_chain<true, 1>)
+                                 : (R == 4 ? lu_chain<false, 4> : R == 2 ? lu_chain<false, 2> : lu_chain<false, 1>);
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kNb), 0, s, LU, ldlu, n, nrhs, (int)nblk, V, ldv, c.z, ++c.tag,
+                               ticket, c.tickets, vec);
+            MFG_LAUNCH_CHECK();
+            c.tickets += grid;
         }
         return MFG_OK;
     }
-    if (subst_by_steps(n, nrhs)) {
+    if (n > kNb && nrhs <= 65535) {
         for (int64_t b = 0; b < n; b += kNb) {  // forward, unit lower: V -> Y
             const int w = (int)std::min<int64_t>(kNb, n - b);
             hipLaunchKernelGGL(lu_subst_step<true>, dim3(blocks(n - b - w, 256), (unsigned)nrhs), dim3(256), 0, s, LU,
@@ -1667,7 +1662,7 @@ static int lu_substitute(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu,
 // unspecified afterwards.  The chain's words are cleared the first time.
 static int lu_solve_impl(int64_t n, int64_t nrhs, const float* LU, int64_t ldlu, const int32_t* dperm, float* B,
                          int64_t ldb, float* X, int64_t ldx, ChainWords& c, hipStream_t s) {
-    const int64_t words = c.tag == 0 ? (int64_t)chain_words(n, c.cols) : 0;
+    const int64_t words = c.z != nullptr && c.tag == 0 ? (int64_t)chain_words(n, nrhs) : 0;
     hipLaunchKernelGGL(gather_rows, dim3(blocks(n * nrhs, 256)), dim3(256), 0, s, n, nrhs, dperm, B, ldb, X, ldx, c.z,
                        words);
     MFG_LAUNCH_CHECK();
@@ -1695,27 +1690,24 @@ struct Buffers {
         ptrs.push_back(*p);
         return MFG_OK;
     }
-    // `lead` bytes and the chain's words, these without memory for all right-hand
-    // sides at once for half of them, and so on.  One allocation, as a second one
-    // and its free are 6 of the 55 us of a small mfg_lu_solve; but two where that
-    // keeps the words within 2 MB, past which an allocation is 40 us (n = 192, 1000
-    // right-hand sides: 157 us with one, 120 with two).
+    // `lead` bytes and, if there is memory for them, the chain's words.  One
+    // allocation, as a second one and its free are 6 of the 55 us of a small
+    // mfg_lu_solve; but two where that keeps the words within 2 MB, past which an
+    // allocation is 40 us (n = 192, 1000 right-hand sides: 157 us with one, 120
+    // with two).
     int get_with_chain(char** p, size_t lead, int64_t n, int64_t nrhs, ChainWords& c) {
         constexpr size_t kSmall = (size_t)2 << 20;
+        const size_t words = chain_words(n, nrhs) * sizeof(*c.z);
         lead = (lead + 255) / 256 * 256;
-        *p = nullptr;
-        for (c.cols = chain_cols(n, nrhs);; c.cols = (c.cols + 1) / 2) {
-            const size_t words = chain_words(n, c.cols) * sizeof(*c.z);
-            const bool two = lead + words > kSmall && words <= kSmall && words > 0;
-            int st = fault_hit(kFaultAlloc) ? MFG_ERR_NO_MEMORY : MFG_OK;
-            if (st == MFG_OK && (!two || *p == nullptr)) st = get(p, two ? lead : lead + words);
-            if (st == MFG_OK && words > 0) {
-                if (two) st = get(&c.z, (size_t)(n * c.cols + 1));
+        if (words > 0 && !fault_hit(kFaultAlloc)) {
+            const bool two = lead + words > kSmall && words <= kSmall;
+            if (get(p, two ? lead : lead + words) == MFG_OK) {
+                if (two) (void)get(&c.z, chain_words(n, nrhs));
                 else c.z = reinterpret_cast<unsigned long long*>(*p + lead);
+                return MFG_OK;
             }
-            if (st == MFG_OK) return MFG_OK;
-            if (c.cols <= 1) return st;
         }
+        return get(p, lead);
     }
     ~Buffers() {
         for (void* p : ptrs) (void)hipFree(p);
